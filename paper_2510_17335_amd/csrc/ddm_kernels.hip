@@ -47,6 +47,12 @@ __device__ __forceinline__ uint32_t first_tile(const TileList& tl, uint32_t* slo
   __syncthreads();
   return __builtin_amdgcn_readfirstlane(*slot);
 }
+// The record of tile t in scalar registers (t is the same for the workgroup).
+__device__ __forceinline__ TileRec tile_record(const TileList& tl, uint32_t t) {
+  const TileRec r = tl.list[t];
+  return TileRec{(uint32_t)__builtin_amdgcn_readfirstlane(r.start), (uint32_t)__builtin_amdgcn_readfirstlane(r.end),
+                 (uint32_t)__builtin_amdgcn_readfirstlane(r.tile)};
+}
 __device__ __forceinline__ void finish_tiles(const TileList& tl) {
   if (!tl.queue || threadIdx.x != 0) return;
   __threadfence();
@@ -81,7 +87,29 @@ __device__ __forceinline__ int64_t node_of(const int base[3], int o0, int o1, in
                 : ((int64_t)(base[0] + o0) * n + (base[1] + o1)) * n + (base[2] + o2);
 }
 
-template <typename T> __device__ __forceinline__ T ld(const void* p, int64_t i) { return static_cast<const T*>(p)[i]; }
+// Byte offset of node (i0, i1[, i2]) in its instance's grid (at most 2^29: 32
+// bits), and the base of stencil row (o0[, o1]), which is the same for every
+// thread.  Row base plus one 32-bit offset per particle: the 3^D loads of a
+// gather need no 64-bit address arithmetic of their own (k_g2p spent 140 of
+// its 627 vector instructions on it, 65 of them quarter-rate multiplies).
+template <typename T, int D> __device__ __forceinline__ uint32_t node_bytes(const KCfg& c, const int i[3]) {
+  uint32_t k = ((uint32_t)i[0] << c.nlog2) + (uint32_t)i[1];
+  if (D == 3) k = (k << c.nlog2) + (uint32_t)i[2];
+  return k * (uint32_t)(kNodeVals * sizeof(T));
+}
+template <typename T, int D>
+__device__ __forceinline__ const Global<T>* stencil_row(const KCfg& c, const T* g, int o0, int o1) {
+  return scalar_base(g + (int64_t)(D == 3 ? (o0 << (2 * c.nlog2)) + (o1 << c.nlog2) : o0 << c.nlog2) * kNodeVals);
+}
+template <typename T> __device__ __forceinline__ const Global<T>* at_bytes(const Global<T>* p, uint32_t off) {
+  return (const Global<T>*)((const Global<char>*)p + off);
+}
+template <typename T> __device__ __forceinline__ T* at_bytes(T* p, uint32_t off) {
+  return reinterpret_cast<T*>(reinterpret_cast<char*>(p) + off);
+}
+template <typename T> __device__ __forceinline__ const T* at_bytes(const T* p, uint32_t off) {
+  return reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + off);
+}
 
 // Row of entry (a, b) of a symmetric D x D matrix stored as its upper triangle.
 template <int D> __device__ __forceinline__ int sym_row(int a, int b) {
@@ -98,6 +126,16 @@ __device__ __forceinline__ Node4<float> ld_node(const float* p) {
 }
 __device__ __forceinline__ Node4<double> ld_node(const double* p) {
   const double2 a = reinterpret_cast<const double2*>(p)[0], b = reinterpret_cast<const double2*>(p)[1];
+  return Node4<double>{{a.x, a.y, b.x, b.y}};
+}
+__device__ __forceinline__ Node4<float> ld_node(const Global<float>* p) {
+  typedef float F4 __attribute__((ext_vector_type(4)));
+  const F4 q = *(const Global<F4>*)p;
+  return Node4<float>{{q.x, q.y, q.z, q.w}};
+}
+__device__ __forceinline__ Node4<double> ld_node(const Global<double>* p) {
+  typedef double D2 __attribute__((ext_vector_type(2)));
+  const D2 a = ((const Global<D2>*)p)[0], b = ((const Global<D2>*)p)[1];
   return Node4<double>{{a.x, a.y, b.x, b.y}};
 }
 __device__ __forceinline__ void st_node(float* p, float a, float b, float c, float d) {
@@ -322,7 +360,7 @@ __device__ __forceinline__ bool p2g_particle(const KCfg& c, const Bufs& b, const
 #pragma unroll
     for (int a = 0; a < D; ++a)
 #pragma unroll
-      for (int bb = a; bb < D; ++bb) tau_out[(int64_t)sym_row<D>(a, bb) * c.ntot + p] = tau[a][bb];
+      for (int bb = a; bb < D; ++bb) scalar_base(tau_out + (int64_t)sym_row<D>(a, bb) * c.ntot)[p] = tau[a][bb];
   }
   const T k_str = -dt * T(I.Vp) * T(4.0 * c.inv_dx * c.inv_dx);
 #pragma unroll
@@ -557,10 +595,9 @@ __global__ void __launch_bounds__(kBlock) k_p2g(KCfg c, Bufs b, TileList tl, con
   __shared__ double win[Win<D>::stride * kNodeVals];
   __shared__ RunLDS<T> rl;
   const uint32_t ntiles = *tl.count;
-  const P<T, D> si = pv<T, D>(st_in, c.ntot), so = pv<T, D>(st_out, c.ntot);
   __shared__ uint32_t tile_slot;
   for (uint32_t t = first_tile(tl, &tile_slot); t < ntiles; t = next_tile(tl, t, &tile_slot)) {
-    const TileRec tr = tl.list[t];
+    const TileRec tr = tile_record(tl, t);
     int inst, org[3];
     tile_origin<D>(c, tr.tile, inst, org);
     const InstDev& I = b.inst[inst];
@@ -572,10 +609,11 @@ __global__ void __launch_bounds__(kBlock) k_p2g(KCfg c, Bufs b, TileList tl, con
       const int rc = min(kBlock, cnt - r0);
       int wb = -1;
       if (threadIdx.x < rc) {
-        const int64_t p = (int64_t)tr.start + r0 + threadIdx.x;
+        const int64_t p0 = (int64_t)tr.start + r0;
+        const P<T, D> si = pv<T, D>(st_in, c.ntot).at(p0), so = pv<T, D>(st_out, c.ntot).at(p0);
         Stencil<T, D> S;
         T A[3][3], vel[3];
-        if (p2g_particle<T, D>(c, b, I, inst, si, so, p, S, A, vel, tau_out)) {
+        if (p2g_particle<T, D>(c, b, I, inst, si, so, threadIdx.x, S, A, vel, tau_out ? tau_out + p0 : nullptr)) {
           // node o receives w_o (q + B o) and w_o m_p with q = m_p v - A f dx and
           // B = A dx (the MLS-MPM momentum m_p v + A (x_i - x_p), x_i - x_p = (o - f) dx)
           T q[3] = {T(0), T(0), T(0)}, B[3][3] = {{T(0), T(0), T(0)}, {T(0), T(0), T(0)}, {T(0), T(0), T(0)}};
@@ -899,7 +937,7 @@ __device__ __forceinline__ void particle_collision(const KCfg& c, const Bufs& b,
 // of its instance, the particle-level collision when PC, and the advanced
 // position.  Returns false when the advance leaves the fixed-point range or
 // the result is not finite (the caller flags it).  Computing everything
-// before the stores lets the compiler keep the kernel at 89 registers.
+// before the stores keeps the kernel at few registers.
 template <typename T, int D, bool PC>
 __device__ __forceinline__ bool g2p_compute(const KCfg& c, const Bufs& b, int inst, int step, const P<T, D>& si,
                                             int64_t p, const Stencil<T, D>& S, const T* __restrict__ g, T (&vn)[3],
@@ -918,16 +956,18 @@ __device__ __forceinline__ bool g2p_compute(const KCfg& c, const Bufs& b, int in
   for (int a = 0; a < 3; ++a)
 #pragma unroll
     for (int k = 0; k < 3; ++k) rr[a][k] = a < D ? (T(k) - S.f[a]) * dx : T(0);
+  const uint32_t nb = node_bytes<T, D>(c, S.base);
 #pragma unroll
   for (int o0 = 0; o0 < 3; ++o0)
 #pragma unroll
     for (int o1 = 0; o1 < (D == 3 ? 3 : 1); ++o1) {
       const T wxy = S.w[0][o0] * (D == 3 ? S.w[1][o1] : T(1));
+      const Global<T>* row = stencil_row<T, D>(c, g, o0, o1);
       T u[3] = {T(0), T(0), T(0)}, ul[3] = {T(0), T(0), T(0)};
 #pragma unroll
       for (int ol = 0; ol < 3; ++ol) {
         const T wl = S.w[D - 1][ol], wr = wl * rr[D - 1][ol];
-        const Node4<T> nd = ld_node(g + (D == 3 ? node_of<D>(S.base, o0, o1, ol, c.n) : node_of<D>(S.base, o0, ol, 0, c.n)) * kNodeVals);
+        const Node4<T> nd = ld_node(at_bytes(row, nb) + ol * kNodeVals);
 #pragma unroll
         for (int a = 0; a < D; ++a) { u[a] += wl * nd.v[a]; ul[a] += wr * nd.v[a]; }
       }
@@ -962,16 +1002,19 @@ __device__ __forceinline__ bool g2p_compute(const KCfg& c, const Bufs& b, int in
 // ---------------------------------------------------------------------------
 // PC: with the particle-level collision (a separate instance, so that the
 // plain kernel keeps its register budget).
-// In FP32 without the particle-level collision the kernel fits 80 registers
-// with no spills: 6 waves per SIMD, more gathers in flight.
+// In FP32 without the particle-level collision the kernel fits 64 registers
+// with no spills: 8 waves per SIMD, more gathers in flight.  It is bound by
+// memory: 45 us for 1.8 M particles, 120 B each, against 36 us for a copy of
+// those bytes at 6 TB/s.
 template <typename T, int D, bool PC>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(PC || sizeof(T) == 8 ? 1 : 6)))
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(PC || sizeof(T) == 8 ? 1 : 8)))
 k_g2p(KCfg c, Bufs b, int step, const void* st_in, void* st_out, const T* __restrict__ post) {
   const int inst = b.blk_inst[blockIdx.x];
   const InstDev& I = b.inst[inst];
-  const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const P<T, D> si = pv<T, D>(st_in, c.ntot), so = pv<T, D>(st_out, c.ntot);
-  if (p - I.off >= I.n) {
+  const int64_t p0 = (int64_t)blockIdx.x * kBlock;
+  const uint32_t p = threadIdx.x;
+  const P<T, D> si = pv<T, D>(st_in, c.ntot).at(p0), so = pv<T, D>(st_out, c.ntot).at(p0);
+  if ((int64_t)p >= I.n - (p0 - I.off)) {
     // padding slots keep a harmless position so they never trip a check
 #pragma unroll
     for (int a = 0; a < D; ++a) so.xr(a, p) = Pos<T>::from_real(0.5);
@@ -1349,14 +1392,12 @@ __global__ void __launch_bounds__(kBlock) k_g2p_adj(KCfg c, Bufs b, TileList tl,
   __shared__ RunLDS<T> rl;
   __shared__ alignas(16) T gwin[Win<D>::nodes][kNodeVals];     // grid velocities of the tile's window
   const uint32_t ntiles = *tl.count;
-  const P<T, D> st = pv<T, D>(stv, c.ntot);
-  const Adj<T, D> an = av<T, D>(adj_next, c.ntot), ac = av<T, D>(adj_cur, c.ntot);
   const T dx = T(c.dx), inv_dx = T(c.inv_dx), Dk = T(4.0 * c.inv_dx * c.inv_dx);
   constexpr int WS = Win<D>::stride;
   // a plain grid-stride loop: the work queue's loop form costs this kernel ten
   // registers and a wave per SIMD
   for (uint32_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    const TileRec tr = tl.list[t];
+    const TileRec tr = tile_record(tl, t);
     int inst, org[3];
     tile_origin<D>(c, tr.tile, inst, org);
     const InstDev& I = b.inst[inst];
@@ -1373,7 +1414,7 @@ __global__ void __launch_bounds__(kBlock) k_g2p_adj(KCfg c, Bufs b, TileList tl,
 #pragma unroll
       for (int a = 0; a < D; ++a) ok &= gi[a] >= 0 && gi[a] < c.n;
       Node4<T> v = {{T(0), T(0), T(0), T(0)}};
-      if (ok) v = ld_node(g + node_of<D>(gi, 0, 0, 0, c.n) * kNodeVals);
+      if (ok) v = ld_node(at_bytes(g, node_bytes<T, D>(c, gi)));
       st_node(gwin[i], v.v[0], v.v[1], v.v[2], v.v[3]);
     }
     __syncthreads();
@@ -1383,7 +1424,10 @@ __global__ void __launch_bounds__(kBlock) k_g2p_adj(KCfg c, Bufs b, TileList tl,
     int wb = -1;
     do {
       if (threadIdx.x >= rc) break;
-      const int64_t p = (int64_t)tr.start + r0 + threadIdx.x;
+      const int64_t p0 = (int64_t)tr.start + r0;
+      const uint32_t p = threadIdx.x;
+      const P<T, D> st = pv<T, D>(stv, c.ntot).at(p0);
+      const Adj<T, D> an = av<T, D>(adj_next, c.ntot).at(p0), ac = av<T, D>(adj_cur, c.ntot).at(p0);
       Stencil<T, D> S;
       if (!make_stencil<T, D>(st, p, c, S)) break;
       T xb[3], vb[3], Cb[3][3];
@@ -1496,7 +1540,7 @@ __global__ void __launch_bounds__(kBlock) k_g2p_adj(KCfg c, Bufs b, TileList tl,
       for (int a = 0; a < D; ++a) any |= win[a * WS + wi] != 0.0;
       if (!any) continue;
       const int gbase[3] = {org[0] + l[0], org[1] + l[1], D == 3 ? org[2] + l[2] : 0};
-      T* dst = gbv + node_of<D>(gbase, 0, 0, 0, c.n) * kNodeVals;
+      T* dst = at_bytes(gbv, node_bytes<T, D>(c, gbase));
 #pragma unroll
       for (int a = 0; a < D; ++a) atomicAdd(dst + a, (T)win[a * WS + wi]);
     }
@@ -1801,15 +1845,17 @@ __device__ __forceinline__ void ftmp_of(const P<T, D>& st, int64_t p, T dt, T Cm
 }
 
 template <typename T, int D, bool SF>
-__global__ void __launch_bounds__(kBlock) k_p2g_adj_gather(KCfg c, Bufs b, const void* stv, const T* __restrict__ tau,
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1))) k_p2g_adj_gather(KCfg c, Bufs b, const void* stv, const T* __restrict__ tau,
                                                            const T* __restrict__ gbar, void* adj_cur, double* pacc) {
   const int inst = b.blk_inst[blockIdx.x];
   const InstDev& I = b.inst[inst];
-  const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  const int64_t p0 = (int64_t)blockIdx.x * kBlock;
+  const uint32_t p = threadIdx.x;
   double acc[1] = {0.0};
-  if (p - I.off < I.n) {
-    const P<T, D> st = pv<T, D>(stv, c.ntot);
-    const Adj<T, D> ac = av<T, D>(adj_cur, c.ntot);
+  if ((int64_t)p < I.n - (p0 - I.off)) {
+    const P<T, D> st = pv<T, D>(stv, c.ntot).at(p0);
+    const Adj<T, D> ac = av<T, D>(adj_cur, c.ntot).at(p0);
+    const T* tp = tau + p0;
     Stencil<T, D> S;
     if (make_stencil<T, D>(st, p, c, S)) {
       const T dt = T(I.dt), mp = T(I.mp), dx = T(c.dx), inv_dx = T(c.inv_dx);
@@ -1821,7 +1867,7 @@ __global__ void __launch_bounds__(kBlock) k_p2g_adj_gather(KCfg c, Bufs b, const
 #pragma unroll
         for (int bb = 0; bb < D; ++bb) {
           Cm[a][bb] = st.C(a, bb, p);
-          A[a][bb] = k_str * tau[(int64_t)sym_row<D>(a, bb) * c.ntot + p] + mp * Cm[a][bb];
+          A[a][bb] = k_str * scalar_base(tp + (int64_t)sym_row<D>(a, bb) * c.ntot)[p] + mp * Cm[a][bb];
         }
 #pragma unroll
       for (int a = 0; a < D; ++a) vel[a] = st.v(a, p);
@@ -1847,6 +1893,7 @@ __global__ void __launch_bounds__(kBlock) k_p2g_adj_gather(KCfg c, Bufs b, const
 #pragma unroll
       for (int a = 0; a < D; ++a) xb[a] = ac.x(a, p);     // G2P part, written by k_g2p_adj
       const T* g = gbar + I.goff * kNodeVals;
+      const uint32_t nb = node_bytes<T, D>(c, S.base);
       T rr[3][3], dwi[3][3];
 #pragma unroll
       for (int a = 0; a < 3; ++a)
@@ -1868,6 +1915,7 @@ __global__ void __launch_bounds__(kBlock) k_p2g_adj_gather(KCfg c, Bufs b, const
           const T wa = S.w[0][o0], wb = D == 3 ? S.w[1][o1] : T(1);
           const T wxy = wa * wb;
           const T a0 = dwi[0][o0] * wb, a1 = D == 3 ? wa * dwi[1][o1] : T(0);
+          const Global<T>* row = stencil_row<T, D>(c, g, o0, o1);
           T t[3] = {T(0), T(0), T(0)};
 #pragma unroll
           for (int a = 0; a < D; ++a)
@@ -1876,8 +1924,7 @@ __global__ void __launch_bounds__(kBlock) k_p2g_adj_gather(KCfg c, Bufs b, const
 #pragma unroll
           for (int ol = 0; ol < 3; ++ol) {
             const T wl = S.w[D - 1][ol];
-            const int64_t nd = (D == 3 ? node_of<D>(S.base, o0, o1, ol, c.n) : node_of<D>(S.base, o0, ol, 0, c.n)) * kNodeVals;
-            const Node4<T> gn = ld_node(g + nd);
+            const Node4<T> gn = ld_node(at_bytes(row, nb) + ol * kNodeVals);
             T sc = mp * gn.v[3];
 #pragma unroll
             for (int a = 0; a < D; ++a) sc += gn.v[a] * t[a];
@@ -1905,6 +1952,9 @@ __global__ void __launch_bounds__(kBlock) k_p2g_adj_gather(KCfg c, Bufs b, const
             if (D == 3) Ab[a][1] += r1 * u[a];
             Ab[a][D - 1] += wxy * ul[a];
           }
+          // at most a plane's nine loads in flight: all 27 at once need more
+          // registers than four waves per SIMD leave
+          if (sizeof(T) == 4 && D == 3 && o1 == 2) __builtin_amdgcn_sched_barrier(0);
         }
       T vb[3] = {T(0), T(0), T(0)};
       T mpb = Gm;
@@ -1929,7 +1979,7 @@ __global__ void __launch_bounds__(kBlock) k_p2g_adj_gather(KCfg c, Bufs b, const
 #pragma unroll
         for (int a = 0; a < D; ++a)
 #pragma unroll
-          for (int bb = 0; bb < D; ++bb) sab += tau[(int64_t)sym_row<D>(a, bb) * c.ntot + p] * Ab[a][bb];
+          for (int bb = 0; bb < D; ++bb) sab += scalar_base(tp + (int64_t)sym_row<D>(a, bb) * c.ntot)[p] * Ab[a][bb];
         acc[0] = -(double)(k_str * sab) * (I.Vp / I.mp);
       } else {
         acc[0] = (double)mpb * I.Vp;
@@ -1944,11 +1994,12 @@ __global__ void __launch_bounds__(kBlock) k_p2g_adj_constit(KCfg c, Bufs b, cons
                                                             void* adj_cur, double* pacc) {
   const int inst = b.blk_inst[blockIdx.x];
   const InstDev& I = b.inst[inst];
-  const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  const int64_t p0 = (int64_t)blockIdx.x * kBlock;
+  const uint32_t p = threadIdx.x;
   double acc[4] = {0, 0, 0, 0};
-  if (p - I.off < I.n) {
-    const P<T, D> st = pv<T, D>(stv, c.ntot);
-    const Adj<T, D> an = av<T, D>(adj_next, c.ntot), ac = av<T, D>(adj_cur, c.ntot);
+  if ((int64_t)p < I.n - (p0 - I.off)) {
+    const P<T, D> st = pv<T, D>(stv, c.ntot).at(p0);
+    const Adj<T, D> an = av<T, D>(adj_next, c.ntot).at(p0), ac = av<T, D>(adj_cur, c.ntot).at(p0);
     const T dt = T(I.dt), mp = T(I.mp);
     const T mu = T(I.mu), lam = T(I.lam), al = T(I.alpha), kc = T(I.kc);
     const T k_str = -dt * T(I.Vp) * T(4.0 * c.inv_dx * c.inv_dx);

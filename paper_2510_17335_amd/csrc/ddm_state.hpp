@@ -14,14 +14,15 @@ namespace ddm {
 template <typename T> struct Pos;
 template <> struct Pos<float> {
   using X = uint32_t;
+  // x n - 1/2 in units of 2^-32, in 32-bit halves: x n has the integer part hi
+  // and the fraction lo, so its cell is hi - 1 below the half and hi above it
+  // (-1, that is 2^32 - 1 unsigned, left of the grid).
   static __device__ __forceinline__ bool cell(X xr, const KCfg& c, int& base, float& f) {
-    const uint64_t q = (uint64_t)xr << c.nlog2;          // x n in units of 2^-32
-    if (q < 0x80000000ull) return false;
-    const uint64_t s = q - 0x80000000ull;                // x n - 1/2
-    const uint64_t b = s >> 32;
-    if (b > (uint64_t)(c.n - 3)) return false;
+    const uint32_t hi = xr >> (32 - c.nlog2), lo = xr << c.nlog2;
+    const uint32_t b = hi - 1u + (lo >> 31);
+    if (b > (uint32_t)(c.n - 3)) return false;
     base = (int)b;
-    f = 0.5f + (float)(uint32_t)(s & 0xFFFFFFFFull) * 2.3283064365386963e-10f;
+    f = 0.5f + (float)(lo ^ 0x80000000u) * 2.3283064365386963e-10f;
     return true;
   }
   static __device__ __forceinline__ double real(X xr) { return (double)xr * 2.3283064365386963e-10; }
@@ -54,26 +55,43 @@ template <> struct Pos<double> {
   static __device__ __forceinline__ double unkey(unsigned long long k) { return __longlong_as_double((long long)k); }
 };
 
+// A pointer that is the same for the whole wave, held in scalar registers: the
+// empty asm hides how it was formed, so that the compiler does not add its
+// parts to the lane's offset first (64-bit vector arithmetic for every access)
+// but indexes it with one 32-bit lane offset.
+template <typename T> using Global = __attribute__((address_space(1))) T;
+template <typename T> __device__ __forceinline__ Global<T>* scalar_base(T* p) {
+  Global<T>* q = (Global<T>*)p;
+#ifdef __HIP_DEVICE_COMPILE__
+  asm("" : "+s"(q));     // (the host pass knows no scalar registers)
+#endif
+  return q;
+}
+
+// With a view shifted to the first slot of a workgroup (at()) and the thread
+// as the index, all rows share one lane offset.
 template <typename T, int D> struct P {
   T* s;
   int64_t ntot;
   using X = typename Pos<T>::X;
-  __device__ __forceinline__ X& xr(int a, int64_t p) const { return reinterpret_cast<X*>(s)[(int64_t)a * ntot + p]; }
-  __device__ __forceinline__ T& v(int a, int64_t p) const { return s[(int64_t)(D + a) * ntot + p]; }
-  __device__ __forceinline__ T& C(int a, int b, int64_t p) const { return s[(int64_t)(2 * D + a * D + b) * ntot + p]; }
-  __device__ __forceinline__ T& G(int a, int b, int64_t p) const {
-    return s[(int64_t)(2 * D + D * D + a * D + b) * ntot + p];
+  __device__ __forceinline__ P at(int64_t p0) const { return P{s + p0, ntot}; }
+  __device__ __forceinline__ Global<X>& xr(int a, int64_t p) const { return scalar_base(reinterpret_cast<X*>(s) + (int64_t)a * ntot)[p]; }
+  __device__ __forceinline__ Global<T>& v(int a, int64_t p) const { return scalar_base(s + (int64_t)(D + a) * ntot)[p]; }
+  __device__ __forceinline__ Global<T>& C(int a, int b, int64_t p) const { return scalar_base(s + (int64_t)(2 * D + a * D + b) * ntot)[p]; }
+  __device__ __forceinline__ Global<T>& G(int a, int b, int64_t p) const {
+    return scalar_base(s + (int64_t)(2 * D + D * D + a * D + b) * ntot)[p];
   }
 };
 // Adjoint states hold plain T in every row.
 template <typename T, int D> struct Adj {
   T* s;
   int64_t ntot;
-  __device__ __forceinline__ T& x(int a, int64_t p) const { return s[(int64_t)a * ntot + p]; }
-  __device__ __forceinline__ T& v(int a, int64_t p) const { return s[(int64_t)(D + a) * ntot + p]; }
-  __device__ __forceinline__ T& C(int a, int b, int64_t p) const { return s[(int64_t)(2 * D + a * D + b) * ntot + p]; }
-  __device__ __forceinline__ T& G(int a, int b, int64_t p) const {
-    return s[(int64_t)(2 * D + D * D + a * D + b) * ntot + p];
+  __device__ __forceinline__ Adj at(int64_t p0) const { return Adj{s + p0, ntot}; }
+  __device__ __forceinline__ Global<T>& x(int a, int64_t p) const { return scalar_base(s + (int64_t)a * ntot)[p]; }
+  __device__ __forceinline__ Global<T>& v(int a, int64_t p) const { return scalar_base(s + (int64_t)(D + a) * ntot)[p]; }
+  __device__ __forceinline__ Global<T>& C(int a, int b, int64_t p) const { return scalar_base(s + (int64_t)(2 * D + a * D + b) * ntot)[p]; }
+  __device__ __forceinline__ Global<T>& G(int a, int b, int64_t p) const {
+    return scalar_base(s + (int64_t)(2 * D + D * D + a * D + b) * ntot)[p];
   }
 };
 
