@@ -218,6 +218,25 @@ void launch_tile_slots(const KCfg& c, const TileList& tl, int64_t max_records, u
 constexpr int kTileBuckets = 16;
 void launch_tile_list(const KCfg& c, const uint32_t* sorted_keys, uint32_t* tstart, uint32_t* tend, TileRec* list,
                       uint32_t* count, uint32_t* tslot, uint32_t* bucket, hipStream_t s);
+// The same binning as a two-level counting sort: state, ids (pid_in may be
+// NULL) and the permutation (may be NULL) in the order of the stable sort by
+// key, the tile list with tslot (and a second copy list2 / count2, may be
+// NULL) and the active set.  nwg: workgroups of the per-tile kernel.
+struct BinBufs {
+  uint32_t *ck, *rank, *tmp;         // [padded slots] scratch
+  uint32_t *tcnt, *tstart;           // [tiles]; tcnt is zero between calls
+  uint32_t* part;                    // bin_part_words() words
+  TileRec* list;
+  uint32_t* count;
+  TileRec* list2;
+  uint32_t* count2;
+  uint32_t* tslot;
+  ActiveSet act;
+};
+bool bin_by_tiles(const KCfg& c, double ppc);
+int64_t bin_part_words(int64_t total_tiles);
+void launch_bin_tiles(int prec, const KCfg& c, const Bufs& b, int nblk, int nwg, const void* src, void* dst,
+                      const uint32_t* pid_in, uint32_t* pid_out, uint32_t* perm_out, const BinBufs& w, hipStream_t s);
 
 // Earth mover's distance of the surface observation to a target point cloud
 // (ddm_emd.hip); arrays are [n_inst][hm_res^2] (points [..][3]).

@@ -63,7 +63,7 @@ struct Layout {
   size_t adj0 = 0, adj1 = 0, gvb = 0, gb = 0, pacc = 0, pose_bar = 0;
   size_t hm_bits = 0, owner = 0, target = 0, hm_val = 0, dldh = 0, region = 0, dldm = 0, loss = 0;
   size_t keys0 = 0, keys1 = 0, vals0 = 0, vals1 = 0, hist = 0, sums = 0, tstart = 0, tend = 0, tiles = 0, tcount = 0;
-  size_t tslot = 0, tbucket = 0, staging = 0, gout = 0, amask = 0, alist = 0, acount = 0, seg_alist = 0, seg_acount = 0;
+  size_t tslot = 0, tbucket = 0, tcnt = 0, tpart = 0, staging = 0, gout = 0, amask = 0, alist = 0, acount = 0, seg_alist = 0, seg_acount = 0;
   size_t treat_acc = 0, tqueue = 0, dpart = 0, ckpt_pid = 0, rpid0 = 0, rpid1 = 0;
   size_t emd_top = 0, emd_own = 0, emd_target = 0, emd_obs = 0, emd_slot = 0, emd_nobs = 0, emd_assign = 0,
          emd_val = 0;
@@ -180,6 +180,8 @@ Layout make_layout(const ddm_config& c, int n_inst, const ddm_instance* in) {
   L.tcount = cv.take(sizeof(uint32_t));
   L.tslot = cv.take(sizeof(uint32_t) * L.total_tiles);
   L.tbucket = cv.take(sizeof(uint32_t) * 2 * ddm::kTileBuckets);
+  L.tcnt = cv.take(sizeof(uint32_t) * L.total_tiles);
+  L.tpart = cv.take(sizeof(uint32_t) * ddm::bin_part_words(L.total_tiles));
   L.staging = cv.take(L.win_bytes * L.total_tiles);
   L.gout = cv.take(L.grid_bytes);
   L.amask = cv.take(sizeof(uint32_t) * L.total_tiles);
@@ -551,7 +553,7 @@ void resolve_events(ddm_ctx* x) {
 }
 
 // Bins the particles of state `src` into `dst` (another buffer): exact cell
-// keys, stable radix sort by (instance, tile, cell), gather of the state rows
+// keys, stable sort by (instance, tile, cell), gather of the state rows
 // (and ids, when given) into sorted order, the occupied-tile list with each
 // tile's staging record, and the active node blocks.  When perm_out / tiles_out are given the
 // permutation and the tile list are also stored there (for the reverse pass).
@@ -562,6 +564,23 @@ ddm_status bin_state(ddm_ctx* x, const void* src, void* dst, const uint32_t* pid
   hipStream_t st = x->stream;
   uint32_t* keys[2] = {x->at<uint32_t>(L.keys0), x->at<uint32_t>(L.keys1)};
   uint32_t* vals[2] = {x->at<uint32_t>(L.vals0), x->at<uint32_t>(L.vals1)};
+  if (ddm::bin_by_tiles(x->kc, x->cfg.ppc)) {
+    ddm::BinBufs w;
+    w.ck = keys[0];
+    w.rank = vals[0];
+    w.tmp = vals[1];
+    w.tcnt = x->at<uint32_t>(L.tcnt);
+    w.tstart = x->at<uint32_t>(L.tstart);
+    w.part = x->at<uint32_t>(L.tpart);
+    w.list = x->at<ddm::TileRec>(L.tiles);
+    w.count = x->at<uint32_t>(L.tcount);
+    w.list2 = tiles_out;
+    w.count2 = tcount_out;
+    w.tslot = x->at<uint32_t>(L.tslot);
+    w.act = x->active();
+    ddm::launch_bin_tiles(x->prec, x->kc, x->bufs(), (int)L.nblk, L.nwg, src, dst, pid_src, pid_dst, perm_out, w, st);
+    return launch_status();
+  }
   int r = 0;
   if (x->kc.det) {
     // deterministic mode: a cell's particles in id order, whatever their slot
@@ -855,6 +874,7 @@ ddm_status ddm_create(const ddm_config* cfg, int32_t n_inst, const ddm_instance*
   s = upload_instances(x, inst);
   if (s == DDM_OK) s = hip_check(hipMemset(x->at(L.err), 0, sizeof(ddm::DevErr)), "clear error word");
   if (s == DDM_OK) s = hip_check(hipMemset(x->at(L.tqueue), 0, 2 * sizeof(uint32_t)), "clear tile queue");
+  if (s == DDM_OK) s = hip_check(hipMemset(x->at(L.tcnt), 0, sizeof(uint32_t) * L.total_tiles), "clear tile counters");
   if (s == DDM_OK && cfg->deterministic)
     s = hip_check(hipMemset(x->at(L.dpart), 0, sizeof(double) * ddm::kDetVals * (size_t)std::max(L.nblk, L.total_tiles)),
                   "clear deterministic partials");

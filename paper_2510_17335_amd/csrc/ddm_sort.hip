@@ -1,7 +1,9 @@
-// Binning of particles: exact integer cell keys from the stored positions, a
-// stable least-significant-digit radix sort (8-bit digits, wave64 ballot
-// ranking), the state gather into sorted order, and the list of occupied
-// tiles that the scatter kernels work on.
+// Binning of particles: exact integer cell keys from the stored positions, the
+// stable sort by key, the state gather into sorted order, and the list of
+// occupied tiles that the scatter kernels work on.  Two ways to the same
+// order: a least-significant-digit radix sort (8-bit digits, wave64 ballot
+// ranking), and a two-level counting sort (by tile with counters, inside a
+// tile in LDS) in four or five launches, described below.
 //
 // Key of a live particle: inst * (n^D + 1) + tile * B^D + cell-in-tile, with
 // tile and cell-in-tile lexicographic in (x, y[, z]) (last axis fastest) and
@@ -436,6 +438,362 @@ void launch_active_set(const KCfg& c, const TileList& tl, const ActiveSet& act, 
   launch_fill_zero(act.count, 1, 4, s);
   hipLaunchKernelGGL(k_mark_active, dim3(nb), dim3(kBlock), 0, s, c, tl, total_tiles, act.mask);
   hipLaunchKernelGGL(k_list_active, dim3(nb), dim3(kBlock), 0, s, total_tiles, act.mask, act.list, act.count);
+}
+
+// ---------------------------------------------------------------------------
+// Two-level counting sort.  The order wanted is (tile, cell, slot), slot being
+// the position before the sort (the stable order).  A tile holds a few hundred
+// particles, so a workgroup can order its tile in LDS; what is left is a
+// counting sort by tile, whose counters need not be stable because the tile's
+// workgroup restores the slot order:
+//   k_bin_count  cell of every particle, its rank in its tile's counter (one
+//                atomic per wave and distinct tile; sorted states have one or
+//                two tiles per wave);
+//   k_bin_table  from the counts: first slot of each tile, the occupied-tile
+//                list with its records, the active node blocks;
+//   k_bin_place  slot numbers to their tile's range; padding keeps its place;
+//   k_bin_order  a workgroup per tile: order by (cell, slot), permutation,
+//                gather of the state rows and ids.
+// The radix sort takes 23 to 31 launches and copies for the same, 4 to 5 us
+// each whatever their size: about 130 us per binning of 27 440 particles on a
+// 64^3 grid against 38 us here, and about 340 us for 3.5 M particles of 32
+// instances against 240 us (most of both the 192 B per particle of the gather).
+// ---------------------------------------------------------------------------
+constexpr int kOrderCap = 2048;           // particles of a tile that k_bin_order holds in LDS
+constexpr int kTableThreads = 1024;
+constexpr int kTableTiles = 4096;         // tiles per workgroup of k_bin_table
+
+// ck[slot] = tile * kTile^D + cell (padding: ~0), rank[slot] = its place in the
+// tile's range; clears mask and *acount for k_bin_table.
+template <int PREC>
+__global__ void __launch_bounds__(kBlock) k_bin_count(KCfg c, Bufs b, const void* state, uint32_t* __restrict__ ck,
+                                                      uint32_t* __restrict__ rank, uint32_t* __restrict__ tcnt,
+                                                      int64_t total_tiles, uint32_t* __restrict__ mask,
+                                                      uint32_t* __restrict__ acount) {
+  const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  for (int64_t t = j; t < total_tiles; t += (int64_t)gridDim.x * kBlock) mask[t] = 0u;
+  if (j == 0) *acount = 0u;
+  const int i = b.blk_inst[blockIdx.x];
+  const InstDev& I = b.inst[i];
+  const int lane = threadIdx.x & 63;
+  const bool live = j - I.off < I.n;
+  uint32_t tile = 0, cell = 0;
+  if (live) {
+    const int nt = c.n / kTile;
+    bool ok = true;
+    for (int a = 0; a < c.dim; ++a) {
+      int q;
+      if (PREC == 0) ok &= cell_f32(static_cast<const uint32_t*>(state)[(int64_t)a * c.ntot + j], c, q);
+      else ok &= cell_f64(static_cast<const double*>(state)[(int64_t)a * c.ntot + j], c, q);
+      tile = tile * nt + q / kTile;
+      cell = cell * kTile + q % kTile;
+    }
+    if (!ok) atomicOr(&b.err->flags, 2u);
+    tile += (uint32_t)(c.nodes >> (c.dim == 3 ? 6 : 4)) * (uint32_t)i;
+  }
+  unsigned long long todo = __ballot(live);
+  uint32_t r = 0;
+  while (todo) {
+    const int lead = __ffsll((long long)todo) - 1;
+    const uint32_t t = (uint32_t)__builtin_amdgcn_readlane((int)tile, lead);
+    const unsigned long long same = __ballot(live && tile == t);
+    uint32_t base = 0;
+    if (lane == lead) base = atomicAdd(&tcnt[t], (uint32_t)__popcll(same));
+    base = (uint32_t)__builtin_amdgcn_readlane((int)base, lead);
+    if (live && tile == t) r = base + (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
+    todo &= ~same;
+  }
+  ck[j] = live ? (tile << (c.dim == 3 ? 6 : 4)) + cell : 0xFFFFFFFFu;
+  rank[j] = r;
+}
+
+// Where k_bin_table writes; list2 / count2 (may be NULL) get a second copy of
+// the tile list.
+struct TableOut {
+  uint32_t* tcnt;
+  uint32_t* tstart;
+  TileRec* list;
+  uint32_t* count;
+  TileRec* list2;
+  uint32_t* count2;
+  uint32_t* tslot;
+  ActiveSet act;
+  uint32_t* part;                         // [workgroups][1 + kTileBuckets]: particles, tiles per bucket
+};
+
+// Sum of v over the workgroup's threads below this one; total in *sum.
+__device__ __forceinline__ uint32_t table_scan(uint32_t v, uint32_t* sum) {
+  __shared__ uint32_t ws[kTableThreads / 64];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  uint32_t x = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  __syncthreads();
+  if (lane == 63) ws[wid] = x;
+  __syncthreads();
+  uint32_t off = 0, tot = 0;
+  for (int w = 0; w < kTableThreads / 64; ++w) {
+    if (w < wid) off += ws[w];
+    tot += ws[w];
+  }
+  *sum = tot;
+  return off + x - v;
+}
+
+// Marks the 3^D blocks around tile gt.
+__device__ __forceinline__ void mark_around(const KCfg& c, uint32_t gt, uint32_t* mask) {
+  const int D = c.dim, tb = c.nlog2 - 2, nt = 1 << tb;
+  const uint32_t per = 1u << (D * tb), inst = gt >> (D * tb), t = gt & (per - 1u);
+  const int q2 = D == 3 ? (int)(t & (uint32_t)(nt - 1)) : 0;
+  const int q1 = (int)((D == 3 ? t >> tb : t) & (uint32_t)(nt - 1)), q0 = (int)(t >> ((D - 1) * tb));
+  for (int a = max(q0 - 1, 0); a <= min(q0 + 1, nt - 1); ++a)
+    for (int e = max(q1 - 1, 0); e <= min(q1 + 1, nt - 1); ++e)
+      for (int f = D == 3 ? max(q2 - 1, 0) : 0; f <= (D == 3 ? min(q2 + 1, nt - 1) : 0); ++f)
+        mask[inst * per + (uint32_t)(D == 3 ? (((a << tb) + e) << tb) + f : (a << tb) + e)] = 1u;
+}
+
+// The table of up to kTableTiles tiles per workgroup.  One workgroup does it
+// in one launch (STAGE 0); more need two: STAGE 1 leaves their sums in part
+// and marks the active blocks, STAGE 2 takes the sums of the workgroups before
+// it.  Records are ordered by particle count, largest bucket first: workgroups
+// are dispatched in list order, so the longest tiles start first.
+template <int STAGE>
+__global__ void __launch_bounds__(kTableThreads) k_bin_table(KCfg c, const InstDev* inst, int64_t total_tiles,
+                                                             TableOut o) {
+  constexpr int PER = kTableTiles / kTableThreads;
+  __shared__ uint32_t hist[kTileBuckets], first[kTileBuckets], sums[1 + kTileBuckets], abase;
+  const int tid = threadIdx.x;
+  const int64_t t0 = (int64_t)blockIdx.x * kTableTiles + (int64_t)tid * PER;
+  if (tid < kTileBuckets) hist[tid] = 0u;
+  if (tid <= kTileBuckets) sums[tid] = 0u;
+  __syncthreads();
+  uint32_t n[PER], own = 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    n[k] = t0 + k < total_tiles ? o.tcnt[t0 + k] : 0u;
+    own += n[k];
+    if (n[k] && STAGE != 2) mark_around(c, (uint32_t)(t0 + k), o.act.mask);
+    if (n[k] && STAGE != 2) atomicAdd(&hist[tile_bucket(n[k])], 1u);
+  }
+  uint32_t tot = 0, before = 0;
+  before = table_scan(own, &tot);
+  __syncthreads();
+  if (STAGE == 1) {
+    uint32_t* pt = o.part + (int64_t)blockIdx.x * (1 + kTileBuckets);
+    if (tid == 0) pt[0] = tot;
+    if (tid < kTileBuckets) pt[1 + tid] = hist[tid];
+    return;
+  }
+  // first record of each bucket (largest first), and what the workgroups before this one hold
+  if (STAGE == 2) {
+    for (int e = tid; e < (int)gridDim.x * (1 + kTileBuckets); e += kTableThreads) {
+      const int w = e / (1 + kTileBuckets), k = e - w * (1 + kTileBuckets);
+      const uint32_t v = o.part[e];
+      if (k > 0) atomicAdd(&hist[k - 1], v);
+      if (w < (int)blockIdx.x) atomicAdd(&sums[k], v);
+    }
+    __syncthreads();
+  }
+  if (tid == 0) {
+    uint32_t acc = 0;
+    for (int k = kTileBuckets - 1; k >= 0; --k) { first[k] = acc; acc += hist[k]; }
+    for (int k = 0; k < kTileBuckets; ++k) first[k] += sums[1 + k];
+    if (blockIdx.x == 0) {
+      *o.count = acc;
+      if (o.count2) *o.count2 = acc;
+    }
+  }
+  __syncthreads();
+  // tile starts: the particles before the tile in its instance, from the instance's first slot
+  uint32_t run = sums[0] + before;
+  const int pb = c.dim * (c.nlog2 - 2);
+  int cur = -1;
+  uint32_t shift = 0;                     // first slot of the instance less the particles of those before it
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int64_t t = t0 + k;
+    if (t >= total_tiles) break;
+    const int i = (int)(t >> pb);
+    if (i != cur) {
+      cur = i;
+      int64_t sum = 0;
+      for (int q = 0; q < i; ++q) sum += inst[q].n;
+      shift = (uint32_t)(inst[i].off - sum);
+    }
+    const uint32_t st = run + shift;
+    run += n[k];
+    o.tstart[t] = st;
+    o.tcnt[t] = 0u;                       // for the next binning
+    uint32_t slot = kNoSlot;
+    if (n[k]) {
+      slot = atomicAdd(&first[tile_bucket(n[k])], 1u);
+      const TileRec r{st, st + n[k], (uint32_t)t};
+      o.list[slot] = r;
+      if (o.list2) o.list2[slot] = r;
+    }
+    o.tslot[t] = slot;
+  }
+  // active blocks (this workgroup's marks are complete here: after the
+  // barriers of one workgroup, or an earlier launch)
+  uint32_t a[PER], na = 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    a[k] = t0 + k < total_tiles ? o.act.mask[t0 + k] : 0u;
+    na += a[k] ? 1u : 0u;
+  }
+  uint32_t atot = 0, pos = table_scan(na, &atot);
+  if (tid == 0) abase = atomicAdd(o.act.count, atot);
+  __syncthreads();
+  pos += abase;
+#pragma unroll
+  for (int k = 0; k < PER; ++k)
+    if (a[k]) o.act.list[pos++] = (uint32_t)(t0 + k);
+}
+
+template <typename W>
+__global__ void __launch_bounds__(kBlock) k_bin_place(KCfg c, Bufs b, const uint32_t* __restrict__ ck,
+                                                      const uint32_t* __restrict__ rank,
+                                                      const uint32_t* __restrict__ tstart, uint32_t* __restrict__ tmp,
+                                                      const W* in, W* out, int rows, const uint32_t* pid_in,
+                                                      uint32_t* pid_out, uint32_t* perm_out) {
+  const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  const uint32_t k = ck[j];
+  if (k != 0xFFFFFFFFu) {
+    tmp[tstart[k >> (c.dim == 3 ? 6 : 4)] + rank[j]] = (uint32_t)j;
+    return;
+  }
+  // padding stays at the end of its instance's range, in order
+  for (int r = 0; r < rows; ++r) out[(int64_t)r * c.ntot + j] = in[(int64_t)r * c.ntot + j];
+  if (pid_out) pid_out[j] = pid_in[j];
+  if (perm_out) perm_out[j] = (uint32_t)j;
+}
+
+template <typename W, int ROWS>
+__global__ void __launch_bounds__(kBlock) k_bin_order(KCfg c, const TileRec* __restrict__ list,
+                                                      const uint32_t* __restrict__ count,
+                                                      const uint32_t* __restrict__ ck, const uint32_t* __restrict__ tmp,
+                                                      const W* __restrict__ in, W* __restrict__ out,
+                                                      const uint32_t* __restrict__ pid_in, uint32_t* __restrict__ pid_out,
+                                                      uint32_t* __restrict__ perm_out) {
+  __shared__ uint32_t byc[kOrderCap], fin[kOrderCap];      // slots by cell, then in order
+  __shared__ uint32_t cnt[64], start[64], fill[64];
+  const int tid = threadIdx.x;
+  const uint32_t cmask = c.dim == 3 ? 63u : 15u;
+  const uint32_t ntiles = *count;
+  for (uint32_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    const TileRec tr = list[t];
+    const int n = (int)(tr.end - tr.start);
+    const uint32_t* ts = tmp + tr.start;
+    if (n <= kOrderCap) {
+      if (tid < 64) { cnt[tid] = 0u; fill[tid] = 0u; }
+      __syncthreads();
+      uint32_t sl[kOrderCap / kBlock], ql[kOrderCap / kBlock];      // this thread's slots and cells
+#pragma unroll
+      for (int k = 0; k < kOrderCap / kBlock; ++k)
+        if (tid + k * kBlock < n) {
+          sl[k] = ts[tid + k * kBlock];
+          ql[k] = ck[sl[k]] & cmask;
+          atomicAdd(&cnt[ql[k]], 1u);
+        }
+      __syncthreads();
+      if (tid < 64) {
+        uint32_t x = cnt[tid];
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const uint32_t y = __shfl_up(x, o, 64);
+          if (tid >= o) x += y;
+        }
+        start[tid] = x - cnt[tid];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < kOrderCap / kBlock; ++k)
+        if (tid + k * kBlock < n) byc[start[ql[k]] + atomicAdd(&fill[ql[k]], 1u)] = sl[k];
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < kOrderCap / kBlock; ++k)
+        if (tid + k * kBlock < n) {
+          const int lo = (int)start[ql[k]], hi = lo + (int)cnt[ql[k]];
+          int at = lo;
+          for (int e = lo; e < hi; ++e) at += byc[e] < sl[k] ? 1 : 0;
+          fin[at] = sl[k];
+        }
+      __syncthreads();
+      for (int i = tid; i < n; i += kBlock) {
+        const uint32_t s = fin[i];
+        const int64_t d = (int64_t)tr.start + i;
+        W v[ROWS];
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) v[r] = in[(int64_t)r * c.ntot + s];
+        if (pid_out) pid_out[d] = pid_in[s];
+        if (perm_out) perm_out[d] = s;
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) out[(int64_t)r * c.ntot + d] = v[r];
+      }
+      __syncthreads();
+    } else {
+      // a tile beyond the LDS capacity: every particle's place by comparison with all
+      for (int i = tid; i < n; i += kBlock) {
+        const uint32_t s = ts[i], q = ck[s] & cmask;
+        int at = 0;
+        for (int k = 0; k < n; ++k) {
+          const uint32_t u = ts[k], e = ck[u] & cmask;
+          at += (e < q || (e == q && u < s)) ? 1 : 0;
+        }
+        const int64_t d = (int64_t)tr.start + at;
+        for (int r = 0; r < ROWS; ++r) out[(int64_t)r * c.ntot + d] = in[(int64_t)r * c.ntot + s];
+        if (pid_out) pid_out[d] = pid_in[s];
+        if (perm_out) perm_out[d] = s;
+      }
+    }
+  }
+}
+
+// The counting sort needs tile * kTile^D + cell below 2^32 - 1, and the bed's
+// tiles (ppc particles per cell at rest) within k_bin_order's LDS with room for
+// compaction; a tile beyond that is still ordered, by the slower comparison.
+bool bin_by_tiles(const KCfg& c, double ppc) {
+  const double cells = c.dim == 3 ? 64.0 : 16.0;
+  return !c.det && (double)c.nodes * c.n_inst < 4294967295.0 && ppc * cells <= kOrderCap / 2;
+}
+
+int64_t bin_part_words(int64_t total_tiles) {
+  return (total_tiles + kTableTiles - 1) / kTableTiles * (1 + kTileBuckets);
+}
+
+void launch_bin_tiles(int prec, const KCfg& c, const Bufs& b, int nblk, int nwg, const void* src, void* dst,
+                      const uint32_t* pid_in, uint32_t* pid_out, uint32_t* perm_out, const BinBufs& w, hipStream_t s) {
+  const int tshift = c.dim == 3 ? 6 : 4;
+  const int64_t total_tiles = (c.nodes >> tshift) * c.n_inst;
+  if (prec == 0)
+    hipLaunchKernelGGL(k_bin_count<0>, dim3(nblk), dim3(kBlock), 0, s, c, b, src, w.ck, w.rank, w.tcnt, total_tiles,
+                       w.act.mask, w.act.count);
+  else
+    hipLaunchKernelGGL(k_bin_count<1>, dim3(nblk), dim3(kBlock), 0, s, c, b, src, w.ck, w.rank, w.tcnt, total_tiles,
+                       w.act.mask, w.act.count);
+  const TableOut o{w.tcnt, w.tstart, w.list, w.count, w.list2, w.count2, w.tslot, w.act, w.part};
+  const unsigned ntw = (unsigned)((total_tiles + kTableTiles - 1) / kTableTiles);
+  if (ntw == 1) {
+    hipLaunchKernelGGL(k_bin_table<0>, dim3(1), dim3(kTableThreads), 0, s, c, b.inst, total_tiles, o);
+  } else {
+    hipLaunchKernelGGL(k_bin_table<1>, dim3(ntw), dim3(kTableThreads), 0, s, c, b.inst, total_tiles, o);
+    hipLaunchKernelGGL(k_bin_table<2>, dim3(ntw), dim3(kTableThreads), 0, s, c, b.inst, total_tiles, o);
+  }
+  const int rows = 2 * c.dim + 2 * c.dim * c.dim;
+#define DDM_BIN(W, R)                                                                                              \
+  hipLaunchKernelGGL((k_bin_place<W>), dim3(nblk), dim3(kBlock), 0, s, c, b, w.ck, w.rank, w.tstart, w.tmp,        \
+                     (const W*)src, (W*)dst, rows, pid_in, pid_out, perm_out);                                     \
+  hipLaunchKernelGGL((k_bin_order<W, R>), dim3(nwg), dim3(kBlock), 0, s, c, w.list, w.count, w.ck, w.tmp,          \
+                     (const W*)src, (W*)dst, pid_in, pid_out, perm_out)
+  if (prec == 0) {
+    if (c.dim == 3) { DDM_BIN(uint32_t, 24); } else { DDM_BIN(uint32_t, 12); }
+  } else {
+    if (c.dim == 3) { DDM_BIN(uint64_t, 24); } else { DDM_BIN(uint64_t, 12); }
+  }
+#undef DDM_BIN
 }
 
 }  // namespace ddm
