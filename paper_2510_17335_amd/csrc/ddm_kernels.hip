@@ -72,13 +72,20 @@ template <typename T, int D> struct Stencil {
 };
 
 template <typename T, int D>
-__device__ __forceinline__ bool make_stencil(const P<T, D>& st, int64_t p, const KCfg& c, Stencil<T, D>& S) {
+__device__ __forceinline__ bool make_stencil(const typename Pos<T>::X (&xr)[3], const KCfg& c, Stencil<T, D>& S) {
 #pragma unroll
   for (int a = 0; a < D; ++a) {
-    if (!Pos<T>::cell(st.xr(a, p), c, S.base[a], S.f[a])) return false;
+    if (!Pos<T>::cell(xr[a], c, S.base[a], S.f[a])) return false;
     bspline(S.f[a], S.w[a], S.dw[a]);
   }
   return true;
+}
+template <typename T, int D>
+__device__ __forceinline__ bool make_stencil(const P<T, D>& st, int64_t p, const KCfg& c, Stencil<T, D>& S) {
+  typename Pos<T>::X xr[3];
+#pragma unroll
+  for (int a = 0; a < D; ++a) xr[a] = st.xr(a, p);
+  return make_stencil<T, D>(xr, c, S);
 }
 
 template <int D>
@@ -328,18 +335,26 @@ template <int D> struct Win {
   }
 };
 
-// Per-particle constitutive update and P2G contributions; emit(node offsets,
-// weight, values) receives the D+1 scattered values of each stencil node.
-template <typename T, int D>
-__device__ __forceinline__ bool p2g_particle(const KCfg& c, const Bufs& b, const InstDev& I, int inst,
-                                             const P<T, D>& si, const P<T, D>& so, int64_t p, Stencil<T, D>& S,
-                                             T (&A)[3][3], T (&vel)[3], T* tau_out) {
-  const T dt = T(I.dt), mp = T(I.mp);
-  T Cm[3][3], Gm[3][3], Ft[3][3];
+// What the constitutive update needs of one particle, in registers.
+template <typename T, int D> struct Part { T C[3][3], G[3][3]; };
+template <typename T, int D> __device__ __forceinline__ void load_part(const P<T, D>& st, int64_t p, Part<T, D>& q) {
 #pragma unroll
   for (int a = 0; a < D; ++a)
 #pragma unroll
-    for (int bb = 0; bb < D; ++bb) { Cm[a][bb] = si.C(a, bb, p); Gm[a][bb] = si.G(a, bb, p); }
+    for (int bb = 0; bb < D; ++bb) { q.C[a][bb] = st.C(a, bb, p); q.G[a][bb] = st.G(a, bb, p); }
+}
+
+// Per-particle constitutive update and P2G contributions: writes G' (and the
+// stress), leaves the stencil, A = -dt V_p (4/dx^2) tau + m_p C and m_p v.
+template <typename T, int D>
+__device__ __forceinline__ bool p2g_particle(const KCfg& c, const Bufs& b, const InstDev& I, int inst,
+                                             const Part<T, D>& q, const P<T, D>& si, const P<T, D>& so, int64_t p,
+                                             Stencil<T, D>& S,
+                                             T (&A)[3][3], T (&vel)[3], T* tau_out) {
+  const T dt = T(I.dt), mp = T(I.mp);
+  const T(&Cm)[3][3] = q.C;
+  const T(&Gm)[3][3] = q.G;
+  T Ft[3][3];
 #pragma unroll
   for (int a = 0; a < D; ++a)
 #pragma unroll
@@ -423,6 +438,16 @@ __device__ __forceinline__ void put_record(RunLDS<T>& L, int t, const T (&q)[3],
   }
 }
 
+template <typename T> struct RunRec { T g[4][4], w4[2]; };
+template <typename T, int D> __device__ __forceinline__ RunRec<T> read_record(const RunLDS<T>& L, int t) {
+  RunRec<T> R;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) ld4<T>(L.rec[k][t], R.g[k]);
+  R.w4[0] = R.w4[1] = T(0);
+  if (D == 3) { R.w4[0] = L.w4[t][0]; R.w4[1] = L.w4[t][1]; }
+  return R;
+}
+
 // Phase 2 for a round of rc slots whose records and wbase are in L (the
 // caller synchronised after writing them).  NV = D + 1 scatters momentum and
 // mass (mass per particle m); NV = D scatters a D-vector.  Work items cover
@@ -437,6 +462,11 @@ __device__ __forceinline__ void put_record(RunLDS<T>& L, int t, const T (&q)[3],
 // whose base cell lies in residue class k (window coordinates modulo 3 per
 // axis), whose 3^D stencils are disjoint, so that every node receives at most
 // one addition per pass and the passes fix the order.
+// An item is a serial chain over its run's particles (about 3.6 us a round on
+// an otherwise empty CU): its record reads are issued one particle ahead of
+// the sums.  Reading ahead the next round's particle states as well costs
+// registers (three waves per SIMD, or scratch) and was slower: 118 and 129 us
+// against 99 us per P2G launch of 1.8 M particles.
 template <int D>
 __device__ __forceinline__ int base_class(int wbase) {
   const int i = wbase / Win<D>::xs, r = wbase - i * Win<D>::xs;
@@ -450,7 +480,8 @@ __device__ void run_scatter_round(RunLDS<T>& L, int rc, double* win, T m) {
   constexpr int NJ = NN / 3;                                  // rows per item
   constexpr int ITEMS = (D == 3 ? 9 : 3) / NJ;                // items per run
   const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
-  const bool flag = t < rc && L.wbase[t] >= 0 && (t == 0 || L.wbase[t] != L.wbase[t - 1]);
+  // slots without a window record (-1) form runs of their own, skipped below
+  const bool flag = t < rc && (t == 0 || L.wbase[t] != L.wbase[t - 1]);
   const unsigned long long bal = __ballot(flag);
   if (lane == 0) L.wcount[wid] = __popcll(bal);
   __syncthreads();
@@ -468,7 +499,7 @@ __device__ void run_scatter_round(RunLDS<T>& L, int rc, double* win, T m) {
     const int j0 = NJ == 3 ? 0 : (D == 3 ? sub % 3 : sub);
     const int s0 = L.start[r], s1 = L.start[r + 1];
     const int base = L.wbase[s0];
-    if (NCOL > 1 && base_class<D>(base) != col) continue;
+    if (base < 0 || (NCOL > 1 && base_class<D>(base) != col)) continue;
     // acc[row j][node k][value]: 3D node (o0, j0 + j, k), 2D node (j0 + j, k)
     T acc[NJ][3][4];
 #pragma unroll
@@ -477,14 +508,12 @@ __device__ void run_scatter_round(RunLDS<T>& L, int rc, double* win, T m) {
       for (int k = 0; k < 3; ++k)
 #pragma unroll
         for (int a = 0; a < 4; ++a) acc[j][k][a] = T(0);
+    // the next particle's record is read while this one's is summed
+    RunRec<T> nx = read_record<T, D>(L, s0);
     for (int sl = s0; sl < s1; ++sl) {
-      if (L.wbase[sl] != base) continue;            // a particle without a window record
-      T g0[4], g1[4], g2[4], g3[4], g4[4] = {T(0), T(0), T(0), T(0)};
-      ld4<T>(L.rec[0][sl], g0);
-      ld4<T>(L.rec[1][sl], g1);
-      ld4<T>(L.rec[2][sl], g2);
-      ld4<T>(L.rec[3][sl], g3);
-      if (D == 3) { g4[0] = L.w4[sl][0]; g4[1] = L.w4[sl][1]; }
+      const RunRec<T> R = nx;
+      nx = read_record<T, D>(L, min(sl + 1, kBlock - 1));
+      const T(&g0)[4] = R.g[0], (&g1)[4] = R.g[1], (&g2)[4] = R.g[2], (&g3)[4] = R.g[3], (&g4)[2] = R.w4;
       // per-axis weights
       const T wa[3] = {g0[3], T(1) - g0[3] - g1[3], g1[3]};
       const T wb[3] = {g2[3], T(1) - g2[3] - g3[3], g3[3]};
@@ -559,11 +588,12 @@ __device__ void mark_stencil_blocks(const KCfg& c, int inst, const int base[3], 
 template <typename T, int D, typename Emit>
 __device__ __forceinline__ void scatter_stencil(const T (&wt)[3][3], const T (&q)[3], const T (&B)[3][3], T m,
                                                 Emit&& emit) {
-#pragma unroll
+  // rolled loops: the rare path of P2G, kept small in code and registers
+#pragma unroll 1
   for (int o0 = 0; o0 < 3; ++o0)
-#pragma unroll
+#pragma unroll 1
     for (int o1 = 0; o1 < 3; ++o1) {
-      const T wxy = wt[0][o0] * wt[1][o1];
+      const T wxy = sel3(wt[0], o0) * sel3(wt[1], o1);
       T t[3] = {T(0), T(0), T(0)};
 #pragma unroll
       for (int a = 0; a < D; ++a) t[a] = q[a] + T(o0) * B[a][0] + T(o1) * B[a][1];
@@ -589,7 +619,7 @@ __device__ __forceinline__ void scatter_stencil(const T (&wt)[3][3], const T (&q
 // window (drifted more than one cell since binning) add to the outlier grid
 // with global atomics and put their node blocks in the active set.
 template <typename T, int D, bool DET>
-__global__ void __launch_bounds__(kBlock) k_p2g(KCfg c, Bufs b, TileList tl, const void* st_in, void* st_out,
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) k_p2g(KCfg c, Bufs b, TileList tl, const void* st_in, void* st_out,
                                                 T* __restrict__ stg, T* __restrict__ gout, ActiveSet act,
                                                 T* __restrict__ tau_out) {
   __shared__ double win[Win<D>::stride * kNodeVals];
@@ -603,17 +633,19 @@ __global__ void __launch_bounds__(kBlock) k_p2g(KCfg c, Bufs b, TileList tl, con
     const InstDev& I = b.inst[inst];
     T* g = gout + I.goff * kNodeVals;
     const T mpt = T(I.mp);
-    for (int i = threadIdx.x; i < Win<D>::stride * kNodeVals; i += kBlock) win[i] = 0.0;
     const int cnt = (int)(tr.end - tr.start);
+    Part<T, D> part;
+    for (int i = threadIdx.x; i < Win<D>::stride * kNodeVals; i += kBlock) win[i] = 0.0;
     for (int r0 = 0; r0 < cnt; r0 += kBlock) {
       const int rc = min(kBlock, cnt - r0);
+      const int64_t p0 = (int64_t)tr.start + r0;
       int wb = -1;
       if (threadIdx.x < rc) {
-        const int64_t p0 = (int64_t)tr.start + r0;
         const P<T, D> si = pv<T, D>(st_in, c.ntot).at(p0), so = pv<T, D>(st_out, c.ntot).at(p0);
+        load_part<T, D>(si, threadIdx.x, part);
         Stencil<T, D> S;
         T A[3][3], vel[3];
-        if (p2g_particle<T, D>(c, b, I, inst, si, so, threadIdx.x, S, A, vel, tau_out ? tau_out + p0 : nullptr)) {
+        if (p2g_particle<T, D>(c, b, I, inst, part, si, so, threadIdx.x, S, A, vel, tau_out ? tau_out + p0 : nullptr)) {
           // node o receives w_o (q + B o) and w_o m_p with q = m_p v - A f dx and
           // B = A dx (the MLS-MPM momentum m_p v + A (x_i - x_p), x_i - x_p = (o - f) dx)
           T q[3] = {T(0), T(0), T(0)}, B[3][3] = {{T(0), T(0), T(0)}, {T(0), T(0), T(0)}, {T(0), T(0), T(0)}};
@@ -644,6 +676,8 @@ __global__ void __launch_bounds__(kBlock) k_p2g(KCfg c, Bufs b, TileList tl, con
         }
       }
       rl.wbase[threadIdx.x] = wb;
+      // the next round's states are on their way while this round is scattered
+      // (the barriers wait for LDS only)
       __syncthreads();
       run_scatter_round<T, D, D + 1, 9, DET ? (D == 3 ? 27 : 9) : 1>(rl, rc, win, mpt);
     }
