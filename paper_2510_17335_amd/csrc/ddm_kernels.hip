@@ -1849,17 +1849,21 @@ void launch_grid_adj(int prec, const KCfg& c, const Bufs& b, int step, const uin
 }
 
 // ---------------------------------------------------------------------------
-// Adjoint of P2G and of the constitutive update, in two kernels so that the
-// 27-node gather and the SVD-frame adjoint do not hold registers at the same
-// time.
-//  k_p2g_adj_gather: rebuilds A = k tau + m_p C from the stored stress, gathers the
-//    grid adjoints (m bar, mv bar) over the stencil and writes x bar (adding
-//    to the G2P part already there), v bar, and A bar into the C bar rows;
-//    the density adjoint V_p (m_p bar + A bar : C) is block-reduced.
-//  k_p2g_adj_constit: tau bar = k A bar, back through the return map and the
-//    SVD (isotropic-function adjoint) and F_tmp = (I + dt C)(I + G); writes
-//    G bar and C bar = m_p A bar + dt F_tmp bar (I + G)^T; material adjoints
+// Adjoint of P2G and of the constitutive update, one particle per thread, in
+// two halves whose registers are not live at the same time:
+//  - rebuilds A = k tau + m_p C from the stored stress, gathers the grid
+//    adjoints (m bar, mv bar) over the stencil, writes x bar (adding to the G2P
+//    part already there) and v bar, and keeps A bar; the density adjoint
+//    V_p (m_p bar + A bar : C) is block-reduced;
+//  - tau bar = k A bar, back through the return map and the SVD
+//    (isotropic-function adjoint) and F_tmp = (I + dt C)(I + G); writes G bar
+//    and C bar = m_p A bar + dt F_tmp bar (I + G)^T; material adjoints
 //    (mu, lambda, alpha, k_c) are block-reduced in double.
+// One kernel since both halves fit four waves per SIMD: as two, A bar went
+// through memory (72 of 372 B per particle) and C was read twice: 193 us per
+// sub-step at 1.8 M particles (FP32) against 133 us, 42 against 28 at 219 488,
+// 18.5 against 14.8 at 27 440; HBM alone needs 79 us at 1.8 M (264 B a
+// particle at 6 TB/s), the rest is the two halves' arithmetic.
 // ---------------------------------------------------------------------------
 template <typename T, int D>
 __device__ __forceinline__ void ftmp_of(const P<T, D>& st, int64_t p, T dt, T Cm[3][3], T Gm[3][3], T Ft[3][3]) {
@@ -1879,17 +1883,19 @@ __device__ __forceinline__ void ftmp_of(const P<T, D>& st, int64_t p, T dt, T Cm
 }
 
 template <typename T, int D, bool SF>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1))) k_p2g_adj_gather(KCfg c, Bufs b, const void* stv, const T* __restrict__ tau,
-                                                           const T* __restrict__ gbar, void* adj_cur, double* pacc) {
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1)))
+k_p2g_adj(KCfg c, Bufs b, const void* stv, const T* __restrict__ tau, const T* __restrict__ gbar, const void* adj_next,
+          void* adj_cur, double* pacc) {
   const int inst = b.blk_inst[blockIdx.x];
   const InstDev& I = b.inst[inst];
   const int64_t p0 = (int64_t)blockIdx.x * kBlock;
   const uint32_t p = threadIdx.x;
-  double acc[1] = {0.0};
+  double acc[5] = {0, 0, 0, 0, 0};        // mu, lambda, alpha, k_c, rho
   if ((int64_t)p < I.n - (p0 - I.off)) {
     const P<T, D> st = pv<T, D>(stv, c.ntot).at(p0);
-    const Adj<T, D> ac = av<T, D>(adj_cur, c.ntot).at(p0);
+    const Adj<T, D> an = av<T, D>(adj_next, c.ntot).at(p0), ac = av<T, D>(adj_cur, c.ntot).at(p0);
     const T* tp = tau + p0;
+    T Ab[3][3] = {{T(0), T(0), T(0)}, {T(0), T(0), T(0)}, {T(0), T(0), T(0)}};
     Stencil<T, D> S;
     if (make_stencil<T, D>(st, p, c, S)) {
       const T dt = T(I.dt), mp = T(I.mp), dx = T(c.dx), inv_dx = T(c.inv_dx);
@@ -1940,7 +1946,6 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(siz
 #pragma unroll
       for (int a = 0; a < D; ++a) { mvv[a] = mp * vel[a]; Bl[a] = A[a][D - 1] * dx; }
       T G[3] = {T(0), T(0), T(0)}, Gm = T(0), xg[3] = {T(0), T(0), T(0)};
-      T Ab[3][3] = {{T(0), T(0), T(0)}, {T(0), T(0), T(0)}, {T(0), T(0), T(0)}};
 #pragma unroll
       for (int o0 = 0; o0 < 3; ++o0)
 #pragma unroll
@@ -2006,7 +2011,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(siz
         ac.x(a, p) = xb[a];
         ac.v(a, p) = vb[a];
 #pragma unroll
-        for (int bb = 0; bb < D; ++bb) { ac.C(a, bb, p) = Ab[a][bb]; mpb += Ab[a][bb] * Cm[a][bb]; }
+        for (int bb = 0; bb < D; ++bb) mpb += Ab[a][bb] * Cm[a][bb];
       }
       if (SF) {
         T sab = T(0);
@@ -2014,36 +2019,21 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(siz
         for (int a = 0; a < D; ++a)
 #pragma unroll
           for (int bb = 0; bb < D; ++bb) sab += scalar_base(tp + (int64_t)sym_row<D>(a, bb) * c.ntot)[p] * Ab[a][bb];
-        acc[0] = -(double)(k_str * sab) * (I.Vp / I.mp);
+        acc[4] = -(double)(k_str * sab) * (I.Vp / I.mp);
       } else {
-        acc[0] = (double)mpb * I.Vp;
+        acc[4] = (double)mpb * I.Vp;
       }
     }
-  }
-  block_accumulate<1>(acc, pacc + (int64_t)inst * 8 + 4, b.dpart);
-}
-
-template <typename T, int D>
-__global__ void __launch_bounds__(kBlock) k_p2g_adj_constit(KCfg c, Bufs b, const void* stv, const void* adj_next,
-                                                            void* adj_cur, double* pacc) {
-  const int inst = b.blk_inst[blockIdx.x];
-  const InstDev& I = b.inst[inst];
-  const int64_t p0 = (int64_t)blockIdx.x * kBlock;
-  const uint32_t p = threadIdx.x;
-  double acc[4] = {0, 0, 0, 0};
-  if ((int64_t)p < I.n - (p0 - I.off)) {
-    const P<T, D> st = pv<T, D>(stv, c.ntot).at(p0);
-    const Adj<T, D> an = av<T, D>(adj_next, c.ntot).at(p0), ac = av<T, D>(adj_cur, c.ntot).at(p0);
+    __builtin_amdgcn_sched_barrier(0);     // the second half's loads after the first half's registers are free
     const T dt = T(I.dt), mp = T(I.mp);
     const T mu = T(I.mu), lam = T(I.lam), al = T(I.alpha), kc = T(I.kc);
     const T k_str = -dt * T(I.Vp) * T(4.0 * c.inv_dx * c.inv_dx);
-    T Cm[3][3], Gm[3][3], Ft[3][3], Ab[3][3], taub[3][3], Fnb[3][3];
+    T Cm[3][3], Gm[3][3], Ft[3][3], taub[3][3], Fnb[3][3];
     ftmp_of<T, D>(st, p, dt, Cm, Gm, Ft);
 #pragma unroll
     for (int a = 0; a < D; ++a)
 #pragma unroll
       for (int bb = 0; bb < D; ++bb) {
-        Ab[a][bb] = ac.C(a, bb, p);
         taub[a][bb] = k_str * Ab[a][bb];
         Fnb[a][bb] = an.G(a, bb, p);
       }
@@ -2070,21 +2060,19 @@ __global__ void __launch_bounds__(kBlock) k_p2g_adj_constit(KCfg c, Bufs b, cons
     acc[2] = (double)alb;
     acc[3] = (double)kcb;
   }
-  block_accumulate<4>(acc, pacc + (int64_t)inst * 8, b.dpart);
+  block_accumulate<5>(acc, pacc + (int64_t)inst * 8, b.dpart);
 }
 
 void launch_p2g_adj(int prec, const KCfg& c, const Bufs& b, int nblk, const void* st, const void* tau, const void* gb,
                     bool stress_form, const void* adj_next, void* adj_cur, double* pacc, hipStream_t s) {
-#define DDM_P2GADJ(T, DD)                                                                                          \
+#define DDM_P2GADJ(T, DD)                                                                                            \
   if (stress_form)                                                                                                 \
-    hipLaunchKernelGGL((k_p2g_adj_gather<T, DD, true>), dim3(nblk), dim3(kBlock), 0, s, c, b, st,                  \
-                       (const T*)tau, (const T*)gb, adj_cur, pacc);                                                \
+    hipLaunchKernelGGL((k_p2g_adj<T, DD, true>), dim3(nblk), dim3(kBlock), 0, s, c, b, st, (const T*)tau,           \
+                       (const T*)gb, adj_next, adj_cur, pacc);                                                      \
   else                                                                                                             \
-    hipLaunchKernelGGL((k_p2g_adj_gather<T, DD, false>), dim3(nblk), dim3(kBlock), 0, s, c, b, st,                 \
-                       (const T*)tau, (const T*)gb, adj_cur, pacc);                                                \
-  if (b.dpart) launch_det_finish(c, b, false, 1, pacc + 4, 8, s);                                                  \
-  hipLaunchKernelGGL((k_p2g_adj_constit<T, DD>), dim3(nblk), dim3(kBlock), 0, s, c, b, st, adj_next, adj_cur, pacc); \
-  if (b.dpart) launch_det_finish(c, b, false, 4, pacc, 8, s);
+    hipLaunchKernelGGL((k_p2g_adj<T, DD, false>), dim3(nblk), dim3(kBlock), 0, s, c, b, st, (const T*)tau,          \
+                       (const T*)gb, adj_next, adj_cur, pacc);                                                      \
+  if (b.dpart) launch_det_finish(c, b, false, 5, pacc, 8, s);
   if (prec == 0) {
     if (c.dim == 3) { DDM_P2GADJ(float, 3) } else { DDM_P2GADJ(float, 2) }
   } else {
