@@ -111,13 +111,9 @@ void launch_diagnostics(int prec, const KCfg& c, const Bufs& b, int nblk, const 
 void launch_eval_math(int fn, const float* x, float* y, int64_t n, hipStream_t s);
 void launch_fill_u32(void* p, int64_t words, uint32_t value, hipStream_t s);
 // Particle state from positions x0[n][D] (instances concatenated): v = 0, C = 0,
-// G = 0 and ids; positions_only writes the position rows and ids alone.
+// G = 0 and ids.
 void launch_init_state(int prec, const KCfg& c, const Bufs& b, int nblk, const void* x0, void* state,
-                       uint32_t* pid, hipStream_t s, bool positions_only = false);
-// Up to kBlobWords * 4 bytes from host memory to device memory, carried in the
-// arguments of a one-block kernel (no host buffer has to outlive the call).
-constexpr int kBlobWords = 128;
-void launch_put_bytes(void* dst, const void* src, size_t bytes, hipStream_t s);
+                       uint32_t* pid, hipStream_t s);
 // P2G writes every occupied tile's window to the staging buffer; particles
 // that left their window add to the dense outlier grid gout (kept zero
 // otherwise) and add their node blocks to the active set.
@@ -163,8 +159,14 @@ struct LossBufs {
   double* dldm;                      // [n_inst]
   double* loss;                      // [n_inst]
 };
+// cleared: the height map, owners and scoop masses are empty already.
 void launch_loss(int prec, const KCfg& c, const Bufs& b, int nblk, const void* state, const uint32_t* pid,
-                 int final_step, const LossBufs& L, hipStream_t s);
+                 int final_step, const LossBufs& L, bool cleared, hipStream_t s);
+// One instance's buffers for a loss without a context (constants and pose row
+// from host memory, carried in the kernel's arguments; positions x0[n][D]).
+void launch_loss_prepare(int prec, const KCfg& c, const InstDev& I, const double* pose_row, const void* x0,
+                         InstDev* inst, void* pose, int* blk, DevErr* err, void* state, uint32_t* pid,
+                         const LossBufs& L, hipStream_t s);
 void launch_loss_seed(int prec, const KCfg& c, const Bufs& b, int nblk, const void* state, const uint32_t* pid,
                       int final_step, const LossBufs& L, void* adj, double* pacc, hipStream_t s);
 

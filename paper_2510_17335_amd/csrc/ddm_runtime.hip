@@ -1034,7 +1034,7 @@ ddm_status ddm_loss(ddm_ctx* x, const double* target_hm_dev, double* loss_dev) {
   {
     Timed t(x, 8);
     ddm::launch_loss(x->prec, x->kc, x->bufs(), (int)x->L.nblk, x->cur(), x->pid(),
-                     (int)x->steps - 1, x->lossbufs(), x->stream);
+                     (int)x->steps - 1, x->lossbufs(), false, x->stream);
     if (x->cfg.w_emd != 0.0)
       ddm::launch_emd(x->prec, x->kc, x->bufs(), (int)x->L.nblk, x->cur(), x->pid(), x->emdbufs(), x->emd_m,
                       x->cfg.w_emd, x->at<double>(x->L.loss), x->stream);
@@ -1617,19 +1617,12 @@ ddm_status ddm_loss_noalloc(const ddm_config* cfg, const ddm_instance* inst, int
     row[8] = std::sin(row[3]);
     row[9] = std::cos(row[3]);
   }
-  float rowf[ddm::kPoseVals];
-  for (int k = 0; k < ddm::kPoseVals; ++k) rowf[k] = (float)row[k];
-  ddm::launch_put_bytes(sc + A.inst, &dev, sizeof(dev), st);
-  ddm::launch_put_bytes(sc + A.poses, prec ? (const void*)row : (const void*)rowf, (size_t)ddm::kPoseVals * esz, st);
-  ddm::launch_fill_zero(sc + A.err, sizeof(ddm::DevErr) / 4, 4, st);
-  ddm::launch_fill_zero(sc + A.blk, nblk, 4, st);            // every block belongs to instance 0
   ddm::Bufs b;
   b.inst = reinterpret_cast<const ddm::InstDev*>(sc + A.inst);
   b.blk_inst = reinterpret_cast<const int*>(sc + A.blk);
   b.poses = sc + A.poses;
   b.err = reinterpret_cast<ddm::DevErr*>(sc + A.err);
   uint32_t* pid = reinterpret_cast<uint32_t*>(sc + A.pid);
-  ddm::launch_init_state(prec, kc, b, (int)nblk, x_dev, sc + A.x, pid, st, true);
   ddm::LossBufs lb;
   lb.hm_bits = reinterpret_cast<unsigned long long*>(sc + A.hm_bits);
   lb.owner = reinterpret_cast<unsigned int*>(sc + A.owner);
@@ -1639,7 +1632,9 @@ ddm_status ddm_loss_noalloc(const ddm_config* cfg, const ddm_instance* inst, int
   lb.region = reinterpret_cast<double*>(sc + A.region);
   lb.dldm = reinterpret_cast<double*>(sc + A.dldm);
   lb.loss = loss_dev;
-  ddm::launch_loss(prec, kc, b, (int)nblk, sc + A.x, pid, final_step >= 0 ? 0 : -1, lb, st);
+  ddm::launch_loss_prepare(prec, kc, dev, row, x_dev, reinterpret_cast<ddm::InstDev*>(sc + A.inst), sc + A.poses,
+                           reinterpret_cast<int*>(sc + A.blk), b.err, sc + A.x, pid, lb, st);
+  ddm::launch_loss(prec, kc, b, (int)nblk, sc + A.x, pid, final_step >= 0 ? 0 : -1, lb, true, st);
   return launch_status();
 }
 
