@@ -384,16 +384,16 @@ __device__ __forceinline__ bool p2g_particle(const KCfg& c, const Bufs& b, const
 // and every atomic instruction costs the same whether 1 or 64 lanes are
 // active, so the gain comes from issuing about 1/ppc as many atomics.
 // ---------------------------------------------------------------------------
-template <typename T> struct alignas(16) RunLDS {
+template <typename T, int BLK> struct alignas(16) RunLDS {
   // group g of slot t (w_a^k: weight of offset k on axis a; w_a^1 = 1 - w_a^0 - w_a^2):
   //   0: q0 q1 q2 w_0^0   1: B00 B01 B02 w_0^2   2: B10 B11 B12 w_1^0
   //   3: B20 B21 B22 w_1^2   and w4: w_2^0 w_2^2
   // (kept small: the G2P adjoint fits 4 workgroups per CU at 40 KB of LDS)
-  T rec[4][kBlock][4];
-  T w4[kBlock][2];
-  short wbase[kBlock];
-  int wcount[kBlock / 64];
-  unsigned short start[kBlock + 1];
+  T rec[4][BLK][4];
+  T w4[BLK][2];
+  short wbase[BLK];
+  int wcount[BLK / 64];
+  unsigned short start[BLK + 1];
 };
 
 template <typename T> __device__ __forceinline__ void st4(T* p, T a, T b, T c, T d) { p[0] = a; p[1] = b; p[2] = c; p[3] = d; }
@@ -407,8 +407,8 @@ template <> __device__ __forceinline__ void ld4<float>(const float* p, float (&o
 }
 
 // Phase-1 record of slot t: q, B and the stencil weights w[axis][offset].
-template <typename T, int D>
-__device__ __forceinline__ void put_record(RunLDS<T>& L, int t, const T (&q)[3], const T (&B)[3][3], const T (&w)[3][3]) {
+template <typename T, int D, int BLK>
+__device__ __forceinline__ void put_record(RunLDS<T, BLK>& L, int t, const T (&q)[3], const T (&B)[3][3], const T (&w)[3][3]) {
   st4<T>(L.rec[0][t], q[0], q[1], D == 3 ? q[2] : T(0), w[0][0]);
   st4<T>(L.rec[1][t], B[0][0], B[0][1], D == 3 ? B[0][2] : T(0), w[0][2]);
   st4<T>(L.rec[2][t], B[1][0], B[1][1], D == 3 ? B[1][2] : T(0), w[1][0]);
@@ -422,7 +422,8 @@ __device__ __forceinline__ void put_record(RunLDS<T>& L, int t, const T (&q)[3],
 }
 
 template <typename T> struct RunRec { T g[4][4], w4[2]; };
-template <typename T, int D> __device__ __forceinline__ RunRec<T> read_record(const RunLDS<T>& L, int t) {
+template <typename T, int D, int BLK>
+__device__ __forceinline__ RunRec<T> read_record(const RunLDS<T, BLK>& L, int t) {
   RunRec<T> R;
 #pragma unroll
   for (int k = 0; k < 4; ++k) ld4<T>(L.rec[k][t], R.g[k]);
@@ -457,25 +458,27 @@ __device__ __forceinline__ int base_class(int wbase) {
   return ((i % 3) * 3 + (r / kWin) % 3) * 3 + (r % kWin) % 3;
 }
 
-template <typename T, int D, int NV, int NN, int NCOL>
-__device__ void run_scatter_round(RunLDS<T>& L, int rc, double* win, T m) {
+template <typename T, int D, int NV, int NN, int NCOL, int BLK>
+__device__ void run_scatter_round(RunLDS<T, BLK>& L, int rc, double* win, T m) {
   constexpr int WS = Win<D>::stride;
   constexpr int NJ = NN / 3;                                  // rows per item
   constexpr int ITEMS = (D == 3 ? 9 : 3) / NJ;                // items per run
   const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
-  // slots without a window record (-1) form runs of their own, skipped below
-  const bool flag = t < rc && (t == 0 || L.wbase[t] != L.wbase[t - 1]);
+  // slots without a window record (-1) form runs of their own, skipped below;
+  // a run also ends every kBlock slots, so that its FP32 sums do not depend on
+  // the width of the workgroup
+  const bool flag = t < rc && (t % kBlock == 0 || L.wbase[t] != L.wbase[t - 1]);
   const unsigned long long bal = __ballot(flag);
   if (lane == 0) L.wcount[wid] = __popcll(bal);
   __syncthreads();
   int off = 0, tot = 0;
 #pragma unroll
-  for (int w = 0; w < kBlock / 64; ++w) { off += w < wid ? L.wcount[w] : 0; tot += L.wcount[w]; }
+  for (int w = 0; w < BLK / 64; ++w) { off += w < wid ? L.wcount[w] : 0; tot += L.wcount[w]; }
   if (flag) L.start[off + __popcll(bal & ((1ull << lane) - 1ull))] = (unsigned short)t;
   if (t == 0) L.start[tot] = (unsigned short)rc;
   __syncthreads();
   for (int col = 0; col < NCOL; ++col) {
-  for (int it = t; it < tot * ITEMS; it += kBlock) {
+  for (int it = t; it < tot * ITEMS; it += BLK) {
     const int r = it / ITEMS, sub = it - r * ITEMS;
     // the item's first row: 3D (o0, j0), 2D j0; rows j0 .. j0 + NJ - 1 along the middle axis
     const int o0 = D == 3 ? (NJ == 3 ? sub : sub / 3) : 0;
@@ -492,10 +495,10 @@ __device__ void run_scatter_round(RunLDS<T>& L, int rc, double* win, T m) {
 #pragma unroll
         for (int a = 0; a < 4; ++a) acc[j][k][a] = T(0);
     // the next particle's record is read while this one's is summed
-    RunRec<T> nx = read_record<T, D>(L, s0);
+    RunRec<T> nx = read_record<T, D, BLK>(L, s0);
     for (int sl = s0; sl < s1; ++sl) {
       const RunRec<T> R = nx;
-      nx = read_record<T, D>(L, min(sl + 1, kBlock - 1));
+      nx = read_record<T, D, BLK>(L, min(sl + 1, BLK - 1));
       const T(&g0)[4] = R.g[0], (&g1)[4] = R.g[1], (&g2)[4] = R.g[2], (&g3)[4] = R.g[3], (&g4)[2] = R.w4;
       // per-axis weights
       const T wa[3] = {g0[3], T(1) - g0[3] - g1[3], g1[3]};
@@ -601,12 +604,12 @@ __device__ __forceinline__ void scatter_stencil(const T (&wt)[3][3], const T (&q
 // grid update sums the windows covering each node.  Particles outside the
 // window (drifted more than one cell since binning) add to the outlier grid
 // with global atomics and put their node blocks in the active set.
-template <typename T, int D, bool DET>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) k_p2g(KCfg c, Bufs b, TileList tl, const void* st_in, void* st_out,
-                                                T* __restrict__ stg, T* __restrict__ gout, ActiveSet act,
-                                                T* __restrict__ tau_out) {
+template <typename T, int D, bool DET, int BLK>
+__global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
+k_p2g(KCfg c, Bufs b, TileList tl, const void* st_in, void* st_out, T* __restrict__ stg, T* __restrict__ gout,
+      ActiveSet act, T* __restrict__ tau_out) {
   __shared__ double win[Win<D>::stride * kNodeVals];
-  __shared__ RunLDS<T> rl;
+  __shared__ RunLDS<T, BLK> rl;
   const uint32_t ntiles = *tl.count;
   __shared__ uint32_t tile_slot;
   for (uint32_t t = first_tile(tl, &tile_slot); t < ntiles; t = next_tile(tl, t, &tile_slot)) {
@@ -618,9 +621,9 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(siz
     const T mpt = T(I.mp);
     const int cnt = (int)(tr.end - tr.start);
     Part<T, D> part;
-    for (int i = threadIdx.x; i < Win<D>::stride * kNodeVals; i += kBlock) win[i] = 0.0;
-    for (int r0 = 0; r0 < cnt; r0 += kBlock) {
-      const int rc = min(kBlock, cnt - r0);
+    for (int i = threadIdx.x; i < Win<D>::stride * kNodeVals; i += BLK) win[i] = 0.0;
+    for (int r0 = 0; r0 < cnt; r0 += BLK) {
+      const int rc = min(BLK, cnt - r0);
       const int64_t p0 = (int64_t)tr.start + r0;
       int wb = -1;
       if (threadIdx.x < rc) {
@@ -646,7 +649,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(siz
           for (int a = 0; a < D; ++a) { loc[a] = S.base[a] - org[a]; inwin &= loc[a] >= 0 && loc[a] <= kWin - 3; }
           if (inwin) {
             wb = Win<D>::idx(loc[0], loc[1], loc[2]);
-            put_record<T, D>(rl, threadIdx.x, q, B, S.w);
+            put_record<T, D, BLK>(rl, threadIdx.x, q, B, S.w);
           } else {
             mark_stencil_blocks<D>(c, inst, S.base, act);
             scatter_stencil<T, D>(S.w, q, B, mpt, [&](int o0, int o1, int o2, const T (&v)[4]) {
@@ -662,12 +665,12 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(siz
       // the next round's states are on their way while this round is scattered
       // (the barriers wait for LDS only)
       __syncthreads();
-      run_scatter_round<T, D, D + 1, 9, DET ? (D == 3 ? 27 : 9) : 1>(rl, rc, win, mpt);
+      run_scatter_round<T, D, D + 1, 9, DET ? (D == 3 ? 27 : 9) : 1, BLK>(rl, rc, win, mpt);
     }
     __syncthreads();
     // the whole window, zeros included, to the tile's staging record
     T* rec = stg + (int64_t)t * (kNodeVals * Win<D>::nodes);
-    for (int i = threadIdx.x; i < Win<D>::nodes; i += kBlock) {
+    for (int i = threadIdx.x; i < Win<D>::nodes; i += BLK) {
       int l[3];
       Win<D>::coords(i, l);
       const int wi = Win<D>::idx(l[0], l[1], l[2]);
@@ -686,19 +689,20 @@ void launch_det_finish(const KCfg& c, const Bufs& b, bool grid_blocks, int nvals
 
 void launch_p2g(int prec, const KCfg& c, const Bufs& b, const TileList& tl, int nwg, const void* st_in, void* st_out,
                 const Staging& stg, void* gout, const ActiveSet& act, void* tau_out, hipStream_t s) {
-#define DDM_P2G(T, DD)                                                                                             \
-  if (c.det)                                                                                                       \
-    hipLaunchKernelGGL((k_p2g<T, DD, true>), dim3(nwg), dim3(kBlock), 0, s, c, b, tl, st_in, st_out, (T*)stg.win,  \
-                       (T*)gout, act, (T*)tau_out);                                                                \
-  else                                                                                                             \
-    hipLaunchKernelGGL((k_p2g<T, DD, false>), dim3(nwg), dim3(kBlock), 0, s, c, b, tl, st_in, st_out, (T*)stg.win, \
-                       (T*)gout, act, (T*)tau_out)
+#define DDM_P2G_(T, DD, DET, BLK)                                                                                     \
+  hipLaunchKernelGGL((k_p2g<T, DD, DET, BLK>), dim3(nwg), dim3(BLK), 0, s, c, b, tl, st_in, st_out, (T*)stg.win,    \
+                     (T*)gout, act, (T*)tau_out)
+#define DDM_P2G(T, DD)                                                                                              \
+  if (c.det) DDM_P2G_(T, DD, true, kBlock);                                                                         \
+  else if (DD == 3 && c.wide) DDM_P2G_(T, DD, false, (DD == 3 ? 2 * kBlock : kBlock));                              \
+  else DDM_P2G_(T, DD, false, kBlock)
   if (prec == 0) {
     if (c.dim == 3) { DDM_P2G(float, 3); } else { DDM_P2G(float, 2); }
   } else {
     if (c.dim == 3) { DDM_P2G(double, 3); } else { DDM_P2G(double, 2); }
   }
 #undef DDM_P2G
+#undef DDM_P2G_
 }
 
 // Blade pose of one sub-step (tip, angle, velocities) from the pose table.
@@ -1501,12 +1505,12 @@ void launch_loss_seed(int prec, const KCfg& c, const Bufs& b, int nblk, const vo
 //   xbar = x'bar + sum_i [grad w (v_i . vb + (4/dx^2) v_i^T C'bar r) - (4/dx^2) w C'bar^T v_i]
 //   v_i bar += w (vb + (4/dx^2) C'bar r)            (scattered to the grid)
 // ---------------------------------------------------------------------------
-template <typename T, int D, bool DET>
-__global__ void __launch_bounds__(kBlock) k_g2p_adj(KCfg c, Bufs b, TileList tl, const void* stv,
-                                                    const T* __restrict__ post, const void* adj_next, void* adj_cur,
-                                                    T* __restrict__ gvb, T* __restrict__ stg) {
+template <typename T, int D, bool DET, int BLK>
+__global__ void __launch_bounds__(BLK) k_g2p_adj(KCfg c, Bufs b, TileList tl, const void* stv,
+                                                 const T* __restrict__ post, const void* adj_next, void* adj_cur,
+                                                 T* __restrict__ gvb, T* __restrict__ stg) {
   __shared__ double win[Win<D>::stride * D];
-  __shared__ RunLDS<T> rl;
+  __shared__ RunLDS<T, BLK> rl;
   __shared__ alignas(16) T gwin[Win<D>::nodes][kNodeVals];     // grid velocities of the tile's window
   const uint32_t ntiles = *tl.count;
   const T dx = T(c.dx), inv_dx = T(c.inv_dx), Dk = T(4.0 * c.inv_dx * c.inv_dx);
@@ -1521,9 +1525,9 @@ __global__ void __launch_bounds__(kBlock) k_g2p_adj(KCfg c, Bufs b, TileList tl,
     const T dt = T(I.dt);
     const T* g = post + I.goff * kNodeVals;
     T* gbv = gvb + I.goff * kNodeVals;
-    for (int i = threadIdx.x; i < WS * D; i += kBlock) win[i] = 0.0;
+    for (int i = threadIdx.x; i < WS * D; i += BLK) win[i] = 0.0;
     // stage the window's grid velocities (nodes outside the grid are never read)
-    for (int i = threadIdx.x; i < Win<D>::nodes; i += kBlock) {
+    for (int i = threadIdx.x; i < Win<D>::nodes; i += BLK) {
       int l[3];
       Win<D>::coords(i, l);
       const int gi[3] = {org[0] + l[0], org[1] + l[1], D == 3 ? org[2] + l[2] : 0};
@@ -1536,8 +1540,8 @@ __global__ void __launch_bounds__(kBlock) k_g2p_adj(KCfg c, Bufs b, TileList tl,
     }
     __syncthreads();
     const int cnt = (int)(tr.end - tr.start);
-    for (int r0 = 0; r0 < cnt; r0 += kBlock) {
-    const int rc = min(kBlock, cnt - r0);
+    for (int r0 = 0; r0 < cnt; r0 += BLK) {
+    const int rc = min(BLK, cnt - r0);
     int wb = -1;
     do {
       if (threadIdx.x >= rc) break;
@@ -1619,7 +1623,7 @@ __global__ void __launch_bounds__(kBlock) k_g2p_adj(KCfg c, Bufs b, TileList tl,
                return ld_node(gwin[wn0 + (D == 3 ? (o0 * kWin + o1) * kWin + o2 : o0 * kWin + o1)]);
              });
         wb = Win<D>::idx(loc[0], loc[1], loc[2]);
-        put_record<T, D>(rl, threadIdx.x, q, B, S.w);
+        put_record<T, D, BLK>(rl, threadIdx.x, q, B, S.w);
       } else {
         body([&](int, int, int, int64_t nd, T w, const T (&t)[3]) {
 #pragma unroll
@@ -1639,10 +1643,10 @@ __global__ void __launch_bounds__(kBlock) k_g2p_adj(KCfg c, Bufs b, TileList tl,
     } while (false);
     rl.wbase[threadIdx.x] = wb;
     __syncthreads();
-    run_scatter_round<T, D, D, 9, DET ? (D == 3 ? 27 : 9) : 1>(rl, rc, win, T(0));
+    run_scatter_round<T, D, D, 9, DET ? (D == 3 ? 27 : 9) : 1, BLK>(rl, rc, win, T(0));
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < Win<D>::nodes; i += kBlock) {
+    for (int i = threadIdx.x; i < Win<D>::nodes; i += BLK) {
       int l[3];
       Win<D>::coords(i, l);
       const int wi = Win<D>::idx(l[0], l[1], l[2]);
@@ -1687,19 +1691,20 @@ __global__ void __launch_bounds__(kBlock) k_adj_windows(KCfg c, Bufs b, const ui
 
 void launch_g2p_adj(int prec, const KCfg& c, const Bufs& b, const TileList& tl, int nwg, const void* st,
                     const void* post, const void* adj_next, void* adj_cur, void* gvb, void* stg, hipStream_t s) {
+#define DDM_G2PADJ_(T, DD, DET, BLK)                                                                             \
+  hipLaunchKernelGGL((k_g2p_adj<T, DD, DET, BLK>), dim3(nwg), dim3(BLK), 0, s, c, b, tl, st, (const T*)post, adj_next, \
+                     adj_cur, (T*)gvb, (T*)stg)
 #define DDM_G2PADJ(T, DD)                                                                                         \
-  if (stg)                                                                                                          \
-    hipLaunchKernelGGL((k_g2p_adj<T, DD, true>), dim3(nwg), dim3(kBlock), 0, s, c, b, tl, st, (const T*)post,      \
-                       adj_next, adj_cur, (T*)gvb, (T*)stg);                                                        \
-  else                                                                                                              \
-    hipLaunchKernelGGL((k_g2p_adj<T, DD, false>), dim3(nwg), dim3(kBlock), 0, s, c, b, tl, st, (const T*)post,     \
-                       adj_next, adj_cur, (T*)gvb, (T*)nullptr)
+  if (stg) DDM_G2PADJ_(T, DD, true, kBlock);                                                                      \
+  else if (DD == 3 && c.wide) DDM_G2PADJ_(T, DD, false, (DD == 3 ? 2 * kBlock : kBlock));                         \
+  else DDM_G2PADJ_(T, DD, false, kBlock)
   if (prec == 0) {
     if (c.dim == 3) { DDM_G2PADJ(float, 3); } else { DDM_G2PADJ(float, 2); }
   } else {
     if (c.dim == 3) { DDM_G2PADJ(double, 3); } else { DDM_G2PADJ(double, 2); }
   }
 #undef DDM_G2PADJ
+#undef DDM_G2PADJ_
 }
 
 void launch_adj_windows(int prec, const KCfg& c, const Bufs& b, const uint32_t* list, const uint32_t* count,

@@ -695,6 +695,20 @@ ddm_status run_segment(ddm_ctx* x, int m, int64_t k_first, int len, const void* 
 // cohesion shift from the friction angle, particle mass and volume, and their
 // derivatives for the final chain rule), the block-to-instance map, and the
 // pose table with its Jacobian; uploaded with synchronous copies.
+// Threads per workgroup of P2G and the G2P adjoint, which take a tile each.  A
+// tile of more than kBlock particles takes kBlock threads several rounds, one
+// after the other; 2 kBlock threads do 512 particles in one.  That is faster
+// while all tiles are resident at once (256 compute units hold two such
+// workgroups each in FP32, one in FP64: registers and LDS): P2G 26.2 -> 20.2 us
+// at 27 440 particles, 25.6 -> 20.4 at 119 168, 28.4 -> 26.1 at 243 200; in FP64
+// 37.0 -> 34.0 at 102 752.  Beyond that the narrow workgroups fill the units
+// better: 29.3 against 29.8 us at 321 632, 99 against 119 at 1.8 M, in FP64 42.9
+// against 51.0 at 196 992.
+bool wide_tiles(const ddm_config& c, int64_t ntot) {
+  const double per_tile = c.ppc * 64.0, tiles = c.precision == DDM_F64 ? 256.0 : 512.0;
+  return c.dim == 3 && per_tile > ddm::kBlock && (double)ntot <= tiles * per_tile;
+}
+
 // Kernel configuration of a context (or of a context-free call) with
 // n_inst instances and ntot padded particle slots.
 ddm::KCfg make_kcfg(const ddm_config& c, int n_inst, int64_t ntot) {
@@ -716,6 +730,7 @@ ddm::KCfg make_kcfg(const ddm_config& c, int n_inst, int64_t ntot) {
   k.w_hm = c.w_hm; k.w_mass = c.w_mass; k.m_target = c.m_target; k.m_ref = c.m_ref;
   k.w_emd = c.w_emd;
   k.det = c.deterministic ? 1 : 0;
+  k.wide = wide_tiles(c, ntot) ? 1 : 0;
   return k;
 }
 
