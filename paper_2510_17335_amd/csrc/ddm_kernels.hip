@@ -768,21 +768,53 @@ __device__ __forceinline__ void gather_windows(const KCfg& c, int inst, const in
       }
 }
 
+// The kernels over active nodes are short chains of dependent loads (about a
+// microsecond each from another XCD's memory), so what does not depend on the
+// node's values is loaded ahead: the listed block before the count is known
+// (the list holds every block of the grid, so a position beyond the count is
+// read in bounds and not used), then the instance's time step and blade pose.
+// Thread t of a workgroup takes node t % NPB of block position (t / NPB).
+template <int D> struct ActiveWalk {
+  static constexpr int NPB = D == 3 ? kTile * kTile * kTile : kTile * kTile;
+  const uint32_t* list;
+  uint32_t last, w, step, gb;
+  __device__ __forceinline__ ActiveWalk(const KCfg& c, const uint32_t* l)
+      : list(l), last((uint32_t)((c.nodes * c.n_inst) / NPB) - 1u), w(blockIdx.x * (kBlock / NPB) + threadIdx.x / NPB),
+        step(gridDim.x * (kBlock / NPB)) {
+    gb = list[min(w, last)];
+  }
+  __device__ __forceinline__ void next() {
+    w += step;
+    gb = list[min(w, last)];
+  }
+  // 3D: a wave has one block, its number in a scalar register
+  __device__ __forceinline__ uint32_t block() const { return D == 3 ? (uint32_t)__builtin_amdgcn_readfirstlane((int)gb) : gb; }
+  __device__ __forceinline__ int64_t item() const { return (int64_t)w * NPB + threadIdx.x % NPB; }
+};
+
+template <typename T> struct NodeConsts { T dt; Blade<T> bl; };
+template <typename T, int D>
+__device__ __forceinline__ NodeConsts<T> node_consts(const KCfg& c, const Bufs& b, int inst, int step) {
+  NodeConsts<T> nc;
+  nc.dt = T(b.inst[inst].dt);
+  if (D == 3 && c.shovel) nc.bl = load_blade<T>(b.poses, inst, c.max_steps, step);
+  return nc;
+}
+
 // Velocity of one node from its momentum and mass (acc = mv, m): v = mv/m + dt g,
-// the shovel contact at the pose of sub-step `step`, the sticky walls; zero
+// the shovel contact at the pose of the sub-step, the sticky walls; zero
 // without mass.
 template <typename T, int D>
-__device__ __forceinline__ void node_velocity(const KCfg& c, const Bufs& b, int inst, int step, const int idx[3],
+__device__ __forceinline__ void node_velocity(const KCfg& c, const NodeConsts<T>& nc, const int idx[3],
                                               const T (&acc)[4], T (&v)[3]) {
   const T m = acc[3];
   v[0] = v[1] = v[2] = T(0);
   if (m > T(0)) {
-    const T dt = T(b.inst[inst].dt);
 #pragma unroll
     for (int a = 0; a < D; ++a) v[a] = acc[a] / m;
-    v[1] += dt * T(c.gravity);
+    v[1] += nc.dt * T(c.gravity);
     if (D == 3 && c.shovel) {
-      const Blade<T> bl = load_blade<T>(b.poses, inst, c.max_steps, step);
+      const Blade<T>& bl = nc.bl;
       const T xi[3] = {T(idx[0]) * T(c.dx), T(idx[1]) * T(c.dx), T(idx[2]) * T(c.dx)};
       const T half[3] = {T(c.half[0]), T(c.half[1]), T(c.half[2])};
       SDF<T> f;
@@ -809,38 +841,35 @@ __global__ void __launch_bounds__(kBlock) k_grid_update(KCfg c, Bufs b, int step
                                                         ActiveSet act, T* __restrict__ pre, int64_t pre_cap,
                                                         T* __restrict__ post, uint32_t* __restrict__ list_out,
                                                         uint32_t* __restrict__ count_out) {
-  constexpr int NPB = D == 3 ? kTile * kTile * kTile : kTile * kTile;
+  ActiveWalk<D> aw(c, act.list);
   const uint32_t nact = *act.count;
   if (count_out && blockIdx.x == 0 && threadIdx.x == 0) *count_out = nact;
-  const int64_t items = (int64_t)nact * NPB;
-  if (pre_cap >= 0 && items > pre_cap && blockIdx.x == 0 && threadIdx.x == 0) flag_error(b.err, 16u, 0);
-  for (int64_t it = (int64_t)blockIdx.x * kBlock + threadIdx.x; it < items; it += (int64_t)gridDim.x * kBlock) {
-    const uint32_t gb = act.list[it / NPB];
-    const int k = (int)(it % NPB);
-    if (list_out && k == 0) list_out[it / NPB] = gb;
+  if (pre_cap >= 0 && (int64_t)nact * ActiveWalk<D>::NPB > pre_cap && blockIdx.x == 0 && threadIdx.x == 0)
+    flag_error(b.err, 16u, 0);
+  for (; aw.w < nact; aw.next()) {
+    const uint32_t gb = aw.block();
+    const int64_t it = aw.item();
+    const int k = (int)threadIdx.x % ActiveWalk<D>::NPB;
+    if (list_out && k == 0) list_out[aw.w] = gb;
     int inst, idx[3];
     int64_t node;
     active_node<D>(c, gb, k, inst, idx, node);
-    const int64_t gid = b.inst[inst].goff + node;
+    const int64_t gid = (int64_t)inst * c.nodes + node;
+    const NodeConsts<T> nc = node_consts<T, D>(c, b, inst, step);
+    T* go = gout + gid * kNodeVals;
+    const Node4<T> o = ld_node(go);
     T acc[4] = {T(0), T(0), T(0), T(0)};
     gather_windows<T, D>(c, inst, idx, stg, tslot, acc);
-    {
-      // particles that left their windows: read and clear
-      T* go = gout + gid * kNodeVals;
-      const Node4<T> o = ld_node(go);
-      if (o.v[3] != T(0) || o.v[0] != T(0) || o.v[1] != T(0) || o.v[2] != T(0)) {
+    // particles that left their windows: add and clear
+    if (o.v[3] != T(0) || o.v[0] != T(0) || o.v[1] != T(0) || o.v[2] != T(0)) {
 #pragma unroll
-        for (int a = 0; a < kNodeVals; ++a) { acc[a] += o.v[a]; go[a] = T(0); }
-      }
+      for (int a = 0; a < kNodeVals; ++a) { acc[a] += o.v[a]; go[a] = T(0); }
     }
     T v[3];
-    node_velocity<T, D>(c, b, inst, step, idx, acc, v);
+    node_velocity<T, D>(c, nc, idx, acc, v);
     if (pre_cap < 0) st_node(pre + gid * kNodeVals, acc[0], acc[1], acc[2], acc[3]);
     else if (it < pre_cap) st_node(pre + it * kNodeVals, acc[0], acc[1], acc[2], acc[3]);
-    post[gid * kNodeVals + 0] = v[0];
-    post[gid * kNodeVals + 1] = v[1];
-    post[gid * kNodeVals + 2] = v[2];
-    post[gid * kNodeVals + 3] = acc[3];
+    st_node(post + gid * kNodeVals, v[0], v[1], v[2], acc[3]);
   }
 }
 
@@ -851,27 +880,36 @@ __global__ void __launch_bounds__(kBlock) k_grid_update(KCfg c, Bufs b, int step
 // keeps only the pre-update grids and rebuilds these.  pre_dense (may be
 // NULL) also receives the pre-update values at their grid positions.
 // Entries beyond the record's capacity (flagged when recorded) read as empty.
+template <typename T> struct PostArgs {
+  int step;
+  const uint32_t *list, *count;
+  const T* pre;
+  int64_t pre_cap;
+  T *post, *pre_dense;
+};
 template <typename T, int D>
-__global__ void __launch_bounds__(kBlock) k_grid_post_from_pre(KCfg c, Bufs b, int step,
-                                                               const uint32_t* __restrict__ list,
-                                                               const uint32_t* __restrict__ count,
-                                                               const T* __restrict__ pre, int64_t pre_cap,
-                                                               T* __restrict__ post, T* __restrict__ pre_dense) {
-  constexpr int NPB = D == 3 ? kTile * kTile * kTile : kTile * kTile;
-  const int64_t items = (int64_t)(*count) * NPB;
-  for (int64_t it = (int64_t)blockIdx.x * kBlock + threadIdx.x; it < items; it += (int64_t)gridDim.x * kBlock) {
+__device__ __forceinline__ void grid_post_from_pre(const KCfg& c, const Bufs& b, const PostArgs<T>& q) {
+  ActiveWalk<D> aw(c, q.list);
+  const uint32_t nact = *q.count;
+  for (; aw.w < nact; aw.next()) {
+    const int64_t it = aw.item();
     int inst, idx[3];
     int64_t node;
-    active_node<D>(c, list[it / NPB], (int)(it % NPB), inst, idx, node);
-    const int64_t gid = b.inst[inst].goff + node;
-    Node4<T> q = {{T(0), T(0), T(0), T(0)}};
-    if (it < pre_cap) q = ld_node(pre + it * kNodeVals);
-    const T acc[4] = {q.v[0], q.v[1], q.v[2], q.v[3]};
+    active_node<D>(c, aw.block(), (int)threadIdx.x % ActiveWalk<D>::NPB, inst, idx, node);
+    const int64_t gid = (int64_t)inst * c.nodes + node;
+    Node4<T> r = {{T(0), T(0), T(0), T(0)}};
+    if (it < q.pre_cap) r = ld_node(q.pre + it * kNodeVals);
+    const NodeConsts<T> nc = node_consts<T, D>(c, b, inst, q.step);
+    const T acc[4] = {r.v[0], r.v[1], r.v[2], r.v[3]};
     T v[3];
-    node_velocity<T, D>(c, b, inst, step, idx, acc, v);
-    st_node(post + gid * kNodeVals, v[0], v[1], v[2], acc[3]);
-    if (pre_dense) st_node(pre_dense + gid * kNodeVals, acc[0], acc[1], acc[2], acc[3]);
+    node_velocity<T, D>(c, nc, idx, acc, v);
+    st_node(q.post + gid * kNodeVals, v[0], v[1], v[2], acc[3]);
+    if (q.pre_dense) st_node(q.pre_dense + gid * kNodeVals, acc[0], acc[1], acc[2], acc[3]);
   }
+}
+template <typename T, int D>
+__global__ void __launch_bounds__(kBlock) k_grid_post_from_pre(KCfg c, Bufs b, PostArgs<T> q) {
+  grid_post_from_pre<T, D>(c, b, q);
 }
 
 static unsigned active_grid(const KCfg& c) {
@@ -886,9 +924,9 @@ void launch_grid_post_from_pre(int prec, const KCfg& c, const Bufs& b, int step,
                                const uint32_t* count, const void* pre, int64_t pre_cap, void* post, void* pre_dense,
                                hipStream_t s) {
   const unsigned nb = active_grid(c);
-#define DDM_GP(T, DD)                                                                                       \
-  hipLaunchKernelGGL((k_grid_post_from_pre<T, DD>), dim3(nb), dim3(kBlock), 0, s, c, b, step, list, count, \
-                     (const T*)pre, pre_cap, (T*)post, (T*)pre_dense)
+#define DDM_GP(T, DD)                                                                    \
+  hipLaunchKernelGGL((k_grid_post_from_pre<T, DD>), dim3(nb), dim3(kBlock), 0, s, c, b, \
+                     (PostArgs<T>{step, list, count, (const T*)pre, pre_cap, (T*)post, (T*)pre_dense}))
   if (prec == 0) {
     if (c.dim == 3) DDM_GP(float, 3); else DDM_GP(float, 2);
   } else {
@@ -1824,19 +1862,29 @@ void launch_pcontact_adj(int prec, const KCfg& c, const Bufs& b, int nblk, int s
 // m bar = -u bar . (mv/m) / m.  Pose adjoints (tip, psi, v_lin, omega) of the
 // sub-step are reduced over the contact nodes.
 // ---------------------------------------------------------------------------
-template <typename T, int D>
+// NEXT: the workgroups of blockIdx.y == 1 rebuild the post-update grid of the
+// sub-step that is reversed next (q) meanwhile.  The two have nothing in
+// common but a launch and its latency (the G2P adjoint is done with the grid
+// that q overwrites): 6.2 and 4.8 us as two launches at 27 440 particles.
+template <typename T, int D, bool NEXT>
 __global__ void __launch_bounds__(kBlock) k_grid_adj(KCfg c, Bufs b, int step, const uint32_t* __restrict__ list,
                                                      const uint32_t* __restrict__ count, const T* __restrict__ pre,
                                                      int64_t pre_cap, T* __restrict__ gvb, T* __restrict__ gb,
-                                                     double* pose_bar) {
-  constexpr int NPB = D == 3 ? kTile * kTile * kTile : kTile * kTile;
-  const int64_t items = (int64_t)(*count) * NPB;
+                                                     double* pose_bar, PostArgs<T> q) {
+  if (NEXT && blockIdx.y == 1) {
+    grid_post_from_pre<T, D>(c, b, q);
+    return;
+  }
+  ActiveWalk<D> aw(c, list);
+  const uint32_t nact = *count;
   // 3D: the 64 lanes of a wave take the 64 nodes of one block, hence one instance
-  for (int64_t it = (int64_t)blockIdx.x * kBlock + threadIdx.x; it < items; it += (int64_t)gridDim.x * kBlock) {
+  for (; aw.w < nact; aw.next()) {
+    const int64_t it = aw.item();
     int inst, idx[3];
     int64_t node;
-    active_node<D>(c, list[it / NPB], (int)(it % NPB), inst, idx, node);
-    const int64_t gid = b.inst[inst].goff + node;
+    active_node<D>(c, aw.block(), (int)threadIdx.x % ActiveWalk<D>::NPB, inst, idx, node);
+    const int64_t gid = (int64_t)inst * c.nodes + node;
+    const NodeConsts<T> nc = node_consts<T, D>(c, b, inst, step);
     double pb[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     bool any = false;
     Node4<T> pr = {{T(0), T(0), T(0), T(0)}};
@@ -1861,14 +1909,13 @@ __global__ void __launch_bounds__(kBlock) k_grid_adj(KCfg c, Bufs b, int step, c
       for (int a = 0; a < D; ++a) wall |= (idx[a] < c.bound) || (idx[a] >= c.n - c.bound);
       if (!wall) {
         T u[3] = {T(0), T(0), T(0)};
-        const T dt = T(b.inst[inst].dt);
 #pragma unroll
         for (int a = 0; a < D; ++a) u[a] = pr.v[a] / m;
-        u[1] += dt * T(c.gravity);
+        u[1] += nc.dt * T(c.gravity);
 #pragma unroll
         for (int a = 0; a < 3; ++a) ub[a] = vb[a];
         if (D == 3 && c.shovel) {
-          const Blade<T> bl = load_blade<T>(b.poses, inst, c.max_steps, step);
+          const Blade<T>& bl = nc.bl;
           const T xi[3] = {T(idx[0]) * T(c.dx), T(idx[1]) * T(c.dx), T(idx[2]) * T(c.dx)};
           const T half[3] = {T(c.half[0]), T(c.half[1]), T(c.half[2])};
           SDF<T> f;
@@ -1899,14 +1946,11 @@ __global__ void __launch_bounds__(kBlock) k_grid_adj(KCfg c, Bufs b, int step, c
         for (int a = 0; a < D; ++a) ub[a] = ub[a] * im;
       }
     }
-    gb[gid * kNodeVals + 0] = ub[0];
-    gb[gid * kNodeVals + 1] = ub[1];
-    gb[gid * kNodeVals + 2] = ub[2];
-    gb[gid * kNodeVals + 3] = mb;
+    st_node(gb + gid * kNodeVals, ub[0], ub[1], ub[2], mb);
     if (D == 3 && c.shovel && __any(any)) {
       // the 64 lanes hold the nodes of one block: its sums go to the block's
       // partials in the deterministic mode
-      double* dst = b.dpart ? b.dpart + (int64_t)list[it / NPB] * kDetVals
+      double* dst = b.dpart ? b.dpart + (int64_t)aw.block() * kDetVals
                             : pose_bar + ((int64_t)inst * c.max_steps + step) * 8;
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
@@ -1921,17 +1965,22 @@ __global__ void __launch_bounds__(kBlock) k_grid_adj(KCfg c, Bufs b, int step, c
 }
 
 void launch_grid_adj(int prec, const KCfg& c, const Bufs& b, int step, const uint32_t* list, const uint32_t* count,
-                     const void* pre, int64_t pre_cap, void* gvb, void* gb, double* pose_bar, hipStream_t s) {
+                     const void* pre, int64_t pre_cap, void* gvb, void* gb, double* pose_bar, const NextPost* next,
+                     hipStream_t s) {
   const unsigned nb = active_grid(c);
-#define DDM_GA(T, DD)                                                                                             \
-  hipLaunchKernelGGL((k_grid_adj<T, DD>), dim3(nb), dim3(kBlock), 0, s, c, b, step, list, count, (const T*)pre,  \
-                     pre_cap, (T*)gvb, (T*)gb, pose_bar)
+  const NextPost q = next ? *next : NextPost{0, nullptr, nullptr, nullptr, nullptr};
+#define DDM_GA_(T, DD, NEXT)                                                                                      \
+  hipLaunchKernelGGL((k_grid_adj<T, DD, NEXT>), dim3(nb, NEXT ? 2 : 1), dim3(kBlock), 0, s, c, b, step, list, count, \
+                     (const T*)pre, pre_cap, (T*)gvb, (T*)gb, pose_bar,                                           \
+                     (PostArgs<T>{q.step, q.list, q.count, (const T*)q.pre, pre_cap, (T*)q.post, nullptr}))
+#define DDM_GA(T, DD) if (next) DDM_GA_(T, DD, true); else DDM_GA_(T, DD, false)
   if (prec == 0) {
-    if (c.dim == 3) DDM_GA(float, 3); else DDM_GA(float, 2);
+    if (c.dim == 3) { DDM_GA(float, 3); } else { DDM_GA(float, 2); }
   } else {
-    if (c.dim == 3) DDM_GA(double, 3); else DDM_GA(double, 2);
+    if (c.dim == 3) { DDM_GA(double, 3); } else { DDM_GA(double, 2); }
   }
 #undef DDM_GA
+#undef DDM_GA_
   if (b.dpart && c.dim == 3 && c.shovel)
     launch_det_finish(c, b, true, 8, pose_bar + (int64_t)step * 8, (int64_t)c.max_steps * 8, s);
 }

@@ -189,8 +189,17 @@ void launch_pcontact_adj(int prec, const KCfg& c, const Bufs& b, int nblk, int s
 // Over the active blocks (list, count) of the sub-step, with the record of
 // its pre-update grid (pre_cap entries in list order); zeroes gvb where it
 // read it.
+// next (may be NULL): the post-update grid of the sub-step reversed next is
+// rebuilt from its record (as launch_grid_post_from_pre) by the same launch.
+struct NextPost {
+  int step;
+  const uint32_t *list, *count;
+  const void* pre;
+  void* post;
+};
 void launch_grid_adj(int prec, const KCfg& c, const Bufs& b, int step, const uint32_t* list, const uint32_t* count,
-                     const void* grid_pre, int64_t pre_cap, void* gvb, void* gb, double* pose_bar, hipStream_t s);
+                     const void* grid_pre, int64_t pre_cap, void* gvb, void* gb, double* pose_bar, const NextPost* next,
+                     hipStream_t s);
 // stress_form: the density adjoint of the sub-step as -sum_p (S_p : A bar_p) / rho,
 // S_p the stress part of A_p (valid while the grid adjoints are untreated,
 // where m bar = -v bar . (mv/m) / m holds); otherwise from the grid mass adjoint.

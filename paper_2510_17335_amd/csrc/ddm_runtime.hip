@@ -1154,8 +1154,12 @@ ddm_status ddm_backward(ddm_ctx* x, const double* dloss_dev, double* grad_dev) {
       const bool treat = rec || x->treat.mode != ddm::kTreatNone;
       const bool reduce = rec || x->treat.mode == ddm::kTreatScale || x->treat.mode == ddm::kTreatNorm;
       if (reduce) { Timed t(x, 9); ddm::launch_fill_zero(acc, (int64_t)ddm::treat_acc_words(x->n_inst), 8, st); }
-      { Timed t(x, 1); ddm::launch_grid_post_from_pre(x->prec, x->kc, b, (int)k, x->seg_alist(m, j), x->seg_acount(m, j),
-                                                      gpre(j), L.rec_items, x->at(L.grid_post), nullptr, st); }
+      // (the others come with the grid adjoint of the sub-step after them)
+      if (j == len - 1) {
+        Timed t(x, 1);
+        ddm::launch_grid_post_from_pre(x->prec, x->kc, b, (int)k, x->seg_alist(m, j), x->seg_acount(m, j), gpre(j),
+                                       L.rec_items, x->at(L.grid_post), nullptr, st);
+      }
       {
         Timed t(x, 4);
         if (x->kc.pcontact)
@@ -1176,8 +1180,13 @@ ddm_status ddm_backward(ddm_ctx* x, const double* dloss_dev, double* grad_dev) {
         Timed t(x, 9);
         treat_vectors(x, rec, TreatTarget{true, x->at(L.gvb), x->seg_alist(m, j), x->seg_acount(m, j), 3, false});
       }
-      { Timed t(x, 5); ddm::launch_grid_adj(x->prec, x->kc, b, (int)k, x->seg_alist(m, j), x->seg_acount(m, j),
-                                            gpre(j), L.rec_items, x->at(L.gvb), x->at(L.gb), x->at<double>(L.pose_bar), st); }
+      {
+        Timed t(x, 5);
+        ddm::NextPost next{(int)k - 1, nullptr, nullptr, nullptr, x->at(L.grid_post)};
+        if (j > 0) { next.list = x->seg_alist(m, j - 1); next.count = x->seg_acount(m, j - 1); next.pre = gpre(j - 1); }
+        ddm::launch_grid_adj(x->prec, x->kc, b, (int)k, x->seg_alist(m, j), x->seg_acount(m, j), gpre(j), L.rec_items,
+                             x->at(L.gvb), x->at(L.gb), x->at<double>(L.pose_bar), j > 0 ? &next : nullptr, st);
+      }
       if (treat) {
         Timed t(x, 9);
         treat_vectors(x, rec, TreatTarget{true, x->at(L.gb), x->seg_alist(m, j), x->seg_acount(m, j), 4, true});
