@@ -415,7 +415,11 @@ ddm_status ddm_set_grad_treatment(ddm_ctx* ctx, int32_t mode, double clip, doubl
  * microseconds of stream time, so a timed run selects only the groups it
  * needs).  Groups: 0 P2G, 1 grid update, 2 G2P, 3 binning (keys, sort,
  * gather, tile list), 4 G2P adjoint, 5 grid adjoint, 6 P2G adjoint, 7 grid
- * clears, 8 loss, 9 gradient treatments and their statistics.
+ * clears, 8 loss, 9 gradient treatments and their statistics.  A G2P that runs
+ * in the launch of the next sub-step's P2G (where that does not bin first) is
+ * counted in group 2, its time in group 0; the post-update grids rebuilt in
+ * the reverse pass are in group 5 with the grid adjoints (the first of a
+ * segment in group 1).
  * groups: bit g selects group g; 0 turns timing off; DDM_TIMING_ALL selects
  * every group.  Synchronises the stream and resets the sums.
  * ddm_read_timing synchronises and returns the summed milliseconds and the

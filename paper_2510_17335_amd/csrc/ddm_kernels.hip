@@ -153,6 +153,17 @@ __device__ __forceinline__ void st_node(double* p, double a, double b, double c,
   reinterpret_cast<double2*>(p)[1] = make_double2(c, d);
 }
 
+// The thread's index, opaque to the compiler: what is computed from it is
+// computed where it is used instead of being held in registers (or scratch)
+// from before a kernel's loops.
+template <int BLK> __device__ __forceinline__ int fresh_thread() {
+  int t = (int)threadIdx.x;
+#ifdef __HIP_DEVICE_COMPILE__
+  asm volatile("" : "+v"(t));
+#endif
+  return t & (BLK - 1);
+}
+
 // Wave64 + block reduction of one double, added atomically to *dst by one lane.
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
@@ -329,11 +340,11 @@ template <typename T, int D> __device__ __forceinline__ void load_part(const P<T
 
 // Per-particle constitutive update and P2G contributions: writes G' (and the
 // stress), leaves the stencil, A = -dt V_p (4/dx^2) tau + m_p C and m_p v.
-template <typename T, int D>
+// late(v, x) gives the velocity and position, which only the end needs.
+template <typename T, int D, typename Late>
 __device__ __forceinline__ bool p2g_particle(const KCfg& c, const Bufs& b, const InstDev& I, int inst,
-                                             const Part<T, D>& q, const P<T, D>& si, const P<T, D>& so, int64_t p,
-                                             Stencil<T, D>& S,
-                                             T (&A)[3][3], T (&vel)[3], T* tau_out) {
+                                             const Part<T, D>& q, Late&& late, const P<T, D>& so, int64_t p,
+                                             Stencil<T, D>& S, T (&A)[3][3], T (&vel)[3], T* tau_out) {
   const T dt = T(I.dt), mp = T(I.mp);
   const T(&Cm)[3][3] = q.C;
   const T(&Gm)[3][3] = q.G;
@@ -365,9 +376,12 @@ __device__ __forceinline__ bool p2g_particle(const KCfg& c, const Bufs& b, const
   for (int a = 0; a < D; ++a)
 #pragma unroll
     for (int bb = 0; bb < D; ++bb) A[a][bb] = k_str * tau[a][bb] + mp * Cm[a][bb];
+  T v[3];
+  typename Pos<T>::X xr[3];
+  late(v, xr);
 #pragma unroll
-  for (int a = 0; a < D; ++a) vel[a] = mp * si.v(a, p);
-  if (!make_stencil<T, D>(si, p, c, S)) { flag_error(b.err, 2u, inst); return false; }
+  for (int a = 0; a < D; ++a) vel[a] = mp * v[a];
+  if (!make_stencil<T, D>(xr, c, S)) { flag_error(b.err, 2u, inst); return false; }
   return true;
 }
 
@@ -463,7 +477,7 @@ __device__ void run_scatter_round(RunLDS<T, BLK>& L, int rc, double* win, T m) {
   constexpr int WS = Win<D>::stride;
   constexpr int NJ = NN / 3;                                  // rows per item
   constexpr int ITEMS = (D == 3 ? 9 : 3) / NJ;                // items per run
-  const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
+  const int t = fresh_thread<BLK>(), lane = t & 63, wid = t >> 6;
   // slots without a window record (-1) form runs of their own, skipped below;
   // a run also ends every kBlock slots, so that its FP32 sums do not depend on
   // the width of the workgroup
@@ -598,113 +612,6 @@ __device__ __forceinline__ void scatter_stencil(const T (&wt)[3][3], const T (&q
     }
 }
 
-// P2G over occupied tiles: one workgroup per tile (grid-stride over the tile
-// list), contributions accumulated with LDS atomics in a kWin^D window that is
-// then stored whole to the tile's staging record (no global atomics); the
-// grid update sums the windows covering each node.  Particles outside the
-// window (drifted more than one cell since binning) add to the outlier grid
-// with global atomics and put their node blocks in the active set.
-template <typename T, int D, bool DET, int BLK>
-__global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
-k_p2g(KCfg c, Bufs b, TileList tl, const void* st_in, void* st_out, T* __restrict__ stg, T* __restrict__ gout,
-      ActiveSet act, T* __restrict__ tau_out) {
-  __shared__ double win[Win<D>::stride * kNodeVals];
-  __shared__ RunLDS<T, BLK> rl;
-  const uint32_t ntiles = *tl.count;
-  __shared__ uint32_t tile_slot;
-  for (uint32_t t = first_tile(tl, &tile_slot); t < ntiles; t = next_tile(tl, t, &tile_slot)) {
-    const TileRec tr = tile_record(tl, t);
-    int inst, org[3];
-    tile_origin<D>(c, tr.tile, inst, org);
-    const InstDev& I = b.inst[inst];
-    T* g = gout + I.goff * kNodeVals;
-    const T mpt = T(I.mp);
-    const int cnt = (int)(tr.end - tr.start);
-    Part<T, D> part;
-    for (int i = threadIdx.x; i < Win<D>::stride * kNodeVals; i += BLK) win[i] = 0.0;
-    for (int r0 = 0; r0 < cnt; r0 += BLK) {
-      const int rc = min(BLK, cnt - r0);
-      const int64_t p0 = (int64_t)tr.start + r0;
-      int wb = -1;
-      if (threadIdx.x < rc) {
-        const P<T, D> si = pv<T, D>(st_in, c.ntot).at(p0), so = pv<T, D>(st_out, c.ntot).at(p0);
-        load_part<T, D>(si, threadIdx.x, part);
-        Stencil<T, D> S;
-        T A[3][3], vel[3];
-        if (p2g_particle<T, D>(c, b, I, inst, part, si, so, threadIdx.x, S, A, vel, tau_out ? tau_out + p0 : nullptr)) {
-          // node o receives w_o (q + B o) and w_o m_p with q = m_p v - A f dx and
-          // B = A dx (the MLS-MPM momentum m_p v + A (x_i - x_p), x_i - x_p = (o - f) dx)
-          T q[3] = {T(0), T(0), T(0)}, B[3][3] = {{T(0), T(0), T(0)}, {T(0), T(0), T(0)}, {T(0), T(0), T(0)}};
-          const T tdx = T(c.dx);
-#pragma unroll
-          for (int a = 0; a < D; ++a) {
-            T af = T(0);
-#pragma unroll
-            for (int bb = 0; bb < D; ++bb) { B[a][bb] = A[a][bb] * tdx; af += B[a][bb] * S.f[bb]; }
-            q[a] = vel[a] - af;
-          }
-          int loc[3] = {0, 0, 0};
-          bool inwin = true;
-#pragma unroll
-          for (int a = 0; a < D; ++a) { loc[a] = S.base[a] - org[a]; inwin &= loc[a] >= 0 && loc[a] <= kWin - 3; }
-          if (inwin) {
-            wb = Win<D>::idx(loc[0], loc[1], loc[2]);
-            put_record<T, D, BLK>(rl, threadIdx.x, q, B, S.w);
-          } else {
-            mark_stencil_blocks<D>(c, inst, S.base, act);
-            scatter_stencil<T, D>(S.w, q, B, mpt, [&](int o0, int o1, int o2, const T (&v)[4]) {
-              T* dst = g + node_of<D>(S.base, o0, o1, o2, c.n) * kNodeVals;
-#pragma unroll
-              for (int a = 0; a < D; ++a) atomicAdd(dst + a, v[a]);
-              atomicAdd(dst + 3, v[3]);
-            });
-          }
-        }
-      }
-      rl.wbase[threadIdx.x] = wb;
-      // the next round's states are on their way while this round is scattered
-      // (the barriers wait for LDS only)
-      __syncthreads();
-      run_scatter_round<T, D, D + 1, 9, DET ? (D == 3 ? 27 : 9) : 1, BLK>(rl, rc, win, mpt);
-    }
-    __syncthreads();
-    // the whole window, zeros included, to the tile's staging record
-    T* rec = stg + (int64_t)t * (kNodeVals * Win<D>::nodes);
-    for (int i = threadIdx.x; i < Win<D>::nodes; i += BLK) {
-      int l[3];
-      Win<D>::coords(i, l);
-      const int wi = Win<D>::idx(l[0], l[1], l[2]);
-      st_node(rec + (int64_t)i * kNodeVals, (T)win[wi], (T)win[Win<D>::stride + wi], (T)win[2 * Win<D>::stride + wi],
-              (T)win[3 * Win<D>::stride + wi]);
-    }
-    __syncthreads();
-  }
-  finish_tiles(tl);
-}
-
-void launch_det_finish(const KCfg& c, const Bufs& b, bool grid_blocks, int nvals, double* dst, int64_t stride,
-                       hipStream_t s) {
-  hipLaunchKernelGGL(k_det_finish, dim3(c.n_inst), dim3(kBlock), 0, s, c, b, grid_blocks ? 1 : 0, nvals, dst, stride);
-}
-
-void launch_p2g(int prec, const KCfg& c, const Bufs& b, const TileList& tl, int nwg, const void* st_in, void* st_out,
-                const Staging& stg, void* gout, const ActiveSet& act, void* tau_out, hipStream_t s) {
-#define DDM_P2G_(T, DD, DET, BLK)                                                                                     \
-  hipLaunchKernelGGL((k_p2g<T, DD, DET, BLK>), dim3(nwg), dim3(BLK), 0, s, c, b, tl, st_in, st_out, (T*)stg.win,    \
-                     (T*)gout, act, (T*)tau_out)
-#define DDM_P2G(T, DD)                                                                                              \
-  if (c.det) DDM_P2G_(T, DD, true, kBlock);                                                                         \
-  else if (DD == 3 && c.wide) DDM_P2G_(T, DD, false, (DD == 3 ? 2 * kBlock : kBlock));                              \
-  else DDM_P2G_(T, DD, false, kBlock)
-  if (prec == 0) {
-    if (c.dim == 3) { DDM_P2G(float, 3); } else { DDM_P2G(float, 2); }
-  } else {
-    if (c.dim == 3) { DDM_P2G(double, 3); } else { DDM_P2G(double, 2); }
-  }
-#undef DDM_P2G
-#undef DDM_P2G_
-}
-
 // Blade pose of one sub-step (tip, angle, velocities) from the pose table.
 template <typename T>
 __device__ __forceinline__ Blade<T> load_blade(const void* poses, int inst, int max_steps, int step) {
@@ -723,6 +630,283 @@ __device__ __forceinline__ void blade_velocity(const Blade<T>& bl, const T xi[3]
   vs[0] = bl.vel[0] + bl.omega * (xi[1] - bl.tip[1]);
   vs[1] = bl.vel[1] - bl.omega * (xi[0] - bl.tip[0]);
   vs[2] = bl.vel[2];
+}
+
+// ---------------------------------------------------------------------------
+// Particle-level collision (Algorithm 1, after the gather): the grid's collision rule
+// applied to a particle's velocity at its position before advection.  A
+// particle in the wall layers (closer than bound cells to a face; the test is
+// exact on the fixed-point position) stops; otherwise, within the contact skin
+// of the blade, the blade's Coulomb contact acts on it.
+// ---------------------------------------------------------------------------
+template <typename T, int D>
+__device__ __forceinline__ bool in_wall_layers(const KCfg& c, const typename Pos<T>::X (&x)[3], double xr[3]) {
+  bool wall = false;
+  xr[0] = xr[1] = xr[2] = 0.0;
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    xr[a] = Pos<T>::real(x[a]);
+    wall |= xr[a] < c.bound * c.dx || xr[a] >= (c.n - c.bound) * c.dx;
+  }
+  return wall;
+}
+
+template <typename T, int D>
+__device__ __forceinline__ void particle_collision(const KCfg& c, const Bufs& b, int inst, int step,
+                                                   const typename Pos<T>::X (&x)[3], T v[3]) {
+  double xr[3];
+  if (in_wall_layers<T, D>(c, x, xr)) {
+    v[0] = v[1] = v[2] = T(0);
+    return;
+  }
+  if (D == 3 && c.shovel) {
+    const Blade<T> bl = load_blade<T>(b.poses, inst, c.max_steps, step);
+    const T xp[3] = {T(xr[0]), T(xr[1]), T(xr[2])};
+    const T half[3] = {T(c.half[0]), T(c.half[1]), T(c.half[2])};
+    SDF<T> f;
+    sdf_eval<T>(bl, half, xp, f);
+    if (f.phi < T(c.skin)) {
+      T vs[3];
+      blade_velocity<T>(bl, xp, vs);
+      coulomb_forward<T>(vs, f.n, T(c.mu_b), v);
+    }
+  }
+}
+
+// G2P of one particle (Algorithm 1, gather to advection) without writing it:
+// v_p = sum w v_i and C_p = (4/dx^2) sum w v_i r^T from the grid velocities g
+// of its instance, the particle-level collision when PC, and the advanced
+// position.  Returns false when the advance leaves the fixed-point range or
+// the result is not finite (the caller flags it).  Computing everything
+// before the stores keeps the kernel at few registers.
+template <typename T, int D, bool PC>
+__device__ __forceinline__ bool g2p_compute(const KCfg& c, const Bufs& b, int inst, int step,
+                                            const typename Pos<T>::X (&xr)[3], const Stencil<T, D>& S,
+                                            const T* __restrict__ g, T (&vn)[3], T (&Cn)[3][3],
+                                            typename Pos<T>::X (&xn)[3]) {
+  const T dx = T(c.dx), Dk = T(4.0 * c.inv_dx * c.inv_dx);
+  // v_p = sum w_o v_o, C_p = (4/dx^2) sum w_o v_o r_o^T with r_o = (o - f) dx:
+  // sums along the last axis first, then per row
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    vn[a] = T(0);
+#pragma unroll
+    for (int bb = 0; bb < 3; ++bb) Cn[a][bb] = T(0);
+  }
+  T rr[3][3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) rr[a][k] = a < D ? (T(k) - S.f[a]) * dx : T(0);
+  const uint32_t nb = node_bytes<T, D>(c, S.base);
+#pragma unroll
+  for (int o0 = 0; o0 < 3; ++o0)
+#pragma unroll
+    for (int o1 = 0; o1 < (D == 3 ? 3 : 1); ++o1) {
+      const T wxy = S.w[0][o0] * (D == 3 ? S.w[1][o1] : T(1));
+      const Global<T>* row = stencil_row<T, D>(c, g, o0, o1);
+      T u[3] = {T(0), T(0), T(0)}, ul[3] = {T(0), T(0), T(0)};
+#pragma unroll
+      for (int ol = 0; ol < 3; ++ol) {
+        const T wl = S.w[D - 1][ol], wr = wl * rr[D - 1][ol];
+        const Node4<T> nd = ld_node(at_bytes(row, nb) + ol * kNodeVals);
+#pragma unroll
+        for (int a = 0; a < D; ++a) { u[a] += wl * nd.v[a]; ul[a] += wr * nd.v[a]; }
+      }
+      const T r0 = Dk * wxy * rr[0][o0], r1 = D == 3 ? Dk * wxy * rr[1][o1] : T(0), wl2 = Dk * wxy;
+#pragma unroll
+      for (int a = 0; a < D; ++a) {
+        vn[a] += wxy * u[a];
+        Cn[a][0] += r0 * u[a];
+        if (D == 3) Cn[a][1] += r1 * u[a];
+        Cn[a][D - 1] += wl2 * ul[a];
+      }
+    }
+  if (PC) particle_collision<T, D>(c, b, inst, step, xr, vn);
+  const T dt = T(b.inst[inst].dt);
+  T chk = T(0);
+  bool ok = true;
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    bool oka;
+    xn[a] = Pos<T>::advance(xr[a], dt * vn[a], oka);
+    ok &= oka;
+    chk += vn[a];
+#pragma unroll
+    for (int bb = 0; bb < D; ++bb) chk += Cn[a][bb];
+  }
+  return isfinite(chk) && ok;
+}
+
+template <typename T> struct GatherArgs { const void* st_x; const T* post; int step, write_vc; };
+
+// The G2P of the sub-step before, for thread threadIdx.x of a tile round whose
+// first slot is p0: C and G into q, v and x into the thread's record, x (and v,
+// C when write_vc) to si.  False when the particle's stencil left the grid
+// (flagged; its state stays).
+template <typename T, int D, int BLK>
+__device__ __forceinline__ bool gather_part(const KCfg& c, const Bufs& b, int inst, const GatherArgs<T>& ga, int64_t p0,
+                                            const P<T, D>& si, RunLDS<T, BLK>& rl, Part<T, D>& q) {
+  using X = typename Pos<T>::X;
+  const uint32_t p = threadIdx.x;
+  const P<T, D> sx = pv<T, D>(ga.st_x, c.ntot).at(p0);
+  Stencil<T, D> S;
+  X xr[3], xn[3];
+#pragma unroll
+  for (int a = 0; a < D; ++a) xr[a] = sx.xr(a, p);
+  if (!make_stencil<T, D>(xr, c, S)) { flag_error(b.err, 2u, inst); return false; }
+  T vn[3];
+  const T* g = ga.post + (int64_t)inst * c.nodes * kNodeVals;
+  if (!g2p_compute<T, D, false>(c, b, inst, ga.step, xr, S, g, vn, q.C, xn)) flag_error(b.err, 1u, inst);
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    si.xr(a, p) = xn[a];
+    rl.rec[0][p][a] = vn[a];
+    reinterpret_cast<X*>(rl.rec[1][p])[a] = xn[a];
+    if (ga.write_vc) {
+      si.v(a, p) = vn[a];
+#pragma unroll
+      for (int bb = 0; bb < D; ++bb) si.C(a, bb, p) = q.C[a][bb];
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < D; ++a)
+#pragma unroll
+    for (int bb = 0; bb < D; ++bb) q.G[a][bb] = si.G(a, bb, p);
+  return true;
+}
+
+// P2G over occupied tiles: one workgroup per tile (grid-stride over the tile
+// list), contributions accumulated with LDS atomics in a kWin^D window that is
+// then stored whole to the tile's staging record (no global atomics); the
+// grid update sums the windows covering each node.  Particles outside the
+// window (drifted more than one cell since binning) add to the outlier grid
+// with global atomics and put their node blocks in the active set.
+// GATHER: the G2P of the sub-step before it first (q: its post-update grid), in
+// the same thread: x from q.st_x and G from st_in, the new x (and v, C when
+// q.write_vc) to st_in; v and C go on to the constitutive update in registers,
+// v and x wait for the scatter in the thread's own LDS record.  A sub-step that
+// does not bin first needs no state but x and G in memory then: 96 B per
+// particle instead of 204 (168 instead of 228 while recording).  Bound by the
+// latency of its chain at four waves per SIMD (128 registers): 136 us at 1.8 M
+// particles against 99 and 46 us for the two launches, 33 against 25 and 12 at
+// 219 488.
+template <typename T, int D, bool DET, int BLK, bool GATHER>
+__global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
+k_p2g(KCfg c, Bufs b, TileList tl, const void* st_in, void* st_out, T* __restrict__ stg, T* __restrict__ gout,
+      ActiveSet act, T* __restrict__ tau_out, GatherArgs<T> q2) {
+  __shared__ double win[Win<D>::stride * kNodeVals];
+  __shared__ RunLDS<T, BLK> rl;
+  const uint32_t ntiles = *tl.count;
+  __shared__ uint32_t tile_slot;
+  for (uint32_t t = first_tile(tl, &tile_slot); t < ntiles; t = next_tile(tl, t, &tile_slot)) {
+    const TileRec tr = tile_record(tl, t);
+    int inst, org[3];
+    tile_origin<D>(c, tr.tile, inst, org);
+    const InstDev& I = b.inst[inst];
+    T* g = gout + I.goff * kNodeVals;
+    const T mpt = T(I.mp);
+    const int cnt = (int)(tr.end - tr.start);
+    for (int i = fresh_thread<BLK>(); i < Win<D>::stride * kNodeVals; i += BLK) win[i] = 0.0;
+    for (int r0 = 0; r0 < cnt; r0 += BLK) {
+      const int rc = min(BLK, cnt - r0);
+      const int64_t p0 = (int64_t)tr.start + r0;
+      int wb = -1;
+      if (threadIdx.x < rc) {
+        const uint32_t p = threadIdx.x;
+        const P<T, D> si = pv<T, D>(st_in, c.ntot).at(p0), so = pv<T, D>(st_out, c.ntot).at(p0);
+        Part<T, D> part;
+        bool moved = true;
+        if (GATHER) moved = gather_part<T, D, BLK>(c, b, inst, q2, p0, si, rl, part);
+        else load_part<T, D>(si, p, part);
+        auto late = [&](T (&v)[3], typename Pos<T>::X (&x)[3]) {
+#pragma unroll
+          for (int a = 0; a < D; ++a) {
+            v[a] = GATHER ? rl.rec[0][p][a] : si.v(a, p);
+            x[a] = GATHER ? reinterpret_cast<const typename Pos<T>::X*>(rl.rec[1][p])[a] : si.xr(a, p);
+          }
+        };
+        Stencil<T, D> S;
+        T A[3][3], vel[3];
+        if (moved && p2g_particle<T, D>(c, b, I, inst, part, late, so, p, S, A, vel, tau_out ? tau_out + p0 : nullptr)) {
+          // node o receives w_o (q + B o) and w_o m_p with q = m_p v - A f dx and
+          // B = A dx (the MLS-MPM momentum m_p v + A (x_i - x_p), x_i - x_p = (o - f) dx)
+          T q[3] = {T(0), T(0), T(0)}, B[3][3] = {{T(0), T(0), T(0)}, {T(0), T(0), T(0)}, {T(0), T(0), T(0)}};
+          const T tdx = T(c.dx);
+#pragma unroll
+          for (int a = 0; a < D; ++a) {
+            T af = T(0);
+#pragma unroll
+            for (int bb = 0; bb < D; ++bb) { B[a][bb] = A[a][bb] * tdx; af += B[a][bb] * S.f[bb]; }
+            q[a] = vel[a] - af;
+          }
+          int loc[3] = {0, 0, 0};
+          bool inwin = true;
+#pragma unroll
+          for (int a = 0; a < D; ++a) { loc[a] = S.base[a] - org[a]; inwin &= loc[a] >= 0 && loc[a] <= kWin - 3; }
+          if (inwin) {
+            wb = Win<D>::idx(loc[0], loc[1], loc[2]);
+            put_record<T, D, BLK>(rl, fresh_thread<BLK>(), q, B, S.w);
+          } else {
+            mark_stencil_blocks<D>(c, inst, S.base, act);
+            scatter_stencil<T, D>(S.w, q, B, mpt, [&](int o0, int o1, int o2, const T (&v)[4]) {
+              T* dst = g + node_of<D>(S.base, o0, o1, o2, c.n) * kNodeVals;
+#pragma unroll
+              for (int a = 0; a < D; ++a) atomicAdd(dst + a, v[a]);
+              atomicAdd(dst + 3, v[3]);
+            });
+          }
+        }
+      }
+      rl.wbase[fresh_thread<BLK>()] = wb;
+      // the next round's states are on their way while this round is scattered
+      // (the barriers wait for LDS only)
+      __syncthreads();
+      run_scatter_round<T, D, D + 1, 9, DET ? (D == 3 ? 27 : 9) : 1, BLK>(rl, rc, win, mpt);
+    }
+    __syncthreads();
+    // the whole window, zeros included, to the tile's staging record
+    T* rec = stg + (int64_t)t * (kNodeVals * Win<D>::nodes);
+    for (int i = fresh_thread<BLK>(); i < Win<D>::nodes; i += BLK) {
+      int l[3];
+      Win<D>::coords(i, l);
+      const int wi = Win<D>::idx(l[0], l[1], l[2]);
+      st_node(rec + (int64_t)i * kNodeVals, (T)win[wi], (T)win[Win<D>::stride + wi], (T)win[2 * Win<D>::stride + wi],
+              (T)win[3 * Win<D>::stride + wi]);
+    }
+    __syncthreads();
+  }
+  finish_tiles(tl);
+}
+
+void launch_det_finish(const KCfg& c, const Bufs& b, bool grid_blocks, int nvals, double* dst, int64_t stride,
+                       hipStream_t s) {
+  hipLaunchKernelGGL(k_det_finish, dim3(c.n_inst), dim3(kBlock), 0, s, c, b, grid_blocks ? 1 : 0, nvals, dst, stride);
+}
+
+void launch_p2g(int prec, const KCfg& c, const Bufs& b, const TileList& tl, int nwg, const GatherStep* ga,
+                const void* st_in, void* st_out, const Staging& stg, void* gout, const ActiveSet& act, void* tau_out,
+                hipStream_t s) {
+  const GatherStep g = ga ? *ga : GatherStep{nullptr, nullptr, 0, 0};
+#define DDM_P2G_(T, DD, DET, BLK, GA)                                                                               \
+  hipLaunchKernelGGL((k_p2g<T, DD, DET, BLK, GA>), dim3(nwg), dim3(BLK), 0, s, c, b, tl, st_in, st_out, (T*)stg.win, \
+                     (T*)gout, act, (T*)tau_out, (GatherArgs<T>{g.st_x, (const T*)g.post, g.step, g.write_vc}))
+#define DDM_P2G(T, DD)                                                                                              \
+  if (c.det) DDM_P2G_(T, DD, true, kBlock, false);                                                                  \
+  else if (DD == 3 && c.wide) {                                                                                     \
+    if (ga) DDM_P2G_(T, DD, false, (DD == 3 ? 2 * kBlock : kBlock), true);                                          \
+    else DDM_P2G_(T, DD, false, (DD == 3 ? 2 * kBlock : kBlock), false);                                            \
+  } else {                                                                                                          \
+    if (ga) DDM_P2G_(T, DD, false, kBlock, true);                                                                   \
+    else DDM_P2G_(T, DD, false, kBlock, false);                                                                     \
+  }
+  if (prec == 0) {
+    if (c.dim == 3) { DDM_P2G(float, 3); } else { DDM_P2G(float, 2); }
+  } else {
+    if (c.dim == 3) { DDM_P2G(double, 3); } else { DDM_P2G(double, 2); }
+  }
+#undef DDM_P2G
+#undef DDM_P2G_
 }
 
 // ---------------------------------------------------------------------------
@@ -951,111 +1135,6 @@ void launch_grid_update(int prec, const KCfg& c, const Bufs& b, int step, const 
 }
 
 // ---------------------------------------------------------------------------
-// Particle-level collision (Algorithm 1, after the gather): the grid's collision rule
-// applied to a particle's velocity at its position before advection.  A
-// particle in the wall layers (closer than bound cells to a face; the test is
-// exact on the fixed-point position) stops; otherwise, within the contact skin
-// of the blade, the blade's Coulomb contact acts on it.
-// ---------------------------------------------------------------------------
-template <typename T, int D>
-__device__ __forceinline__ bool in_wall_layers(const KCfg& c, const P<T, D>& st, int64_t p, double xr[3]) {
-  bool wall = false;
-  xr[0] = xr[1] = xr[2] = 0.0;
-#pragma unroll
-  for (int a = 0; a < D; ++a) {
-    xr[a] = Pos<T>::real(st.xr(a, p));
-    wall |= xr[a] < c.bound * c.dx || xr[a] >= (c.n - c.bound) * c.dx;
-  }
-  return wall;
-}
-
-template <typename T, int D>
-__device__ __forceinline__ void particle_collision(const KCfg& c, const Bufs& b, int inst, int step,
-                                                   const P<T, D>& st, int64_t p, T v[3]) {
-  double xr[3];
-  if (in_wall_layers<T, D>(c, st, p, xr)) {
-    v[0] = v[1] = v[2] = T(0);
-    return;
-  }
-  if (D == 3 && c.shovel) {
-    const Blade<T> bl = load_blade<T>(b.poses, inst, c.max_steps, step);
-    const T xp[3] = {T(xr[0]), T(xr[1]), T(xr[2])};
-    const T half[3] = {T(c.half[0]), T(c.half[1]), T(c.half[2])};
-    SDF<T> f;
-    sdf_eval<T>(bl, half, xp, f);
-    if (f.phi < T(c.skin)) {
-      T vs[3];
-      blade_velocity<T>(bl, xp, vs);
-      coulomb_forward<T>(vs, f.n, T(c.mu_b), v);
-    }
-  }
-}
-
-// G2P of one particle (Algorithm 1, gather to advection) without writing it:
-// v_p = sum w v_i and C_p = (4/dx^2) sum w v_i r^T from the grid velocities g
-// of its instance, the particle-level collision when PC, and the advanced
-// position.  Returns false when the advance leaves the fixed-point range or
-// the result is not finite (the caller flags it).  Computing everything
-// before the stores keeps the kernel at few registers.
-template <typename T, int D, bool PC>
-__device__ __forceinline__ bool g2p_compute(const KCfg& c, const Bufs& b, int inst, int step, const P<T, D>& si,
-                                            int64_t p, const Stencil<T, D>& S, const T* __restrict__ g, T (&vn)[3],
-                                            T (&Cn)[3][3], typename Pos<T>::X (&xn)[3]) {
-  const T dx = T(c.dx), Dk = T(4.0 * c.inv_dx * c.inv_dx);
-  // v_p = sum w_o v_o, C_p = (4/dx^2) sum w_o v_o r_o^T with r_o = (o - f) dx:
-  // sums along the last axis first, then per row
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    vn[a] = T(0);
-#pragma unroll
-    for (int bb = 0; bb < 3; ++bb) Cn[a][bb] = T(0);
-  }
-  T rr[3][3];
-#pragma unroll
-  for (int a = 0; a < 3; ++a)
-#pragma unroll
-    for (int k = 0; k < 3; ++k) rr[a][k] = a < D ? (T(k) - S.f[a]) * dx : T(0);
-  const uint32_t nb = node_bytes<T, D>(c, S.base);
-#pragma unroll
-  for (int o0 = 0; o0 < 3; ++o0)
-#pragma unroll
-    for (int o1 = 0; o1 < (D == 3 ? 3 : 1); ++o1) {
-      const T wxy = S.w[0][o0] * (D == 3 ? S.w[1][o1] : T(1));
-      const Global<T>* row = stencil_row<T, D>(c, g, o0, o1);
-      T u[3] = {T(0), T(0), T(0)}, ul[3] = {T(0), T(0), T(0)};
-#pragma unroll
-      for (int ol = 0; ol < 3; ++ol) {
-        const T wl = S.w[D - 1][ol], wr = wl * rr[D - 1][ol];
-        const Node4<T> nd = ld_node(at_bytes(row, nb) + ol * kNodeVals);
-#pragma unroll
-        for (int a = 0; a < D; ++a) { u[a] += wl * nd.v[a]; ul[a] += wr * nd.v[a]; }
-      }
-      const T r0 = Dk * wxy * rr[0][o0], r1 = D == 3 ? Dk * wxy * rr[1][o1] : T(0), wl2 = Dk * wxy;
-#pragma unroll
-      for (int a = 0; a < D; ++a) {
-        vn[a] += wxy * u[a];
-        Cn[a][0] += r0 * u[a];
-        if (D == 3) Cn[a][1] += r1 * u[a];
-        Cn[a][D - 1] += wl2 * ul[a];
-      }
-    }
-  if (PC) particle_collision<T, D>(c, b, inst, step, si, p, vn);
-  const T dt = T(b.inst[inst].dt);
-  T chk = T(0);
-  bool ok = true;
-#pragma unroll
-  for (int a = 0; a < D; ++a) {
-    bool oka;
-    xn[a] = Pos<T>::advance(si.xr(a, p), dt * vn[a], oka);
-    ok &= oka;
-    chk += vn[a];
-#pragma unroll
-    for (int bb = 0; bb < D; ++bb) chk += Cn[a][bb];
-  }
-  return isfinite(chk) && ok;
-}
-
-// ---------------------------------------------------------------------------
 // G2P (Algorithm 1, gather to advection): v_p = sum w v_i, C_p = (4/dx^2) sum w v_i r^T,
 // the particle-level collision when enabled, x_p += dt v_p.
 // ---------------------------------------------------------------------------
@@ -1080,10 +1159,12 @@ k_g2p(KCfg c, Bufs b, int step, const void* st_in, void* st_out, const T* __rest
     return;
   }
   Stencil<T, D> S;
-  if (!make_stencil<T, D>(si, p, c, S)) { flag_error(b.err, 2u, inst); return; }
+  typename Pos<T>::X xr[3], xn[3];
+#pragma unroll
+  for (int a = 0; a < D; ++a) xr[a] = si.xr(a, p);
+  if (!make_stencil<T, D>(xr, c, S)) { flag_error(b.err, 2u, inst); return; }
   T vn[3], Cn[3][3];
-  typename Pos<T>::X xn[3];
-  const bool ok = g2p_compute<T, D, PC>(c, b, inst, step, si, p, S, post + I.goff * kNodeVals, vn, Cn, xn);
+  const bool ok = g2p_compute<T, D, PC>(c, b, inst, step, xr, S, post + (int64_t)inst * c.nodes * kNodeVals, vn, Cn, xn);
 #pragma unroll
   for (int a = 0; a < D; ++a) {
     so.xr(a, p) = xn[a];
@@ -1563,9 +1644,9 @@ __global__ void __launch_bounds__(BLK) k_g2p_adj(KCfg c, Bufs b, TileList tl, co
     const T dt = T(I.dt);
     const T* g = post + I.goff * kNodeVals;
     T* gbv = gvb + I.goff * kNodeVals;
-    for (int i = threadIdx.x; i < WS * D; i += BLK) win[i] = 0.0;
+    for (int i = fresh_thread<BLK>(); i < WS * D; i += BLK) win[i] = 0.0;
     // stage the window's grid velocities (nodes outside the grid are never read)
-    for (int i = threadIdx.x; i < Win<D>::nodes; i += BLK) {
+    for (int i = fresh_thread<BLK>(); i < Win<D>::nodes; i += BLK) {
       int l[3];
       Win<D>::coords(i, l);
       const int gi[3] = {org[0] + l[0], org[1] + l[1], D == 3 ? org[2] + l[2] : 0};
@@ -1661,7 +1742,7 @@ __global__ void __launch_bounds__(BLK) k_g2p_adj(KCfg c, Bufs b, TileList tl, co
                return ld_node(gwin[wn0 + (D == 3 ? (o0 * kWin + o1) * kWin + o2 : o0 * kWin + o1)]);
              });
         wb = Win<D>::idx(loc[0], loc[1], loc[2]);
-        put_record<T, D, BLK>(rl, threadIdx.x, q, B, S.w);
+        put_record<T, D, BLK>(rl, fresh_thread<BLK>(), q, B, S.w);
       } else {
         body([&](int, int, int, int64_t nd, T w, const T (&t)[3]) {
 #pragma unroll
@@ -1679,12 +1760,12 @@ __global__ void __launch_bounds__(BLK) k_g2p_adj(KCfg c, Bufs b, TileList tl, co
 #pragma unroll
       for (int a = 0; a < D; ++a) ac.x(a, p) = xb[a];
     } while (false);
-    rl.wbase[threadIdx.x] = wb;
+    rl.wbase[fresh_thread<BLK>()] = wb;
     __syncthreads();
     run_scatter_round<T, D, D, 9, DET ? (D == 3 ? 27 : 9) : 1, BLK>(rl, rc, win, T(0));
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < Win<D>::nodes; i += BLK) {
+    for (int i = fresh_thread<BLK>(); i < Win<D>::nodes; i += BLK) {
       int l[3];
       Win<D>::coords(i, l);
       const int wi = Win<D>::idx(l[0], l[1], l[2]);
@@ -1782,8 +1863,11 @@ __global__ void __launch_bounds__(kBlock) k_pcontact_adj(KCfg c, Bufs b, int ste
     const P<T, D> st = pv<T, D>(stv, c.ntot);
     const Adj<T, D> an = av<T, D>(adj_next, c.ntot);
     const T dt = T(I.dt);
+    typename Pos<T>::X xq[3];
+#pragma unroll
+    for (int a = 0; a < D; ++a) xq[a] = st.xr(a, p);
     double xr[3];
-    if (in_wall_layers<T, D>(c, st, p, xr)) {
+    if (in_wall_layers<T, D>(c, xq, xr)) {
 #pragma unroll
       for (int a = 0; a < D; ++a) an.v(a, p) = -dt * an.x(a, p);
     } else if (D == 3 && c.shovel) {

@@ -120,8 +120,14 @@ void launch_init_state(int prec, const KCfg& c, const Bufs& b, int nblk, const v
 // otherwise) and add their node blocks to the active set.
 // tau_out (may be NULL): the Kirchhoff stress of every particle, symmetric
 // rows (00, 01, 02, 11, 12, 22; 2D: 00, 01, 11) of stride ntot, for the reverse pass.
-void launch_p2g(int prec, const KCfg& c, const Bufs& b, const TileList& tl, int nwg, const void* st_in, void* st_out,
-                const Staging& stg, void* gout, const ActiveSet& act, void* tau_out, hipStream_t s);
+// ga (may be NULL): the G2P of the sub-step before it (number step, post-update
+// grid post) runs first in the same launch: x from st_x, the new x (and v, C
+// when write_vc) to st_in, which holds G.  Not in the deterministic mode and
+// not with the particle-level collision.
+struct GatherStep { const void* st_x; const void* post; int step, write_vc; };
+void launch_p2g(int prec, const KCfg& c, const Bufs& b, const TileList& tl, int nwg, const GatherStep* ga,
+                const void* st_in, void* st_out, const Staging& stg, void* gout, const ActiveSet& act, void* tau_out,
+                hipStream_t s);
 // Grid update over the active blocks: sums the staged windows and the outlier
 // grid (zeroing what it read) into grid_pre (m, mv), writes grid_post (v, m).
 // pre_cap < 0: grid_pre is the dense grid; pre_cap >= 0: grid_pre is a record

@@ -625,21 +625,46 @@ int tile_workgroups(const ddm_ctx* x) {
   return x->cfg.tile_workgroups > 0 ? (int)x->cfg.tile_workgroups : x->L.nwg;
 }
 
+// Whether the G2P of a sub-step may run in the launch of the next sub-step's
+// P2G (when that does not bin first).
+bool can_join(const ddm_ctx* x) { return !x->kc.det && !x->kc.pcontact; }
+
 // One forward sub-step from st_in to st_out (may alias) with the given tile
 // list; grids given.  The reverse pass also keeps the stress (tau_out) and the
-// active blocks of the sub-step (list_out, count_out).
+// active blocks of the sub-step (list_out, count_out).  scattered: the launch
+// of the sub-step before has done this one's P2G already (joined).  join (may
+// be NULL): the sub-step after it, whose P2G takes this one's G2P with it; its
+// state is st_out then and only x and G of it are valid unless keep_vc.
+struct Join {
+  void* st_out;
+  void* tau_out;
+  bool keep_vc;
+};
 ddm_status forward_step(ddm_ctx* x, int64_t step, const ddm::TileList& tl, const void* st_in, void* st_out,
-                        void* gpre, void* gpost, void* tau_out = nullptr, uint32_t* list_out = nullptr,
-                        uint32_t* count_out = nullptr) {
+                        void* gpre, void* gpost, bool scattered, const Join* join, void* tau_out = nullptr,
+                        uint32_t* list_out = nullptr, uint32_t* count_out = nullptr) {
   const ddm::Bufs b = x->bufs();
   const ddm::Staging stg = x->staging();
   const ddm::ActiveSet act = x->active();
   void* gout = x->at(x->L.gout);
-  { Timed t(x, 0); ddm::launch_p2g(x->prec, x->kc, b, tl, tile_workgroups(x), st_in, st_out, stg, gout, act, tau_out, x->stream); }
+  if (!scattered) {
+    Timed t(x, 0);
+    ddm::launch_p2g(x->prec, x->kc, b, tl, tile_workgroups(x), nullptr, st_in, st_out, stg, gout, act, tau_out,
+                    x->stream);
+  }
   // a recorded sub-step (list_out given) writes its pre-update grid as a record in active-list order
   { Timed t(x, 1); ddm::launch_grid_update(x->prec, x->kc, b, (int)step, stg, gout, act, gpre,
                                            list_out ? x->L.rec_items : -1, gpost, list_out, count_out, x->stream); }
-  { Timed t(x, 2); ddm::launch_g2p(x->prec, x->kc, b, (int)x->L.nblk, (int)step, st_in, st_out, gpost, x->stream); }
+  if (join) {
+    { Timed t(x, 2); }                   // counted, its time is P2G's
+    Timed t(x, 0);
+    const ddm::GatherStep ga{st_in, gpost, (int)step, join->keep_vc ? 1 : 0};
+    ddm::launch_p2g(x->prec, x->kc, b, tl, tile_workgroups(x), &ga, st_out, join->st_out, stg, gout, act,
+                    join->tau_out, x->stream);
+  } else {
+    Timed t(x, 2);
+    ddm::launch_g2p(x->prec, x->kc, b, (int)x->L.nblk, (int)step, st_in, st_out, gpost, x->stream);
+  }
   return launch_status();
 }
 
@@ -648,6 +673,17 @@ ddm_status forward_step(ddm_ctx* x, int64_t step, const ddm::TileList& tl, const
 bool sort_due(const ddm_ctx* x, int64_t step) {
   const int R = x->cfg.sort_every;
   return x->need_sort || x->cfg.deterministic || (R > 0 && step % R == 0);
+}
+
+// One sub-step of the current state in place.  last: no sub-step follows it in
+// this run of sub-steps; scattered carries a joined launch from one to the next.
+ddm_status step_in_place(ddm_ctx* x, int64_t step, bool last, bool& scattered) {
+  const bool join = !last && can_join(x) && !sort_due(x, step + 1);
+  const Join next{x->cur(), nullptr, false};
+  const ddm_status s = forward_step(x, step, x->tiles(), x->cur(), x->cur(), x->at(x->L.grid_pre),
+                                    x->at(x->L.grid_post), scattered, join ? &next : nullptr);
+  scattered = join;
+  return s;
 }
 
 // Runs `len` sub-steps from step k_first into the segment buffers as the
@@ -668,6 +704,7 @@ ddm_status run_segment(ddm_ctx* x, int m, int64_t k_first, int len, const void* 
   uint32_t* rp[2] = {x->at<uint32_t>(x->L.rpid0), x->at<uint32_t>(x->L.rpid1)};
   const uint32_t* rpid_cur = replay_pid;
   int rsel = 0;
+  bool scattered = false;
   for (int j = 0; j < len; ++j) {
     if (bins[j]) {
       const uint32_t* pin = move_pid ? x->pid() : rpid_cur;
@@ -682,11 +719,15 @@ ddm_status run_segment(ddm_ctx* x, int m, int64_t k_first, int len, const void* 
       DDM_HIP(hipMemcpyAsync(x->slot(m, 0), src, x->L.state_bytes, hipMemcpyDeviceToDevice, x->stream));
     }
     tl_of[j] = last;
-    const bool next_bins = j + 1 < len && bins[j + 1];
-    const ddm_status s = forward_step(x, k_first + j, x->seg_tiles(m, last), x->slot(m, j),
-                                      next_bins ? spare : x->slot(m, j + 1), x->gpre(m, j), x->at(x->L.grid_post),
-                                      x->tau(m, j), x->seg_alist(m, j), x->seg_acount(m, j));
+    // where sub-step i writes its state: the next slot, or the spare buffer for the next binning
+    auto out = [&](int i) { return i + 1 < len && bins[i + 1] ? spare : x->slot(m, i + 1); };
+    const bool join = j + 1 < len && !bins[j + 1] && can_join(x);
+    const Join next{join ? out(j + 1) : nullptr, join ? x->tau(m, j + 1) : nullptr, true};
+    const ddm_status s = forward_step(x, k_first + j, x->seg_tiles(m, last), x->slot(m, j), out(j), x->gpre(m, j),
+                                      x->at(x->L.grid_post), scattered, join ? &next : nullptr, x->tau(m, j),
+                                      x->seg_alist(m, j), x->seg_acount(m, j));
     if (s != DDM_OK) return s;
+    scattered = join;
   }
   return DDM_OK;
 }
@@ -939,14 +980,14 @@ ddm_status ddm_step(ddm_ctx* x, int32_t n_steps) {
   if (n_steps < 0) return fail(DDM_EINVAL, "n_steps < 0");
   if (x->cfg.shovel && x->steps + n_steps > x->cfg.max_steps)
     return fail(DDM_EINVAL, "steps beyond max_steps (the pose table length)");
+  bool scattered = false;
   for (int i = 0; i < n_steps; ++i) {
     if (sort_due(x, x->steps)) {
       const ddm_status s = bin_current(x);
       if (s != DDM_OK) return s;
       x->need_sort = false;
     }
-    const ddm_status s = forward_step(x, x->steps, x->tiles(), x->cur(), x->cur(), x->at(x->L.grid_pre),
-                                      x->at(x->L.grid_post));
+    const ddm_status s = step_in_place(x, x->steps, i + 1 == n_steps, scattered);
     if (s != DDM_OK) return s;
     ++x->steps;
     x->grid_valid = true;
@@ -974,6 +1015,7 @@ ddm_status ddm_rollout(ddm_ctx* x, int32_t n_steps) {
   const int64_t s_rec = (int64_t)first_rec * K;
   {
   Phase plain("unrecorded sub-steps", s_rec > 0);
+  bool scattered = false;
   for (int i = 0; i < s_rec; ++i) {
     // Checkpoints hold the state before the binning of their step; every
     // checkpointed step re-bins, so a replayed segment needs nothing older.
@@ -991,8 +1033,8 @@ ddm_status ddm_rollout(ddm_ctx* x, int32_t n_steps) {
       x->need_sort = false;
       x->rec_sorted[(size_t)i] = 1;
     }
-    const ddm_status s = forward_step(x, k0 + i, x->tiles(), x->cur(), x->cur(), x->at(x->L.grid_pre),
-                                      x->at(x->L.grid_post));
+    // (the next sub-step's checkpoint and binning need the whole state)
+    const ddm_status s = step_in_place(x, k0 + i, i + 1 == s_rec || (i + 1) % K == 0, scattered);
     if (s != DDM_OK) return s;
     ++x->steps;
     x->grid_valid = true;
@@ -1359,13 +1401,14 @@ ddm_status ddm_autotune(ddm_ctx* x, const char* cache_path, int32_t* sort_every_
       x->need_sort = true;
       DDM_HIP(hipEventRecord(e0, x->stream));
       ddm_status r = DDM_OK;
+      bool scattered = false;
       for (int i = 0; i < P && r == DDM_OK; ++i) {
         // pose rows 0 .. P-1: the cost of a sub-step does not depend on the pose
         if (sort_due(x, i)) {
           r = bin_current(x);
           x->need_sort = false;
         }
-        if (r == DDM_OK) r = forward_step(x, i, x->tiles(), x->cur(), x->cur(), x->at(L.grid_pre), x->at(L.grid_post));
+        if (r == DDM_OK) r = step_in_place(x, i, i + 1 == P, scattered);
       }
       DDM_HIP(hipEventRecord(e1, x->stream));
       DDM_HIP(hipEventSynchronize(e1));
