@@ -1619,13 +1619,37 @@ void launch_loss_seed(int prec, const KCfg& c, const Bufs& b, int nblk, const vo
   if (b.dpart) launch_det_finish(c, b, false, 1, pacc + 4, 8, s);
 }
 
+// What the G2P adjoint needs of one particle, in registers.
+template <typename T, int D> struct AdjPart {
+  typename Pos<T>::X xr[3];
+  T x[3], v[3], C[3][3];
+};
+template <typename T, int D>
+__device__ __forceinline__ void load_adj_part(const P<T, D>& st, const Adj<T, D>& an, int64_t p, AdjPart<T, D>& q) {
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    q.xr[a] = st.xr(a, p);
+    q.x[a] = an.x(a, p);
+    q.v[a] = an.v(a, p);
+#pragma unroll
+    for (int bb = 0; bb < D; ++bb) q.C[a][bb] = an.C(a, bb, p);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Adjoint of G2P + advection.  With vb = v'bar + dt x'bar:
 //   xbar = x'bar + sum_i [grad w (v_i . vb + (4/dx^2) v_i^T C'bar r) - (4/dx^2) w C'bar^T v_i]
 //   v_i bar += w (vb + (4/dx^2) C'bar r)            (scattered to the grid)
+// Bound by the latency of its chain: list record, then window and particles,
+// then 27 nodes from LDS, at four waves per SIMD (128 registers).  So the
+// window's 512 nodes and the first round's particles are loaded together, before
+// the accumulation window is cleared, and the nodes are read a plane of nine at
+// a time.  One after the other and in a rolled loop this was 26.8 us at 219 488
+// particles and 98.4 us at 1.8 M; it is 23.2 and 84.9 (1.9 and 6.5 us of
+// it from the loads, the rest from the planes; all 27 nodes at once cost a wave per SIMD).
 // ---------------------------------------------------------------------------
 template <typename T, int D, bool DET, int BLK>
-__global__ void __launch_bounds__(BLK) k_g2p_adj(KCfg c, Bufs b, TileList tl, const void* stv,
+__global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) k_g2p_adj(KCfg c, Bufs b, TileList tl, const void* stv,
                                                  const T* __restrict__ post, const void* adj_next, void* adj_cur,
                                                  T* __restrict__ gvb, T* __restrict__ stg) {
   __shared__ double win[Win<D>::stride * D];
@@ -1644,39 +1668,53 @@ __global__ void __launch_bounds__(BLK) k_g2p_adj(KCfg c, Bufs b, TileList tl, co
     const T dt = T(I.dt);
     const T* g = post + I.goff * kNodeVals;
     T* gbv = gvb + I.goff * kNodeVals;
-    for (int i = fresh_thread<BLK>(); i < WS * D; i += BLK) win[i] = 0.0;
-    // stage the window's grid velocities (nodes outside the grid are never read)
-    for (int i = fresh_thread<BLK>(); i < Win<D>::nodes; i += BLK) {
+    // the window's grid velocities and the first round's particles are on their
+    // way together (nodes outside the grid are never read)
+    constexpr int NST = (Win<D>::nodes + BLK - 1) / BLK;
+    Node4<T> nv[NST];
+    const int t0 = fresh_thread<BLK>();
+#pragma unroll
+    for (int k = 0; k < NST; ++k) {
       int l[3];
-      Win<D>::coords(i, l);
+      Win<D>::coords(t0 + k * BLK, l);
       const int gi[3] = {org[0] + l[0], org[1] + l[1], D == 3 ? org[2] + l[2] : 0};
-      bool ok = true;
+      bool ok = t0 + k * BLK < Win<D>::nodes;
 #pragma unroll
       for (int a = 0; a < D; ++a) ok &= gi[a] >= 0 && gi[a] < c.n;
-      Node4<T> v = {{T(0), T(0), T(0), T(0)}};
-      if (ok) v = ld_node(at_bytes(g, node_bytes<T, D>(c, gi)));
-      st_node(gwin[i], v.v[0], v.v[1], v.v[2], v.v[3]);
+      nv[k] = Node4<T>{{T(0), T(0), T(0), T(0)}};
+      if (ok) nv[k] = ld_node(at_bytes(g, node_bytes<T, D>(c, gi)));
     }
-    __syncthreads();
     const int cnt = (int)(tr.end - tr.start);
+    AdjPart<T, D> part;
+    auto load_round = [&](int r0) {
+      if ((int)threadIdx.x < cnt - r0) {
+        const int64_t q0 = (int64_t)tr.start + r0;
+        load_adj_part<T, D>(pv<T, D>(stv, c.ntot).at(q0), av<T, D>(adj_next, c.ntot).at(q0), threadIdx.x, part);
+      }
+    };
+    load_round(0);
+    for (int i = t0; i < WS * D; i += BLK) win[i] = 0.0;
+#pragma unroll
+    for (int k = 0; k < NST; ++k)
+      if (t0 + k * BLK < Win<D>::nodes) st_node(gwin[t0 + k * BLK], nv[k].v[0], nv[k].v[1], nv[k].v[2], nv[k].v[3]);
+    __syncthreads();
     for (int r0 = 0; r0 < cnt; r0 += BLK) {
     const int rc = min(BLK, cnt - r0);
     int wb = -1;
+    if (r0 > 0) load_round(r0);
     do {
       if (threadIdx.x >= rc) break;
       const int64_t p0 = (int64_t)tr.start + r0;
       const uint32_t p = threadIdx.x;
-      const P<T, D> st = pv<T, D>(stv, c.ntot).at(p0);
-      const Adj<T, D> an = av<T, D>(adj_next, c.ntot).at(p0), ac = av<T, D>(adj_cur, c.ntot).at(p0);
+      const Adj<T, D> ac = av<T, D>(adj_cur, c.ntot).at(p0);
       Stencil<T, D> S;
-      if (!make_stencil<T, D>(st, p, c, S)) break;
-      T xb[3], vb[3], Cb[3][3];
+      if (!make_stencil<T, D>(part.xr, c, S)) break;
+      T xb[3], vb[3];
+      const T(&Cb)[3][3] = part.C;
 #pragma unroll
       for (int a = 0; a < D; ++a) {
-        xb[a] = an.x(a, p);
-        vb[a] = an.v(a, p) + dt * xb[a];
-#pragma unroll
-        for (int bb = 0; bb < D; ++bb) Cb[a][bb] = an.C(a, bb, p);
+        xb[a] = part.x[a];
+        vb[a] = part.v[a] + dt * xb[a];
       }
       int loc[3] = {0, 0, 0};
       bool inwin = true;
@@ -1697,12 +1735,13 @@ __global__ void __launch_bounds__(BLK) k_g2p_adj(KCfg c, Bufs b, TileList tl, co
         for (int k = 0; k < 3; ++k) dwi[a][k] = S.dw[a][k] * inv_dx;
       }
       T xg[3] = {T(0), T(0), T(0)}, vw[3] = {T(0), T(0), T(0)};
-      auto body = [&](auto&& emit, auto&& load) {
-        // Offsets 0 and 1 stay loops: unrolling all 27 nodes hoists their
-        // loads and costs occupancy.
-#pragma unroll 1
-        for (int o0 = 0; o0 < 3; ++o0)
-#pragma unroll 1
+      auto body = [&](auto unr, auto&& emit, auto&& load) {
+        constexpr int kRows = decltype(unr)::value;   // rows whose loads may be in flight together
+        // unrolled a plane of nine nodes at a time (all 27 loads in flight would
+        // cost a wave per SIMD); the path through global memory stays rolled
+#pragma unroll kRows
+        for (int o0 = 0; o0 < 3; ++o0) {
+#pragma unroll kRows
           for (int o1 = 0; o1 < 3; ++o1) {
             const T w0 = sel3(S.w[0], o0), w1 = sel3(S.w[1], o1);
             const T wxy = w0 * w1;
@@ -1733,18 +1772,20 @@ __global__ void __launch_bounds__(BLK) k_g2p_adj(KCfg c, Bufs b, TileList tl, co
 #pragma unroll
             for (int a = 0; a < D; ++a) vw[a] += wxy * u[a];
           }
+          __builtin_amdgcn_sched_barrier(0);
+        }
       };
       if (inwin) {
         // the scatter of w_o t_o happens in the run phase
         const int wn0 = D == 3 ? (loc[0] * kWin + loc[1]) * kWin + loc[2] : loc[0] * kWin + loc[1];
-        body([&](int, int, int, int64_t, T, const T (&)[3]) {},
+        body(std::integral_constant<int, 3>(), [&](int, int, int, int64_t, T, const T (&)[3]) {},
              [&](int o0, int o1, int o2, int64_t) {
                return ld_node(gwin[wn0 + (D == 3 ? (o0 * kWin + o1) * kWin + o2 : o0 * kWin + o1)]);
              });
         wb = Win<D>::idx(loc[0], loc[1], loc[2]);
         put_record<T, D, BLK>(rl, fresh_thread<BLK>(), q, B, S.w);
       } else {
-        body([&](int, int, int, int64_t nd, T w, const T (&t)[3]) {
+        body(std::integral_constant<int, 1>(), [&](int, int, int, int64_t nd, T w, const T (&t)[3]) {
 #pragma unroll
                for (int a = 0; a < D; ++a) atomicAdd(gbv + nd + a, w * t[a]);
              },
