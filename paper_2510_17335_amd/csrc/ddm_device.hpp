@@ -13,18 +13,15 @@ template <typename T> struct Lim;
 template <> struct Lim<float> {
   static constexpr int sweeps = 6;
   static __device__ __forceinline__ float tol() { return 1e-6f; }
+  static __device__ __forceinline__ float tiny() { return 1e-36f; }
 };
 template <> struct Lim<double> {
   static constexpr int sweeps = 12;
   static __device__ __forceinline__ double tol() { return 1e-16; }
+  static __device__ __forceinline__ double tiny() { return 1e-290; }
 };
 
 template <typename T> __device__ __forceinline__ T dsqrt(T x) { return sqrt(x); }
-// Square root of an argument that is never subnormal (at least 1e-12): the
-// hardware v_sqrt_f32 (about 1 ulp, no rescaling or rounding fix-up) in
-// float, the library routine in double.
-template <typename T> __device__ __forceinline__ T fsqrt(T x) { return sqrt(x); }
-template <> __device__ __forceinline__ float fsqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
 // a[i] for a run-time i in {0, 1, 2} by selects, so that a loop counter used
 // as the index does not move a register array to scratch memory.
 template <typename T> __device__ __forceinline__ T sel3(const T (&a)[3], int i) {
@@ -33,13 +30,31 @@ template <typename T> __device__ __forceinline__ T sel3(const T (&a)[3], int i) 
 template <typename T> __device__ __forceinline__ T dabs(T x) { return x < T(0) ? -x : x; }
 
 // Reciprocal and reciprocal square root: the hardware approximations
-// (v_rcp_f32, v_rsq_f32, about 1 ulp) in float, exact division in double.
+// (v_rcp_f32, v_rsq_f32, about 1 ulp) in float.  In double the hardware's
+// (about 2^-23) with one step of third order, r (1 + e + e^2) and
+// y (1 + e/2 + 3 e^2/8) of the residuals e = 1 - x r, 1 - x y^2, whose e^3 is
+// below the rounding: within 2 ulp, 5 and 7 instructions, where the correctly
+// rounded division takes 11 and the root 16.  v_div_fixup puts in the results
+// for zero, infinity and NaN; frsq's result for zero is not used.
 template <typename T> __device__ __forceinline__ T frcp(T x);
 template <> __device__ __forceinline__ float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
-template <> __device__ __forceinline__ double frcp(double x) { return 1.0 / x; }
+template <> __device__ __forceinline__ double frcp(double x) {
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = __builtin_fma(-x, r, 1.0);
+  return __builtin_amdgcn_div_fixup(__builtin_fma(r, __builtin_fma(e, e, e), r), x, 1.0);
+}
 template <typename T> __device__ __forceinline__ T frsq(T x);
 template <> __device__ __forceinline__ float frsq(float x) { return __builtin_amdgcn_rsqf(x); }
-template <> __device__ __forceinline__ double frsq(double x) { return 1.0 / sqrt(x); }
+template <> __device__ __forceinline__ double frsq(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = __builtin_fma(-x * y, y, 1.0);
+  return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
+}
+// Square root of an argument that is never subnormal (at least 1e-12): the
+// hardware v_sqrt_f32 (about 1 ulp, no rescaling or rounding fix-up) in
+// float, the library routine in double.
+template <typename T> __device__ __forceinline__ T fsqrt(T x) { return sqrt(x); }
+template <> __device__ __forceinline__ float fsqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
 
 // log(1 + x) and exp(x) - 1 for small x.  In float: the hardware base-2
 // logarithm and exponential (v_log_f32, v_exp_f32) with the classical
@@ -83,6 +98,13 @@ template <typename T> __device__ __forceinline__ T sigma_min() { return T(1e-6);
 // (stopped when the off-diagonal part is below tol relative to the diagonal),
 // eigenvalues left on the diagonal of a and sorted in decreasing order, each
 // column swap of V paired with a sign flip so that det V stays +1.
+// The rotation of (p, q), d = a_qq - a_pp.  In double: cos^2 = (1 + |d| / h) / 2
+// and sin cos = sgn(d) a_pq / h with h = hypot(d, 2 a_pq), two reciprocal square
+// roots.  In float, where a root or a reciprocal is one instruction: tan =
+// sgn(theta) / (|theta| + sqrt(theta^2 + 1)), theta = d / (2 a_pq).  (The other
+// form was no faster there, and gradients moved by 1e-6 when the adjoint took a
+// rotation that rounds otherwise than the forward pass's: the return map's case
+// then differs for particles on the yield surface.)
 // ---------------------------------------------------------------------------
 template <typename T, int D>
 __device__ __forceinline__ void jacobi_sym(T a[3][3], T V[3][3], T ev[3]) {
@@ -106,11 +128,24 @@ __device__ __forceinline__ void jacobi_sym(T a[3][3], T V[3][3], T ev[3]) {
       const T apq = a[p][q];
       // a zero a_pq gives t = 0, the identity rotation (selected rather than
       // branched over: no merge of register copies in the unrolled sweeps)
-      const T theta = (a[q][q] - a[p][p]) * frcp(T(2) * apq);
-      const T tr = (theta >= T(0) ? T(1) : T(-1)) * frcp(dabs(theta) + fsqrt(theta * theta + T(1)));
-      const T t = apq == T(0) ? T(0) : tr;
-      const T c = frsq(t * t + T(1));
-      const T sn = t * c;
+      T t, c, sn;
+      if (sizeof(T) == 4) {
+        const T theta = (a[q][q] - a[p][p]) * frcp(T(2) * apq);
+        const T tr = (theta >= T(0) ? T(1) : T(-1)) * frcp(dabs(theta) + fsqrt(theta * theta + T(1)));
+        t = apq == T(0) ? T(0) : tr;
+        c = frsq(t * t + T(1));
+        sn = t * c;
+      } else {
+        const T d = a[q][q] - a[p][p];
+        const T h2 = d * d + T(4) * apq * apq;
+        const T rh = frsq(h2);                                       // 1 / hypot(d, 2 a_pq)
+        const T c2 = T(0.5) + T(0.5) * dabs(d) * rh;                 // cos^2
+        const T rc = frsq(c2);
+        const bool turn = h2 > Lim<T>::tiny();
+        sn = turn ? (d < T(0) ? -apq : apq) * rh * rc : T(0);
+        c = turn ? c2 * rc : T(1);
+        t = turn ? sn * rc : T(0);
+      }
       a[p][p] -= t * apq;
       a[q][q] += t * apq;
       a[p][q] = a[q][p] = T(0);
@@ -280,16 +315,15 @@ __device__ __forceinline__ void divided(const DP<T>& o, T mu, T ds, T sj, T gj, 
 }
 
 // ---------------------------------------------------------------------------
-// Constitutive update of one particle, on the displacement gradient G = F - I
-// (kept instead of F so that small strains keep their relative precision).
-// F = U diag(s) V^T = R S (polar): V and s^2 - 1 from the eigen-decomposition
-// of F^T F - I = G + G^T + G^T G, eps = ln s = log1p(s^2 - 1)/2,
-// R - I = (G - (S - I)) S^-1, U = R V.  Outputs, without cancellation:
-//   G' = F' - I = (S' - I) + (R - I) + (R - I)(S' - I), S' - I = V diag(expm1(eps')) V^T
-//   tau = U diag(h) U^T.
+// Singular value decomposition and return map of one particle, on the
+// displacement gradient G = F - I (kept instead of F so that small strains keep
+// their relative precision): F = U diag(s) V^T, V and s^2 - 1 from the
+// eigen-decomposition of F^T F - I = G + G^T + G^T G, eps = ln s =
+// log1p(s^2 - 1)/2, and U = F V diag(1/s) = V + (G V - V diag(s - 1)) diag(1/s),
+// whose second term is of the size of the strain.
 // ---------------------------------------------------------------------------
 template <typename T, int D> struct Constit {
-  T U[3][3], V[3][3], s[3], sm1[3], eps[3], RmI[3][3];
+  T U[3][3], V[3][3], s[3], sm1[3], eps[3];
   bool clamped[3];
   int nclamp;
   DP<T> dp;
@@ -334,87 +368,29 @@ __device__ __forceinline__ void constit_forward(const T G[3][3], T mu, T lam, T 
       c.eps[i] = T(0.5) * flog1p(l);
     }
   }
-  // R - I = (G - (S - I)) S^-1; S - I = V diag(s - 1) V^T and S^-1 are
-  // symmetric, so each entry pair is formed once
-  T GmS[3][3], Sinv[3][3], is[3];
 #pragma unroll
-  for (int k = 0; k < D; ++k) is[k] = frcp(c.s[k]);
+  for (int j = 0; j < D; ++j) {
+    const T is = frcp(c.s[j]);
 #pragma unroll
-  for (int i = 0; i < D; ++i)
+    for (int i = 0; i < D; ++i) {
+      T acc = -c.V[i][j] * c.sm1[j];
 #pragma unroll
-    for (int j = i; j < D; ++j) {
-      T smi = T(0), si = T(0);
-#pragma unroll
-      for (int k = 0; k < D; ++k) {
-        const T vv = c.V[i][k] * c.V[j][k];
-        smi += vv * c.sm1[k];
-        si += vv * is[k];
-      }
-      GmS[i][j] = G[i][j] - smi;
-      GmS[j][i] = G[j][i] - smi;
-      Sinv[i][j] = Sinv[j][i] = si;
+      for (int k = 0; k < D; ++k) acc += G[i][k] * c.V[k][j];
+      c.U[i][j] = c.V[i][j] + acc * is;
     }
-#pragma unroll
-  for (int i = 0; i < D; ++i)
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-      T acc = T(0);
-#pragma unroll
-      for (int k = 0; k < D; ++k) acc += GmS[i][k] * Sinv[k][j];
-      c.RmI[i][j] = acc;
-    }
-#pragma unroll
-  for (int i = 0; i < D; ++i)
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-      T acc = c.V[i][j];
-#pragma unroll
-      for (int k = 0; k < D; ++k) acc += c.RmI[i][k] * c.V[k][j];
-      c.U[i][j] = acc;
-    }
+  }
   dp_forward<T, D>(c.eps, mu, lam, alpha, kc, c.dp);
 }
 
-template <typename T, int D>
-__device__ __forceinline__ void constit_outputs(const Constit<T, D>& c, T Gn[3][3], T tau[3][3]) {
-  T em[3], SpmI[3][3];
-#pragma unroll
-  for (int k = 0; k < D; ++k) em[k] = fexpm1(c.dp.ep[k]);
-  // both are symmetric: the upper triangle is computed and mirrored
-#pragma unroll
-  for (int i = 0; i < D; ++i)
-#pragma unroll
-    for (int j = i; j < D; ++j) {
-      T a = T(0), b = T(0);
-#pragma unroll
-      for (int k = 0; k < D; ++k) {
-        a += c.V[i][k] * em[k] * c.V[j][k];
-        b += c.U[i][k] * c.dp.h[k] * c.U[j][k];
-      }
-      SpmI[i][j] = SpmI[j][i] = a;
-      tau[i][j] = tau[j][i] = b;
-    }
-#pragma unroll
-  for (int i = 0; i < D; ++i)
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-      T acc = SpmI[i][j] + c.RmI[i][j];
-#pragma unroll
-      for (int k = 0; k < D; ++k) acc += c.RmI[i][k] * SpmI[k][j];
-      Gn[i][j] = acc;
-    }
-}
-
-// The forward constitutive update alone (P2G), without the polar factors.
+// The forward constitutive update (P2G), without U.
 // Since eps' and eps share the eigenvectors V of F^T F,
 //   F' = U diag(s') V^T = F V diag(exp(eps' - eps)) V^T,
 // so G' = G + M + G M with M = V diag(expm1(d)) V^T, d = eps' - eps taken per
 // case without cancellation (0 inside the cone, apex - eps in tension,
 // -(dgam/|dev|) dev on projection): an elastic step leaves G' = G exactly.
 // With U = F' V diag(1/s'), tau = U diag(h) U^T = F' N F'^T, N = V diag(h / s'^2) V^T,
-// s'^2 = (1 + lambda'_i)(1 + expm1(d_i))^2.  The result equals
-// constit_forward + constit_outputs up to rounding (clamped singular values
-// aside, which are flagged).  Returns the number of clamps.
+// s'^2 = (1 + lambda'_i)(1 + expm1(d_i))^2 (clamped singular values aside,
+// which are flagged).  Returns the number of clamps.
 template <typename T, int D>
 __device__ __forceinline__ int constit_step(const T G[3][3], T mu, T lam, T alpha, T kc, T Gn[3][3], T tau[3][3]) {
   T a[3][3], V[3][3], ev[3];
