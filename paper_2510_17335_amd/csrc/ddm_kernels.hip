@@ -2124,8 +2124,12 @@ void launch_grid_adj(int prec, const KCfg& c, const Bufs& b, int step, const uin
 // One kernel since both halves fit four waves per SIMD: as two, A bar went
 // through memory (72 of 372 B per particle) and C was read twice: 193 us per
 // sub-step at 1.8 M particles (FP32) against 133 us, 42 against 28 at 219 488,
-// 18.5 against 14.8 at 27 440; HBM alone needs 79 us at 1.8 M (264 B a
-// particle at 6 TB/s), the rest is the two halves' arithmetic.
+// 18.5 against 14.8 at 27 440.  The gather's sums by node, row and plane (rather
+// than by node and row) and the accumulator slots then gave 121, 24.5 and
+// 14.1 us.  HBM alone needs 79 us at 1.8 M (264 B a particle at 6 TB/s), the
+// vector units about as much.  Tried without gain: the second half's loads ahead
+// of the gather (136 and 29.6 us), all 27 nodes in flight at two waves per SIMD
+// (171 us, and 18.7 at 27 440), the planes in a rolled loop (equal).
 // ---------------------------------------------------------------------------
 template <typename T, int D>
 __device__ __forceinline__ void ftmp_of(const P<T, D>& st, int64_t p, T dt, T Cm[3][3], T Gm[3][3], T Ft[3][3]) {
@@ -2145,7 +2149,7 @@ __device__ __forceinline__ void ftmp_of(const P<T, D>& st, int64_t p, T dt, T Cm
 }
 
 template <typename T, int D, bool SF>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1)))
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
 k_p2g_adj(KCfg c, Bufs b, const void* stv, const T* __restrict__ tau, const T* __restrict__ gbar, const void* adj_next,
           void* adj_cur, double* pacc) {
   const int inst = b.blk_inst[blockIdx.x];
@@ -2180,7 +2184,7 @@ k_p2g_adj(KCfg c, Bufs b, const void* stv, const T* __restrict__ tau, const T* _
       //   v bar          m_p G
       //   A bar          sum w_o g_v r_o^T
       //   x bar         += sum grad w_o (m_p g_m + g_v . t_o) - A^T G
-      // The sums run along the last axis first and are factored by axis.
+      // The sums run along the last axis, then over a plane, then over the planes.
       // Density: every particle of an instance has the mass m_p = rho V_p,
       // so node o's mass m_o and the part mv_o - f_o of its momentum that is
       // not stress (f_o = sum_p w_op S_p r_op, S_p = k tau_p) are linear in
@@ -2208,20 +2212,30 @@ k_p2g_adj(KCfg c, Bufs b, const void* stv, const T* __restrict__ tau, const T* _
 #pragma unroll
       for (int a = 0; a < D; ++a) { mvv[a] = mp * vel[a]; Bl[a] = A[a][D - 1] * dx; }
       T G[3] = {T(0), T(0), T(0)}, Gm = T(0), xg[3] = {T(0), T(0), T(0)};
+      // t_o of the first node; it advances by a column of A dx per node
+      T t0[3] = {T(0), T(0), T(0)}, Bx[3] = {T(0), T(0), T(0)}, By[3] = {T(0), T(0), T(0)};
 #pragma unroll
-      for (int o0 = 0; o0 < 3; ++o0)
+      for (int a = 0; a < D; ++a) {
+        t0[a] = mvv[a] + A[a][0] * rr[0][0] + (D == 3 ? A[a][1] * rr[1][0] : T(0)) + A[a][D - 1] * rr[D - 1][0];
+        Bx[a] = A[a][0] * dx;
+        if (D == 3) By[a] = A[a][1] * dx;
+      }
+      T wr[3], wr1[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) { wr[k] = S.w[D - 1][k] * rr[D - 1][k]; wr1[k] = D == 3 ? S.w[1][k] * rr[1][k] : T(0); }
+#pragma unroll
+      for (int o0 = 0; o0 < 3; ++o0) {
+        // sums over the plane o0 (2D: the row) with its weights along the other axes
+        T U[3] = {T(0), T(0), T(0)}, U1[3] = {T(0), T(0), T(0)}, UL[3] = {T(0), T(0), T(0)};
+        T Um = T(0), Sw = T(0), S1 = T(0), Sd = T(0), tr[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) tr[a] = t0[a];
 #pragma unroll
         for (int o1 = 0; o1 < (D == 3 ? 3 : 1); ++o1) {
-          // 3D: row (o0, o1) along axis 2; 2D: row o0 along axis 1
-          const T wa = S.w[0][o0], wb = D == 3 ? S.w[1][o1] : T(1);
-          const T wxy = wa * wb;
-          const T a0 = dwi[0][o0] * wb, a1 = D == 3 ? wa * dwi[1][o1] : T(0);
           const Global<T>* row = stencil_row<T, D>(c, g, o0, o1);
-          T t[3] = {T(0), T(0), T(0)};
+          T u[3] = {T(0), T(0), T(0)}, ul[3] = {T(0), T(0), T(0)}, um = T(0), sw = T(0), sd = T(0), t[3];
 #pragma unroll
-          for (int a = 0; a < D; ++a)
-            t[a] = mvv[a] + A[a][0] * rr[0][o0] + (D == 3 ? A[a][1] * rr[1][o1] : T(0)) + A[a][D - 1] * rr[D - 1][0];
-          T u[3] = {T(0), T(0), T(0)}, ul[3] = {T(0), T(0), T(0)}, um = T(0), sw = T(0), sd = T(0);
+          for (int a = 0; a < 3; ++a) t[a] = tr[a];
 #pragma unroll
           for (int ol = 0; ol < 3; ++ol) {
             const T wl = S.w[D - 1][ol];
@@ -2232,31 +2246,42 @@ k_p2g_adj(KCfg c, Bufs b, const void* stv, const T* __restrict__ tau, const T* _
             sw += wl * sc;
             sd += dwi[D - 1][ol] * sc;
             um += wl * gn.v[3];
-            const T wr = wl * rr[D - 1][ol];
 #pragma unroll
-            for (int a = 0; a < D; ++a) { u[a] += wl * gn.v[a]; ul[a] += wr * gn.v[a]; t[a] += Bl[a]; }
+            for (int a = 0; a < D; ++a) {
+              u[a] += wl * gn.v[a];
+              ul[a] += wr[ol] * gn.v[a];
+              if (ol < 2) t[a] += Bl[a];
+            }
           }
-          Gm += wxy * um;
-          if (D == 3) {
-            xg[0] += a0 * sw;
-            xg[1] += a1 * sw;
-            xg[2] += wxy * sd;
-          } else {
-            xg[0] += a0 * sw;
-            xg[1] += wa * sd;
-          }
-          const T r0 = wxy * rr[0][o0], r1 = D == 3 ? wxy * rr[1][o1] : T(0);
+          const T wb = D == 3 ? S.w[1][o1] : T(1);
+          Um += wb * um;
+          Sw += wb * sw;
+          Sd += wb * sd;
+          if (D == 3) S1 += dwi[1][o1] * sw;
 #pragma unroll
           for (int a = 0; a < D; ++a) {
-            G[a] += wxy * u[a];
-            Ab[a][0] += r0 * u[a];
-            if (D == 3) Ab[a][1] += r1 * u[a];
-            Ab[a][D - 1] += wxy * ul[a];
+            U[a] += wb * u[a];
+            UL[a] += wb * ul[a];
+            if (D == 3) { U1[a] += wr1[o1] * u[a]; tr[a] += By[a]; }
           }
-          // at most a plane's nine loads in flight: all 27 at once need more
-          // registers than four waves per SIMD leave
-          if (sizeof(T) == 4 && D == 3 && o1 == 2) __builtin_amdgcn_sched_barrier(0);
         }
+        const T wa = S.w[0][o0], wr0 = wa * rr[0][o0];
+        Gm += wa * Um;
+        xg[0] += dwi[0][o0] * Sw;
+        if (D == 3) xg[1] += wa * S1;
+        xg[D - 1] += wa * Sd;
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+          G[a] += wa * U[a];
+          Ab[a][0] += wr0 * U[a];
+          if (D == 3) Ab[a][1] += wa * U1[a];
+          Ab[a][D - 1] += wa * UL[a];
+          t0[a] += Bx[a];
+        }
+        // at most a plane's nine loads in flight: all 27 at once need more
+        // registers than four waves per SIMD leave
+        if (sizeof(T) == 4 && D == 3) __builtin_amdgcn_sched_barrier(0);
+      }
       T vb[3] = {T(0), T(0), T(0)};
       T mpb = Gm;
 #pragma unroll
