@@ -9,6 +9,7 @@ namespace ddm {
 constexpr int kBlock = 256;          // particle kernels: threads per block, and the
                                      // padding unit of every instance's particle range
 constexpr int kDetVals = 8;          // partial sums per block in the deterministic mode
+constexpr int kAccSlots = 64;        // material-adjoint accumulators per instance (a power of two)
 constexpr int kNodeVals = 4;         // node record: mv[0..2] (or v), m
 constexpr int kPoseVals = 10;        // device pose row of a sub-step
 constexpr int kSkillParams = 5;      // skill parameters of the pose Jacobian (depth, angle, push, displace, push angle)

@@ -157,7 +157,7 @@ Layout make_layout(const ddm_config& c, int n_inst, const ddm_instance* in) {
   L.adj1 = cv.take(L.state_bytes);
   L.gvb = cv.take(L.grid_bytes);
   L.gb = cv.take(L.grid_bytes);
-  L.pacc = cv.take(sizeof(double) * 8 * n_inst);
+  L.pacc = cv.take(sizeof(double) * 8 * ddm::kAccSlots * n_inst);
   L.treat_acc = cv.take(sizeof(unsigned long long) * ddm::treat_acc_words(n_inst));
   L.pose_bar = cv.take(sizeof(double) * 8 * (size_t)n_inst * c.max_steps);
   L.hm_bits = cv.take(sizeof(unsigned long long) * (size_t)n_inst * npix);
@@ -1147,7 +1147,7 @@ ddm_status ddm_backward(ddm_ctx* x, const double* dloss_dev, double* grad_dev) {
   const ddm::Bufs b = x->bufs();
   const int esz = x->prec ? 8 : 4;
   hipStream_t st = x->stream;
-  ddm::launch_fill_zero(x->at(L.pacc), (int64_t)8 * x->n_inst, 8, st);
+  ddm::launch_fill_zero(x->at(L.pacc), (int64_t)8 * ddm::kAccSlots * x->n_inst, 8, st);
   ddm::launch_fill_zero(x->at(L.pose_bar), (int64_t)8 * x->n_inst * x->cfg.max_steps, 8, st);
   // the v-bar grid starts at zero; each grid adjoint step clears what it read
   { Timed t(x, 7); ddm::launch_fill_zero(x->at(L.gvb), (int64_t)L.grid_bytes / esz, esz, st); }
