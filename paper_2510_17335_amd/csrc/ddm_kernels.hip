@@ -1646,6 +1646,111 @@ __device__ __forceinline__ void load_adj_part(const P<T, D>& st, const Adj<T, D>
   }
 }
 
+// The G2P adjoint of particle p: x bar to ac, its record for the scatter to
+// rl; returns the node of the window that its stencil starts at, -1 when the
+// particle lies outside the window (and scattered to the grid itself).
+template <typename T, int D, int BLK>
+__device__ __forceinline__ int g2p_adj_particle(const KCfg& c, const int (&org)[3], T dt, const T* g, T* gbv,
+                                                const T (*gwin)[kNodeVals], RunLDS<T, BLK>& rl, const AdjPart<T, D>& part,
+                                                const Adj<T, D>& ac, uint32_t p) {
+  const T dx = T(c.dx), inv_dx = T(c.inv_dx), Dk = T(4.0 * c.inv_dx * c.inv_dx);
+  int wb = -1;
+  Stencil<T, D> S;
+  if (!make_stencil<T, D>(part.xr, c, S)) return -1;
+  T xb[3], vb[3];
+  const T(&Cb)[3][3] = part.C;
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    xb[a] = part.x[a];
+    vb[a] = part.v[a] + dt * xb[a];
+  }
+  int loc[3] = {0, 0, 0};
+  bool inwin = true;
+#pragma unroll
+  for (int a = 0; a < D; ++a) { loc[a] = S.base[a] - org[a]; inwin &= loc[a] >= 0 && loc[a] <= kWin - 3; }
+  // With t_o = vb + Dk C'bar r_o = q + B o (q = vb - B f, B = Dk dx C'bar):
+  //   node o receives w_o t_o;
+  //   xbar += sum_o grad w_o (v_o . t_o) - Dk C'bar^T sum_o w_o v_o,
+  // the first sum factored by axis (weights are products of per-axis terms).
+  T q[3] = {T(0), T(0), T(0)}, B[3][3], dwi[3][3];
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    T bf = T(0);
+#pragma unroll
+    for (int bb = 0; bb < D; ++bb) { B[a][bb] = Dk * dx * Cb[a][bb]; bf += B[a][bb] * S.f[bb]; }
+    q[a] = vb[a] - bf;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) dwi[a][k] = S.dw[a][k] * inv_dx;
+  }
+  T xg[3] = {T(0), T(0), T(0)}, vw[3] = {T(0), T(0), T(0)};
+  auto body = [&](auto unr, auto&& emit, auto&& load) {
+    constexpr int kRows = decltype(unr)::value;   // rows whose loads may be in flight together
+    // unrolled a plane of nine nodes at a time (all 27 loads in flight would
+    // cost a wave per SIMD); the path through global memory stays rolled
+#pragma unroll kRows
+    for (int o0 = 0; o0 < 3; ++o0) {
+#pragma unroll kRows
+      for (int o1 = 0; o1 < 3; ++o1) {
+        const T w0 = sel3(S.w[0], o0), w1 = sel3(S.w[1], o1);
+        const T wxy = w0 * w1;
+        const T a0 = sel3(dwi[0], o0) * w1, a1 = w0 * sel3(dwi[1], o1);
+        T t[3] = {T(0), T(0), T(0)}, u[3] = {T(0), T(0), T(0)}, sw = T(0), sd = T(0);
+#pragma unroll
+        for (int a = 0; a < D; ++a) t[a] = q[a] + T(o0) * B[a][0] + T(o1) * B[a][1];
+#pragma unroll
+        for (int o2 = 0; o2 < (D == 3 ? 3 : 1); ++o2) {
+          const T w2 = D == 3 ? S.w[2][o2] : T(1);
+          const T w = wxy * w2;
+          const int64_t nd = node_of<D>(S.base, o0, o1, o2, c.n) * kNodeVals;
+          const Node4<T> gv = load(o0, o1, o2, nd);
+          T sdot = T(0);
+#pragma unroll
+          for (int a = 0; a < D; ++a) { sdot += gv.v[a] * t[a]; u[a] += w2 * gv.v[a]; }
+          sw += w2 * sdot;
+          if (D == 3) sd += dwi[2][o2] * sdot;
+          emit(o0, o1, o2, nd, w, t);
+          if (D == 3) {
+#pragma unroll
+            for (int a = 0; a < D; ++a) t[a] += B[a][2];
+          }
+        }
+        xg[0] += a0 * sw;
+        xg[1] += a1 * sw;
+        if (D == 3) xg[2] += wxy * sd;
+#pragma unroll
+        for (int a = 0; a < D; ++a) vw[a] += wxy * u[a];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  if (inwin) {
+    // the scatter of w_o t_o happens in the run phase
+    const int wn0 = D == 3 ? (loc[0] * kWin + loc[1]) * kWin + loc[2] : loc[0] * kWin + loc[1];
+    body(std::integral_constant<int, 3>(), [&](int, int, int, int64_t, T, const T (&)[3]) {},
+         [&](int o0, int o1, int o2, int64_t) {
+           return ld_node(gwin[wn0 + (D == 3 ? (o0 * kWin + o1) * kWin + o2 : o0 * kWin + o1)]);
+         });
+    wb = Win<D>::idx(loc[0], loc[1], loc[2]);
+    put_record<T, D, BLK>(rl, fresh_thread<BLK>(), q, B, S.w);
+  } else {
+    body(std::integral_constant<int, 1>(), [&](int, int, int, int64_t nd, T w, const T (&t)[3]) {
+#pragma unroll
+           for (int a = 0; a < D; ++a) atomicAdd(gbv + nd + a, w * t[a]);
+         },
+         [&](int, int, int, int64_t nd) { return ld_node(g + nd); });
+  }
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    T ctv = T(0);
+#pragma unroll
+    for (int bb = 0; bb < D; ++bb) ctv += Cb[bb][a] * vw[bb];
+    xb[a] += xg[a] - Dk * ctv;
+  }
+#pragma unroll
+  for (int a = 0; a < D; ++a) ac.x(a, p) = xb[a];
+  return wb;
+}
+
 // ---------------------------------------------------------------------------
 // Adjoint of G2P + advection.  With vb = v'bar + dt x'bar:
 //   xbar = x'bar + sum_i [grad w (v_i . vb + (4/dx^2) v_i^T C'bar r) - (4/dx^2) w C'bar^T v_i]
@@ -1666,7 +1771,6 @@ __global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(sizeof
   __shared__ RunLDS<T, BLK> rl;
   __shared__ alignas(16) T gwin[Win<D>::nodes][kNodeVals];     // grid velocities of the tile's window
   const uint32_t ntiles = *tl.count;
-  const T dx = T(c.dx), inv_dx = T(c.inv_dx), Dk = T(4.0 * c.inv_dx * c.inv_dx);
   constexpr int WS = Win<D>::stride;
   // a plain grid-stride loop: the work queue's loop form costs this kernel ten
   // registers and a wave per SIMD
@@ -1712,105 +1816,10 @@ __global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(sizeof
     const int rc = min(BLK, cnt - r0);
     int wb = -1;
     if (r0 > 0) load_round(r0);
-    do {
-      if (threadIdx.x >= rc) break;
+    if (threadIdx.x < rc) {
       const int64_t p0 = (int64_t)tr.start + r0;
-      const uint32_t p = threadIdx.x;
-      const Adj<T, D> ac = av<T, D>(adj_cur, c.ntot).at(p0);
-      Stencil<T, D> S;
-      if (!make_stencil<T, D>(part.xr, c, S)) break;
-      T xb[3], vb[3];
-      const T(&Cb)[3][3] = part.C;
-#pragma unroll
-      for (int a = 0; a < D; ++a) {
-        xb[a] = part.x[a];
-        vb[a] = part.v[a] + dt * xb[a];
-      }
-      int loc[3] = {0, 0, 0};
-      bool inwin = true;
-#pragma unroll
-      for (int a = 0; a < D; ++a) { loc[a] = S.base[a] - org[a]; inwin &= loc[a] >= 0 && loc[a] <= kWin - 3; }
-      // With t_o = vb + Dk C'bar r_o = q + B o (q = vb - B f, B = Dk dx C'bar):
-      //   node o receives w_o t_o;
-      //   xbar += sum_o grad w_o (v_o . t_o) - Dk C'bar^T sum_o w_o v_o,
-      // the first sum factored by axis (weights are products of per-axis terms).
-      T q[3] = {T(0), T(0), T(0)}, B[3][3], dwi[3][3];
-#pragma unroll
-      for (int a = 0; a < D; ++a) {
-        T bf = T(0);
-#pragma unroll
-        for (int bb = 0; bb < D; ++bb) { B[a][bb] = Dk * dx * Cb[a][bb]; bf += B[a][bb] * S.f[bb]; }
-        q[a] = vb[a] - bf;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) dwi[a][k] = S.dw[a][k] * inv_dx;
-      }
-      T xg[3] = {T(0), T(0), T(0)}, vw[3] = {T(0), T(0), T(0)};
-      auto body = [&](auto unr, auto&& emit, auto&& load) {
-        constexpr int kRows = decltype(unr)::value;   // rows whose loads may be in flight together
-        // unrolled a plane of nine nodes at a time (all 27 loads in flight would
-        // cost a wave per SIMD); the path through global memory stays rolled
-#pragma unroll kRows
-        for (int o0 = 0; o0 < 3; ++o0) {
-#pragma unroll kRows
-          for (int o1 = 0; o1 < 3; ++o1) {
-            const T w0 = sel3(S.w[0], o0), w1 = sel3(S.w[1], o1);
-            const T wxy = w0 * w1;
-            const T a0 = sel3(dwi[0], o0) * w1, a1 = w0 * sel3(dwi[1], o1);
-            T t[3] = {T(0), T(0), T(0)}, u[3] = {T(0), T(0), T(0)}, sw = T(0), sd = T(0);
-#pragma unroll
-            for (int a = 0; a < D; ++a) t[a] = q[a] + T(o0) * B[a][0] + T(o1) * B[a][1];
-#pragma unroll
-            for (int o2 = 0; o2 < (D == 3 ? 3 : 1); ++o2) {
-              const T w2 = D == 3 ? S.w[2][o2] : T(1);
-              const T w = wxy * w2;
-              const int64_t nd = node_of<D>(S.base, o0, o1, o2, c.n) * kNodeVals;
-              const Node4<T> gv = load(o0, o1, o2, nd);
-              T sdot = T(0);
-#pragma unroll
-              for (int a = 0; a < D; ++a) { sdot += gv.v[a] * t[a]; u[a] += w2 * gv.v[a]; }
-              sw += w2 * sdot;
-              if (D == 3) sd += dwi[2][o2] * sdot;
-              emit(o0, o1, o2, nd, w, t);
-              if (D == 3) {
-#pragma unroll
-                for (int a = 0; a < D; ++a) t[a] += B[a][2];
-              }
-            }
-            xg[0] += a0 * sw;
-            xg[1] += a1 * sw;
-            if (D == 3) xg[2] += wxy * sd;
-#pragma unroll
-            for (int a = 0; a < D; ++a) vw[a] += wxy * u[a];
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      };
-      if (inwin) {
-        // the scatter of w_o t_o happens in the run phase
-        const int wn0 = D == 3 ? (loc[0] * kWin + loc[1]) * kWin + loc[2] : loc[0] * kWin + loc[1];
-        body(std::integral_constant<int, 3>(), [&](int, int, int, int64_t, T, const T (&)[3]) {},
-             [&](int o0, int o1, int o2, int64_t) {
-               return ld_node(gwin[wn0 + (D == 3 ? (o0 * kWin + o1) * kWin + o2 : o0 * kWin + o1)]);
-             });
-        wb = Win<D>::idx(loc[0], loc[1], loc[2]);
-        put_record<T, D, BLK>(rl, fresh_thread<BLK>(), q, B, S.w);
-      } else {
-        body(std::integral_constant<int, 1>(), [&](int, int, int, int64_t nd, T w, const T (&t)[3]) {
-#pragma unroll
-               for (int a = 0; a < D; ++a) atomicAdd(gbv + nd + a, w * t[a]);
-             },
-             [&](int, int, int, int64_t nd) { return ld_node(g + nd); });
-      }
-#pragma unroll
-      for (int a = 0; a < D; ++a) {
-        T ctv = T(0);
-#pragma unroll
-        for (int bb = 0; bb < D; ++bb) ctv += Cb[bb][a] * vw[bb];
-        xb[a] += xg[a] - Dk * ctv;
-      }
-#pragma unroll
-      for (int a = 0; a < D; ++a) ac.x(a, p) = xb[a];
-    } while (false);
+      wb = g2p_adj_particle<T, D, BLK>(c, org, dt, g, gbv, gwin, rl, part, av<T, D>(adj_cur, c.ntot).at(p0), threadIdx.x);
+    }
     rl.wbase[fresh_thread<BLK>()] = wb;
     __syncthreads();
     run_scatter_round<T, D, D, 9, DET ? (D == 3 ? 27 : 9) : 1, BLK>(rl, rc, win, T(0));
