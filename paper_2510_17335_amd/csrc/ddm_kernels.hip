@@ -161,6 +161,7 @@ template <int BLK> __device__ __forceinline__ int fresh_thread() {
 #ifdef __HIP_DEVICE_COMPILE__
   asm volatile("" : "+v"(t));
 #endif
+  static_assert((BLK & (BLK - 1)) == 0, "the mask bounds the index");
   return t & (BLK - 1);
 }
 
@@ -911,9 +912,14 @@ void launch_p2g(int prec, const KCfg& c, const Bufs& b, const TileList& tl, int 
                      (T*)gout, act, (T*)tau_out, (GatherArgs<T>{g.st_x, (const T*)g.post, g.step, g.write_vc}))
 #define DDM_P2G(T, DD)                                                                                              \
   if (c.det) DDM_P2G_(T, DD, true, kBlock, false);                                                                  \
-  else if (DD == 3 && c.wide) {                                                                                     \
-    if (ga) DDM_P2G_(T, DD, false, (DD == 3 ? 2 * kBlock : kBlock), true);                                          \
-    else DDM_P2G_(T, DD, false, (DD == 3 ? 2 * kBlock : kBlock), false);                                            \
+  else if (DD == 3 && sizeof(T) == 4 && c.wide == 2) {                                                              \
+    constexpr int kBLK = DD == 3 && sizeof(T) == 4 ? 4 * kBlock : kBlock;                                           \
+    if (ga) DDM_P2G_(T, DD, false, kBLK, true);                                                                     \
+    else DDM_P2G_(T, DD, false, kBLK, false);                                                                       \
+  } else if (DD == 3 && c.wide) {                                                                                   \
+    constexpr int kBLK = DD == 3 ? 2 * kBlock : kBlock;                                                             \
+    if (ga) DDM_P2G_(T, DD, false, kBLK, true);                                                                     \
+    else DDM_P2G_(T, DD, false, kBLK, false);                                                                       \
   } else {                                                                                                          \
     if (ga) DDM_P2G_(T, DD, false, kBlock, true);                                                                   \
     else DDM_P2G_(T, DD, false, kBlock, false);                                                                     \
@@ -1883,6 +1889,7 @@ void launch_g2p_adj(int prec, const KCfg& c, const Bufs& b, const TileList& tl, 
                      adj_cur, (T*)gvb, (T*)stg)
 #define DDM_G2PADJ(T, DD)                                                                                         \
   if (stg) DDM_G2PADJ_(T, DD, true, kBlock);                                                                      \
+  else if (DD == 3 && sizeof(T) == 4 && c.wide == 2) DDM_G2PADJ_(T, DD, false, (DD == 3 && sizeof(T) == 4 ? 4 * kBlock : kBlock)); \
   else if (DD == 3 && c.wide) DDM_G2PADJ_(T, DD, false, (DD == 3 ? 2 * kBlock : kBlock));                         \
   else DDM_G2PADJ_(T, DD, false, kBlock)
   if (prec == 0) {

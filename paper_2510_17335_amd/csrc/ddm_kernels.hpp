@@ -65,7 +65,7 @@ struct KCfg {
   double w_hm, w_mass, m_target, m_ref;
   double w_emd;
   int det;                           // deterministic mode: fixed-order window and reduction sums
-  int wide;                          // tile kernels with 2 kBlock threads per workgroup (wide_tiles in ddm_runtime.hip)
+  int wide;                          // tile kernels with kBlock << wide threads per workgroup (wide_tiles in ddm_runtime.hip)
 };
 
 // Node of an active-set item: item i is node i % 4^D of listed block i / 4^D.

@@ -736,18 +736,30 @@ ddm_status run_segment(ddm_ctx* x, int m, int64_t k_first, int len, const void* 
 // cohesion shift from the friction angle, particle mass and volume, and their
 // derivatives for the final chain rule), the block-to-instance map, and the
 // pose table with its Jacobian; uploaded with synchronous copies.
-// Threads per workgroup of P2G and the G2P adjoint, which take a tile each.  A
-// tile of more than kBlock particles takes kBlock threads several rounds, one
-// after the other; 2 kBlock threads do 512 particles in one.  That is faster
-// while all tiles are resident at once (256 compute units hold two such
-// workgroups each in FP32, one in FP64: registers and LDS): P2G 26.2 -> 20.2 us
-// at 27 440 particles, 25.6 -> 20.4 at 119 168, 28.4 -> 26.1 at 243 200; in FP64
-// 37.0 -> 34.0 at 102 752.  Beyond that the narrow workgroups fill the units
-// better: 29.3 against 29.8 us at 321 632, 99 against 119 at 1.8 M, in FP64 42.9
-// against 51.0 at 196 992.
-bool wide_tiles(const ddm_config& c, int64_t ntot) {
+// Threads per workgroup of P2G and the G2P adjoint, which take a tile each:
+// kBlock << the value returned.  A tile of more particles than threads takes
+// several rounds, one after the other, so wider workgroups are faster while all
+// tiles are resident at once (256 compute units hold two of 2 kBlock threads
+// each in FP32, one in FP64: registers and LDS): P2G 26.2 -> 20.2 us at 27 440
+// particles, 25.6 -> 20.4 at 119 168, 28.4 -> 26.1 at 243 200; in FP64 37.0 ->
+// 34.0 at 102 752.  Beyond that the narrow workgroups fill the units better: 29.3
+// against 29.8 us at 321 632, 99 against 119 at 1.8 M, in FP64 42.9 against 51.0
+// at 196 992.
+// 4 kBlock threads (FP32 only: 128 registers, one workgroup a unit) take the
+// tiles that hold a little more than the 512 particles of a full one in one
+// round as well: joined G2P + P2G 25.0 -> 19.3 us and the G2P adjoint 15.6 -> 13.2
+// at 27 440 particles, 23.0 -> 19.1 and 14.4 -> 13.2 at 55 296 in 245 tiles; past
+// 256 tiles they are slower (24.4 -> 26.5 us at 75 712 particles in about 290,
+// 20.4 -> 28.7 at 84 640 in a layer of five cells).  The occupied tiles are not
+// known here: a bed five cells high or more has up to 2.5 per full one and each
+// instance some at its edges.  Below some full tiles there is nothing to gain
+// (15.6 and 15.8 us at 1152 particles).
+int wide_tiles(const ddm_config& c, int64_t ntot, int n_inst) {
   const double per_tile = c.ppc * 64.0, tiles = c.precision == DDM_F64 ? 256.0 : 512.0;
-  return c.dim == 3 && per_tile > ddm::kBlock && (double)ntot <= tiles * per_tile;
+  if (c.dim != 3 || !(per_tile > ddm::kBlock) || !((double)ntot <= tiles * per_tile)) return 0;
+  const bool most = c.precision != DDM_F64 && per_tile >= 2 * ddm::kBlock && (double)ntot >= 8.0 * per_tile &&
+                    2.5 * (double)ntot + 8.0 * n_inst * per_tile <= 256.0 * per_tile;
+  return most ? 2 : 1;
 }
 
 // Kernel configuration of a context (or of a context-free call) with
@@ -771,7 +783,7 @@ ddm::KCfg make_kcfg(const ddm_config& c, int n_inst, int64_t ntot) {
   k.w_hm = c.w_hm; k.w_mass = c.w_mass; k.m_target = c.m_target; k.m_ref = c.m_ref;
   k.w_emd = c.w_emd;
   k.det = c.deterministic ? 1 : 0;
-  k.wide = wide_tiles(c, ntot) ? 1 : 0;
+  k.wide = wide_tiles(c, ntot, n_inst);
   return k;
 }
 
