@@ -43,6 +43,7 @@ struct InstDev {
   double dmu_dE, dmu_dnu, dlam_dE, dlam_dnu, dal_dphi, dkc_dphi;   // chain to (E, nu, phi_deg)
   int64_t off, n;                    // first padded particle slot and particle count
   int64_t goff;                      // first grid node of the instance
+  int64_t pad;                       // padding slots before the instance: off less the particles before it
   double tip0[3];
 };
 

@@ -789,8 +789,9 @@ ddm::KCfg make_kcfg(const ddm_config& c, int n_inst, int64_t ntot) {
 
 // Device constants of instance i: Lame constants, alpha_f and the cohesion
 // shift (Sec. III-A, Eq. DP), particle mass and volume, the chain to
-// (E, nu, phi_deg), its first padded slot `off` and its grid offset.
-ddm::InstDev make_instdev(const ddm_config& c, const ddm_instance& s, int i, int64_t off, int64_t nodes) {
+// (E, nu, phi_deg), its first padded slot `off` (after `pad` padding slots) and
+// its grid offset.
+ddm::InstDev make_instdev(const ddm_config& c, const ddm_instance& s, int i, int64_t off, int64_t pad, int64_t nodes) {
   ddm::InstDev d;
   const double dxd = std::pow(1.0 / c.n_grid, c.dim);
   const double E = s.E, nu = s.nu, ph = s.phi_deg * kPi / 180.0, sp = std::sin(ph), cp = std::cos(ph);
@@ -813,6 +814,7 @@ ddm::InstDev make_instdev(const ddm_config& c, const ddm_instance& s, int i, int
   d.off = off;
   d.n = s.n_particles;
   d.goff = (int64_t)i * nodes;
+  d.pad = pad;
   for (int a = 0; a < 3; ++a) d.tip0[a] = s.tip0[a];
   return d;
 }
@@ -825,13 +827,14 @@ ddm_status upload_instances(ddm_ctx* x, const ddm_instance* inst) {
   ddm_status s = DDM_OK;
   std::vector<ddm::InstDev> dev(n_inst);
   std::vector<int> blk((size_t)L.nblk);
-  int64_t off = 0;
+  int64_t off = 0, pad = 0;
   for (int i = 0; i < n_inst; ++i) {
     const ddm_instance& s = inst[i];
-    dev[i] = make_instdev(*cfg, s, i, off, k.nodes);
+    dev[i] = make_instdev(*cfg, s, i, off, pad, k.nodes);
     const int64_t np = pad_up(s.n_particles, ddm::kBlock);
     for (int64_t bI = off / ddm::kBlock; bI < (off + np) / ddm::kBlock; ++bI) blk[(size_t)bI] = i;
     off += np;
+    pad += np - s.n_particles;
   }
   const size_t js = (size_t)8 * kSkill;      // pose Jacobian values per sub-step
   std::vector<double> poses((size_t)n_inst * cfg->max_steps * 8, 0.0), jac((size_t)n_inst * cfg->max_steps * js, 0.0);
@@ -1685,7 +1688,7 @@ ddm_status ddm_loss_noalloc(const ddm_config* cfg, const ddm_instance* inst, int
   ddm_config c1 = *cfg;
   c1.max_steps = 1;
   ddm::KCfg kc = make_kcfg(c1, 1, ntot);
-  const ddm::InstDev dev = make_instdev(*cfg, *inst, 0, 0, kc.nodes);
+  const ddm::InstDev dev = make_instdev(*cfg, *inst, 0, 0, 0, kc.nodes);
   double row[ddm::kPoseVals] = {0};
   if (final_step >= 0 && cfg->shovel) {
     ddm_config cp = *cfg;

@@ -543,16 +543,28 @@ __device__ __forceinline__ uint32_t table_scan(uint32_t v, uint32_t* sum) {
   return off + x - v;
 }
 
-// Marks the 3^D blocks around tile gt.
-__device__ __forceinline__ void mark_around(const KCfg& c, uint32_t gt, uint32_t* mask) {
+// Of the four tiles 4 i .. 4 i + 3, those with an occupied tile among the 3^D
+// around them, a bit each.  nib(j): the occupied ones of tiles 4 j .. 4 j + 3.  A
+// row of tiles along the last axis holds whole fours (grids have 16 nodes a
+// side at least), so a row's part is three of them.  Read like this it takes
+// 3 us of the launch on a 64^3 grid (10.9 in all); each occupied tile marking the blocks
+// around it, in memory or by LDS atomics on the words that its neighbours mark
+// as well, took 8.
+template <typename Nib>
+__device__ __forceinline__ uint32_t near_occupied(const KCfg& c, uint32_t i, Nib&& nib) {
   const int D = c.dim, tb = c.nlog2 - 2, nt = 1 << tb;
-  const uint32_t per = 1u << (D * tb), inst = gt >> (D * tb), t = gt & (per - 1u);
-  const int q2 = D == 3 ? (int)(t & (uint32_t)(nt - 1)) : 0;
-  const int q1 = (int)((D == 3 ? t >> tb : t) & (uint32_t)(nt - 1)), q0 = (int)(t >> ((D - 1) * tb));
+  const uint32_t per = 1u << (D * tb), first = (4u * i) & ~(per - 1u), t = (4u * i) & (per - 1u);
+  const int ql = (int)(t & (uint32_t)(nt - 1)), qm = D == 3 ? (int)((t >> tb) & (uint32_t)(nt - 1)) : 0;
+  const int q0 = (int)(t >> ((D - 1) * tb));
+  uint32_t near = 0;
   for (int a = max(q0 - 1, 0); a <= min(q0 + 1, nt - 1); ++a)
-    for (int e = max(q1 - 1, 0); e <= min(q1 + 1, nt - 1); ++e)
-      for (int f = D == 3 ? max(q2 - 1, 0) : 0; f <= (D == 3 ? min(q2 + 1, nt - 1) : 0); ++f)
-        mask[inst * per + (uint32_t)(D == 3 ? (((a << tb) + e) << tb) + f : (a << tb) + e)] = 1u;
+    for (int e = max(qm - 1, 0); e <= (D == 3 ? min(qm + 1, nt - 1) : 0); ++e) {
+      const uint32_t j = (first + (uint32_t)((D == 3 ? (a << tb) + e : a) << tb) + (uint32_t)ql) >> 2;
+      // tiles ql - 1 .. ql + 4 of the row
+      const uint32_t w = (ql > 0 ? nib(j - 1u) >> 3 : 0u) | nib(j) << 1 | (ql + 4 < nt ? (nib(j + 1u) & 1u) << 5 : 0u);
+      near |= w | w >> 1 | w >> 2;
+    }
+  return near & 15u;
 }
 
 // The table of up to kTableTiles tiles per workgroup.  One workgroup does it
@@ -565,22 +577,41 @@ __global__ void __launch_bounds__(kTableThreads) k_bin_table(KCfg c, const InstD
                                                              TableOut o) {
   constexpr int PER = kTableTiles / kTableThreads;
   __shared__ uint32_t hist[kTileBuckets], first[kTileBuckets], sums[1 + kTileBuckets], abase;
+  __shared__ unsigned char occ[kTableThreads];
   const int tid = threadIdx.x;
   const int64_t t0 = (int64_t)blockIdx.x * kTableTiles + (int64_t)tid * PER;
   if (tid < kTileBuckets) hist[tid] = 0u;
   if (tid <= kTileBuckets) sums[tid] = 0u;
   __syncthreads();
-  uint32_t n[PER], own = 0;
+  static_assert(PER == 4, "near_occupied takes four tiles");
+  uint32_t n[PER], own = 0, full = 0;
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     n[k] = t0 + k < total_tiles ? o.tcnt[t0 + k] : 0u;
     own += n[k];
-    if (n[k] && STAGE != 2) mark_around(c, (uint32_t)(t0 + k), o.act.mask);
+    if (n[k]) full |= 1u << k;
     if (n[k] && STAGE != 2) atomicAdd(&hist[tile_bucket(n[k])], 1u);
   }
+  if (STAGE != 2) occ[tid] = (unsigned char)full;
   uint32_t tot = 0, before = 0;
   before = table_scan(own, &tot);
   __syncthreads();
+  // active blocks of this thread; tiles of other workgroups by their counts
+  // (which the second launch clears)
+  uint32_t marked = 0;
+  if (STAGE != 2 && t0 < total_tiles) {
+    marked = near_occupied(c, (uint32_t)(t0 / PER), [&](uint32_t j) -> uint32_t {
+      const uint32_t r = j - blockIdx.x * kTableThreads;
+      if (r < (uint32_t)kTableThreads) return occ[r];
+      uint32_t v = 0;
+#pragma unroll
+      for (int k = 0; k < PER; ++k) v |= o.tcnt[(int64_t)j * PER + k] ? 1u << k : 0u;
+      return v;
+    });
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      if ((marked >> k) & 1u) o.act.mask[t0 + k] = 1u;
+  }
   if (STAGE == 1) {
     uint32_t* pt = o.part + (int64_t)blockIdx.x * (1 + kTileBuckets);
     if (tid == 0) pt[0] = tot;
@@ -597,11 +628,18 @@ __global__ void __launch_bounds__(kTableThreads) k_bin_table(KCfg c, const InstD
     }
     __syncthreads();
   }
-  if (tid == 0) {
-    uint32_t acc = 0;
-    for (int k = kTileBuckets - 1; k >= 0; --k) { first[k] = acc; acc += hist[k]; }
-    for (int k = 0; k < kTileBuckets; ++k) first[k] += sums[1 + k];
-    if (blockIdx.x == 0) {
+  if (tid < 64) {
+    static_assert(kTileBuckets <= 64, "a lane per bucket");
+    const int k = kTileBuckets - 1 - tid;
+    const uint32_t h = k >= 0 ? hist[k] : 0u;
+    uint32_t acc = h;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t y = __shfl_up(acc, d, 64);
+      if (tid >= d) acc += y;
+    }
+    if (k >= 0) first[k] = acc - h + sums[1 + k];
+    if (blockIdx.x == 0 && tid == 63) {
       *o.count = acc;
       if (o.count2) *o.count2 = acc;
     }
@@ -611,7 +649,7 @@ __global__ void __launch_bounds__(kTableThreads) k_bin_table(KCfg c, const InstD
   uint32_t run = sums[0] + before;
   const int pb = c.dim * (c.nlog2 - 2);
   int cur = -1;
-  uint32_t shift = 0;                     // first slot of the instance less the particles of those before it
+  uint32_t shift = 0;                     // the padding before the instance
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     const int64_t t = t0 + k;
@@ -619,9 +657,7 @@ __global__ void __launch_bounds__(kTableThreads) k_bin_table(KCfg c, const InstD
     const int i = (int)(t >> pb);
     if (i != cur) {
       cur = i;
-      int64_t sum = 0;
-      for (int q = 0; q < i; ++q) sum += inst[q].n;
-      shift = (uint32_t)(inst[i].off - sum);
+      shift = (uint32_t)inst[i].pad;
     }
     const uint32_t st = run + shift;
     run += n[k];
@@ -636,12 +672,11 @@ __global__ void __launch_bounds__(kTableThreads) k_bin_table(KCfg c, const InstD
     }
     o.tslot[t] = slot;
   }
-  // active blocks (this workgroup's marks are complete here: after the
-  // barriers of one workgroup, or an earlier launch)
+  // list of the active blocks
   uint32_t a[PER], na = 0;
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
-    a[k] = t0 + k < total_tiles ? o.act.mask[t0 + k] : 0u;
+    a[k] = STAGE == 0 ? (marked >> k) & 1u : (t0 + k < total_tiles ? o.act.mask[t0 + k] : 0u);
     na += a[k] ? 1u : 0u;
   }
   uint32_t atot = 0, pos = table_scan(na, &atot);
