@@ -150,6 +150,26 @@ def algorithmic_bytes_p2g(n_particles, n_active, b=4, d=3):
     return n_particles * per_particle + n_active * (d + 1) * b
 
 
+def algorithmic_bytes_p2g_joined(n_particles, n_active, recorded, b=4, d=3):
+    """A P2G launch that does the G2P of the sub-step before as well (the launches
+    of sub-steps that no binning precedes): per particle x and G read and
+    written (v and C stay in registers; a recorded sub-step writes them); per
+    active node the v gathered and the (d + 1) b added.  recorded: the share of
+    recorded sub-steps."""
+    per_particle = 2 * (d + d * d) * b + recorded * (d + d * d) * b
+    return n_particles * per_particle + n_active * (2 * d + 1) * b
+
+
+def algorithmic_bytes_p2g_mean(n_particles, n_active, sort_every, recorded=0.0, period=None, b=4, d=3):
+    """Mean over the P2G launches of a run that bins every sort_every sub-steps
+    (0: once) and at the start of every period sub-steps."""
+    period = period or max(1, sort_every)
+    bins = -(-period // sort_every) if sort_every else 1
+    plain = min(1.0, bins / period)
+    return plain * algorithmic_bytes_p2g(n_particles, n_active, b, d) \
+        + (1.0 - plain) * algorithmic_bytes_p2g_joined(n_particles, n_active, recorded, b, d)
+
+
 def algorithmic_bytes_pass(n_particles, n_active, b=4, d=3):
     """Bytes per particle-step that a fwd+bwd pass must move: per particle the
     state written and read in the forward (2 S_p), again in the recompute
@@ -496,7 +516,7 @@ def forward_bench(args, torch, ddm):
         print(f"# plain loop: {t_plain * 1e3:.1f} ms/step, {plain_value:.3e} particle-steps/s", flush=True)
 
     p2g_ms, p2g_n = timing["p2g"]
-    per_launch = algorithmic_bytes_p2g(n, n_act, b, d)
+    per_launch = algorithmic_bytes_p2g_mean(n, n_act, R, period=None if R else steps, b=b, d=d)
     achieved = per_launch / (p2g_ms / p2g_n * 1e-3) / 1e9 if p2g_n else None
     fwd_bytes = algorithmic_bytes_forward(n, n_act, b, d)
     bound = HBM_PEAK_GBS * 1e9 / fwd_bytes
@@ -634,7 +654,9 @@ def main():
     dom = max(breakdown, key=lambda k: breakdown[k][0])
     p2g_ms, p2g_n = timing["p2g"]
     esz = 8 if args.precision == "f64" else 4
-    per_launch_bytes = algorithmic_bytes_p2g(n_part, n_act, b=esz)
+    per_launch_bytes = algorithmic_bytes_p2g_mean(
+        n_part, n_act, R, recorded=min(1.0, ws[0].steps * args.steps / p2g_n) if p2g_n else 0.0,
+        period=ws[0].checkpoint_every, b=esz)
     achieved = per_launch_bytes / (p2g_ms / p2g_n * 1e-3) / 1e9 if p2g_n else None
     breakdown = {k: {"ms": round(v[0], 3), "launches": v[1]} for k, v in breakdown.items() if v[1]}
 

@@ -472,7 +472,8 @@ __device__ __forceinline__ RunRec<T> read_record(const RunLDS<T, BLK>& L, int t)
 // in 3D, the whole stencil in 2D), NN = 3 a row along the last axis (fewer
 // registers, more items, but each item reads the run's records again).  Both
 // scatter kernels use planes: P2G ran 568 us per launch with rows and 516 with
-// planes on the 64-instance workload.  Ends synchronised.
+// planes on the 64-instance workload, and 27.5 against 24.9 us at 27 440
+// particles, where units stand idle.  Ends synchronised.
 // NCOL = 1: every item adds to the window at once (LDS atomics in arbitrary
 // order).  NCOL = 3^D (the deterministic mode, with particles binned before
 // the sub-step so that a cell's particles form one run): pass k takes the runs
@@ -807,9 +808,10 @@ __device__ __forceinline__ bool gather_part(const KCfg& c, const Bufs& b, int in
 // v and x wait for the scatter in the thread's own LDS record.  A sub-step that
 // does not bin first needs no state but x and G in memory then: 96 B per
 // particle instead of 204 (168 instead of 228 while recording).  Bound by the
-// latency of its chain at four waves per SIMD (128 registers): 136 us at 1.8 M
-// particles against 99 and 46 us for the two launches, 33 against 25 and 12 at
-// 219 488.
+// latency of its chain at four waves per SIMD (128 registers), at large sizes by
+// the vector units (70 % busy, 2025 instructions per 64 particles): 130 us at
+// 1.8 M particles against 99 and 46 us for the two launches, 31 against 25 and
+// 12 at 219 488.  Loading the first tile's record with the count changed nothing.
 template <typename T, int D, bool DET, int BLK, bool GATHER>
 __global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
 k_p2g(KCfg c, Bufs b, TileList tl, const void* st_in, void* st_out, T* __restrict__ stg, T* __restrict__ gout,
@@ -1774,8 +1776,13 @@ __device__ __forceinline__ int g2p_adj_particle(const KCfg& c, const int (&org)[
 // window's 512 nodes and the first round's particles are loaded together, before
 // the accumulation window is cleared, and the nodes are read a plane of nine at
 // a time.  One after the other and in a rolled loop this was 26.8 us at 219 488
-// particles and 98.4 us at 1.8 M; it is 23.2 and 84.9 (1.9 and 6.5 us of
-// it from the loads, the rest from the planes; all 27 nodes at once cost a wave per SIMD).
+// particles and 98.4 us at 1.8 M; then 23.2 and 84.9 (1.9 and 6.5 us of it from
+// the loads, the rest from the planes; all 27 nodes at once cost a wave per
+// SIMD).  The particle's part as a function of its own (107 to 110 registers,
+// 128 and a spill within the loop's body) gave 77.0 at 1.8 M.  Joined with the
+// P2G adjoint of the sub-step after, tile by tile, the two were slower (51
+// against 48 us at 219 488, 224 against 205 at 1.8 M): tiles fill fewer compute
+// units and lanes than the P2G adjoint does by itself.
 // ---------------------------------------------------------------------------
 template <typename T, int D, bool DET, int BLK>
 __global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) k_g2p_adj(KCfg c, Bufs b, TileList tl, const void* stv,
