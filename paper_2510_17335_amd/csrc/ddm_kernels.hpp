@@ -67,6 +67,7 @@ struct KCfg {
   double w_emd;
   int det;                           // deterministic mode: fixed-order window and reduction sums
   int wide;                          // tile kernels with kBlock << wide threads per workgroup (wide_tiles in ddm_runtime.hip)
+  int bucket_shift;                  // tiles are listed by particle count in buckets of 2^bucket_shift (tile_bucket in ddm_sort.hip)
 };
 
 // Node of an active-set item: item i is node i % 4^D of listed block i / 4^D.

@@ -784,6 +784,9 @@ ddm::KCfg make_kcfg(const ddm_config& c, int n_inst, int64_t ntot) {
   k.w_emd = c.w_emd;
   k.det = c.deterministic ? 1 : 0;
   k.wide = wide_tiles(c, ntot, n_inst);
+  // up to four workgroups of kBlock threads on each of 256 compute units, unless
+  // they take a tile of more than 512 particles in one round or (2D) never meet one
+  k.bucket_shift = c.dim == 3 && k.wide != 2 && (double)ntot <= 1024.0 * 64.0 * c.ppc ? 6 : 5;
   return k;
 }
 

@@ -318,11 +318,19 @@ __global__ void k_tile_bounds(KCfg c, const uint32_t* keys, int tshift, uint32_t
 
 // One record per occupied tile (a workgroup takes a whole tile, however many
 // particles it holds), and the record of each tile in tslot.  The records
-// are ordered by particle count, largest first, in buckets of 32 particles
+// are ordered by particle count, largest first, in buckets of 2^shift particles
 // (kTileBuckets, the last open-ended): workgroups are dispatched in list
 // order, so the longest tiles start first and the short ones fill the end of
 // the launch (P2G 566 -> 532 us per launch on the 64-instance batch).
-__device__ __forceinline__ int tile_bucket(uint32_t n) { return min(kTileBuckets - 1, (int)(n >> 5)); }
+// Buckets of 32 leave all tiles above 480 in one.  Of 64 they set those beyond
+// 512, with a round more to do, apart: while all workgroups are resident or
+// nearly so, the longest decides the launch (joined G2P + P2G 37.0 -> 35.0 us for
+// five beds of 54 872 particles, 31.4 -> 31.0 at 219 488, the G2P adjoint 23.2 ->
+// 22.6).  In larger contexts the G2P adjoint loses more (75.5 -> 78.7 us at 1.8 M
+// particles, 142.7 -> 147.9 for 24 beds) than P2G gains (129.5 -> 128.7).
+__device__ __forceinline__ int tile_bucket(uint32_t n, int shift) {
+  return min(kTileBuckets - 1, (int)((n - 1u) >> shift));
+}
 
 // Counts per bucket: a workgroup histogram in LDS, then one global add per
 // bucket and workgroup.
@@ -332,7 +340,7 @@ __global__ void k_tile_buckets(int64_t total_tiles, const uint32_t* tstart, cons
   __syncthreads();
   const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   const uint32_t e = t < total_tiles ? tend[t] : 0u;
-  if (e != 0u) atomicAdd(&h[tile_bucket(e - tstart[t])], 1u);
+  if (e != 0u) atomicAdd(&h[tile_bucket(e - tstart[t], 5)], 1u);
   __syncthreads();
   if (threadIdx.x < kTileBuckets && h[threadIdx.x] != 0u) atomicAdd(&bucket[threadIdx.x], h[threadIdx.x]);
 }
@@ -359,7 +367,7 @@ __global__ void k_tile_list(int64_t total_tiles, const uint32_t* tstart, const u
   const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   const uint32_t e = t < total_tiles ? tend[t] : 0u;
   const uint32_t st = e != 0u ? tstart[t] : 0u;
-  const int bk = tile_bucket(e - st);
+  const int bk = tile_bucket(e - st, 5);
   const uint32_t rank = e != 0u ? atomicAdd(&h[bk], 1u) : 0u;
   __syncthreads();
   if (threadIdx.x < kTileBuckets && h[threadIdx.x] != 0u)
@@ -590,7 +598,7 @@ __global__ void __launch_bounds__(kTableThreads) k_bin_table(KCfg c, const InstD
     n[k] = t0 + k < total_tiles ? o.tcnt[t0 + k] : 0u;
     own += n[k];
     if (n[k]) full |= 1u << k;
-    if (n[k] && STAGE != 2) atomicAdd(&hist[tile_bucket(n[k])], 1u);
+    if (n[k] && STAGE != 2) atomicAdd(&hist[tile_bucket(n[k], c.bucket_shift)], 1u);
   }
   if (STAGE != 2) occ[tid] = (unsigned char)full;
   uint32_t tot = 0, before = 0;
@@ -665,7 +673,7 @@ __global__ void __launch_bounds__(kTableThreads) k_bin_table(KCfg c, const InstD
     o.tcnt[t] = 0u;                       // for the next binning
     uint32_t slot = kNoSlot;
     if (n[k]) {
-      slot = atomicAdd(&first[tile_bucket(n[k])], 1u);
+      slot = atomicAdd(&first[tile_bucket(n[k], c.bucket_shift)], 1u);
       const TileRec r{st, st + n[k], (uint32_t)t};
       o.list[slot] = r;
       if (o.list2) o.list2[slot] = r;
