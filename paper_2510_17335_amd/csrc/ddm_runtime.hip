@@ -121,7 +121,9 @@ Layout make_layout(const ddm_config& c, int n_inst, const ddm_instance* in) {
   L.poses = cv.take((size_t)n_inst * c.max_steps * ddm::kPoseVals * b);
   L.pose_jac = cv.take((size_t)n_inst * c.max_steps * 8 * ddm::kSkillParams * sizeof(double));
   L.err = cv.take(sizeof(ddm::DevErr));
+  // (err, tqueue and tcnt are cleared together)
   L.tqueue = cv.take(2 * sizeof(uint32_t));
+  L.tcnt = cv.take(sizeof(uint32_t) * L.total_tiles);
   L.pid = cv.take(sizeof(uint32_t) * ntot);
   L.pid_tmp = cv.take(sizeof(uint32_t) * ntot);
   L.cur = cv.take(L.state_bytes);
@@ -180,7 +182,6 @@ Layout make_layout(const ddm_config& c, int n_inst, const ddm_instance* in) {
   L.tcount = cv.take(sizeof(uint32_t));
   L.tslot = cv.take(sizeof(uint32_t) * L.total_tiles);
   L.tbucket = cv.take(sizeof(uint32_t) * 2 * ddm::kTileBuckets);
-  L.tcnt = cv.take(sizeof(uint32_t) * L.total_tiles);
   L.tpart = cv.take(sizeof(uint32_t) * ddm::bin_part_words(L.total_tiles));
   L.staging = cv.take(L.win_bytes * L.total_tiles);
   L.gout = cv.take(L.grid_bytes);
@@ -946,9 +947,10 @@ ddm_status ddm_create(const ddm_config* cfg, int32_t n_inst, const ddm_instance*
   x->kc = make_kcfg(*cfg, n_inst, L.ntot);
 
   s = upload_instances(x, inst);
-  if (s == DDM_OK) s = hip_check(hipMemset(x->at(L.err), 0, sizeof(ddm::DevErr)), "clear error word");
-  if (s == DDM_OK) s = hip_check(hipMemset(x->at(L.tqueue), 0, 2 * sizeof(uint32_t)), "clear tile queue");
-  if (s == DDM_OK) s = hip_check(hipMemset(x->at(L.tcnt), 0, sizeof(uint32_t) * L.total_tiles), "clear tile counters");
+  // one synchronous clear: each takes some 50 us of a context's creation
+  if (s == DDM_OK)
+    s = hip_check(hipMemset(x->at(L.err), 0, L.tcnt + sizeof(uint32_t) * L.total_tiles - L.err),
+                  "clear error word, tile queue and tile counters");
   if (s == DDM_OK && cfg->deterministic)
     s = hip_check(hipMemset(x->at(L.dpart), 0, sizeof(double) * ddm::kDetVals * (size_t)std::max(L.nblk, L.total_tiles)),
                   "clear deterministic partials");
