@@ -194,6 +194,19 @@ __device__ __forceinline__ void block_accumulate(double (&v)[N], double* dst, do
   }
 }
 
+// The sums of a workgroup of one wave, added by a lane each.
+template <int N>
+__device__ __forceinline__ void wave_accumulate(const double (&v)[N], double* dst) {
+  const int lane = threadIdx.x & 63;
+  double mine = 0.0;
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const double s = wave_sum(v[k]);
+    if (lane == k) mine = s;
+  }
+  if (lane < N && mine != 0.0) atomicAdd(&dst[lane], mine);
+}
+
 // The accumulator slot of this workgroup among its instance's kAccSlots (8
 // doubles each, summed by k_grad_final).  Additions to one address follow one
 // another at about 10 ns: with one slot per instance the 857 workgroups of the
@@ -2167,7 +2180,9 @@ void launch_grid_adj(int prec, const KCfg& c, const Bufs& b, int step, const uin
 // sub-step at 1.8 M particles (FP32) against 133 us, 42 against 28 at 219 488,
 // 18.5 against 14.8 at 27 440.  The gather's sums by node, row and plane (rather
 // than by node and row) and the accumulator slots then gave 121, 24.5 and
-// 14.1 us.  HBM alone needs 79 us at 1.8 M (264 B a particle at 6 TB/s), the
+// 14.1 us; workgroups of one wave, which wait for no other at the sums and are
+// placed one by one, 118, 23.9 and 13.5 (the deterministic mode keeps a partial per
+// kBlock particles).  HBM alone needs 79 us at 1.8 M (264 B a particle at 6 TB/s), the
 // vector units about as much.  Tried without gain: the second half's loads ahead
 // of the gather (136 and 29.6 us), all 27 nodes in flight at two waves per SIMD
 // (171 us, and 18.7 at 27 440), the planes in a rolled loop (equal).
@@ -2189,13 +2204,13 @@ __device__ __forceinline__ void ftmp_of(const P<T, D>& st, int64_t p, T dt, T Cm
     }
 }
 
-template <typename T, int D, bool SF>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
+template <typename T, int D, bool SF, int BLK>
+__global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
 k_p2g_adj(KCfg c, Bufs b, const void* stv, const T* __restrict__ tau, const T* __restrict__ gbar, const void* adj_next,
           void* adj_cur, double* pacc) {
-  const int inst = b.blk_inst[blockIdx.x];
+  const int inst = b.blk_inst[blockIdx.x / (kBlock / BLK)];
   const InstDev& I = b.inst[inst];
-  const int64_t p0 = (int64_t)blockIdx.x * kBlock;
+  const int64_t p0 = (int64_t)blockIdx.x * BLK;
   const uint32_t p = threadIdx.x;
   double acc[5] = {0, 0, 0, 0, 0};        // mu, lambda, alpha, k_c, rho
   if ((int64_t)p < I.n - (p0 - I.off)) {
@@ -2388,25 +2403,31 @@ k_p2g_adj(KCfg c, Bufs b, const void* stv, const T* __restrict__ tau, const T* _
     acc[2] = (double)alb;
     acc[3] = (double)kcb;
   }
-  block_accumulate<5>(acc, acc_slot(pacc, inst), b.dpart);
+  if constexpr (BLK == 64) wave_accumulate<5>(acc, acc_slot(pacc, inst));
+  else block_accumulate<5>(acc, acc_slot(pacc, inst), b.dpart);
 }
 
 void launch_p2g_adj(int prec, const KCfg& c, const Bufs& b, int nblk, const void* st, const void* tau, const void* gb,
                     bool stress_form, const void* adj_next, void* adj_cur, double* pacc, hipStream_t s) {
+#define DDM_P2GADJ_(T, DD, SF, BLK)                                                                                  \
+  hipLaunchKernelGGL((k_p2g_adj<T, DD, SF, BLK>), dim3(nblk * (kBlock / BLK)), dim3(BLK), 0, s, c, b, st,            \
+                     (const T*)tau, (const T*)gb, adj_next, adj_cur, pacc)
 #define DDM_P2GADJ(T, DD)                                                                                            \
-  if (stress_form)                                                                                                 \
-    hipLaunchKernelGGL((k_p2g_adj<T, DD, true>), dim3(nblk), dim3(kBlock), 0, s, c, b, st, (const T*)tau,           \
-                       (const T*)gb, adj_next, adj_cur, pacc);                                                      \
-  else                                                                                                             \
-    hipLaunchKernelGGL((k_p2g_adj<T, DD, false>), dim3(nblk), dim3(kBlock), 0, s, c, b, st, (const T*)tau,          \
-                       (const T*)gb, adj_next, adj_cur, pacc);                                                      \
-  if (b.dpart) launch_det_finish(c, b, false, 5, pacc, 8 * kAccSlots, s);
+  if (c.det) {                                                                                                       \
+    if (stress_form) DDM_P2GADJ_(T, DD, true, kBlock);                                                               \
+    else DDM_P2GADJ_(T, DD, false, kBlock);                                                                          \
+    if (b.dpart) launch_det_finish(c, b, false, 5, pacc, 8 * kAccSlots, s);                                          \
+  } else {                                                                                                           \
+    if (stress_form) DDM_P2GADJ_(T, DD, true, 64);                                                                   \
+    else DDM_P2GADJ_(T, DD, false, 64);                                                                              \
+  }
   if (prec == 0) {
     if (c.dim == 3) { DDM_P2GADJ(float, 3) } else { DDM_P2GADJ(float, 2) }
   } else {
     if (c.dim == 3) { DDM_P2GADJ(double, 3) } else { DDM_P2GADJ(double, 2) }
   }
 #undef DDM_P2GADJ
+#undef DDM_P2GADJ_
 }
 
 // ---------------------------------------------------------------------------
