@@ -795,7 +795,7 @@ __device__ __forceinline__ bool gather_part(const KCfg& c, const Bufs& b, int in
   for (int a = 0; a < D; ++a) {
     si.xr(a, p) = xn[a];
     rl.rec[0][rec_pos(p)][a] = vn[a];
-    reinterpret_cast<X*>(rl.rec[1][rec_pos(p)])[a] = xn[a];
+    rl.rec[1][rec_pos(p)][a] = Pos<T>::hold(xn[a]);
     if (ga.write_vc) {
       si.v(a, p) = vn[a];
 #pragma unroll
@@ -857,7 +857,7 @@ k_p2g(KCfg c, Bufs b, TileList tl, const void* st_in, void* st_out, T* __restric
 #pragma unroll
           for (int a = 0; a < D; ++a) {
             v[a] = GATHER ? rl.rec[0][rec_pos(p)][a] : si.v(a, p);
-            x[a] = GATHER ? reinterpret_cast<const typename Pos<T>::X*>(rl.rec[1][rec_pos(p)])[a] : si.xr(a, p);
+            x[a] = GATHER ? Pos<T>::held(rl.rec[1][rec_pos(p)][a]) : si.xr(a, p);
           }
         };
         Stencil<T, D> S;

@@ -37,6 +37,9 @@ template <> struct Pos<float> {
   }
   static __device__ __forceinline__ unsigned long long key(X xr) { return (unsigned long long)xr; }
   static __device__ __forceinline__ double unkey(unsigned long long k) { return (double)k * 2.3283064365386963e-10; }
+  // the stored position in a place for a T, and back
+  static __device__ __forceinline__ float hold(X xr) { return __uint_as_float(xr); }
+  static __device__ __forceinline__ X held(float h) { return __float_as_uint(h); }
 };
 template <> struct Pos<double> {
   using X = double;
@@ -53,6 +56,8 @@ template <> struct Pos<double> {
   static __device__ __forceinline__ X from_real(double x) { return x; }
   static __device__ __forceinline__ unsigned long long key(X xr) { return (unsigned long long)__double_as_longlong(xr); }
   static __device__ __forceinline__ double unkey(unsigned long long k) { return __longlong_as_double((long long)k); }
+  static __device__ __forceinline__ double hold(X xr) { return xr; }
+  static __device__ __forceinline__ X held(double h) { return h; }
 };
 
 // A pointer that is the same for the whole wave, held in scalar registers: the
