@@ -53,6 +53,63 @@ __device__ __forceinline__ TileRec tile_record(const TileList& tl, uint32_t t) {
   return TileRec{(uint32_t)__builtin_amdgcn_readfirstlane(r.start), (uint32_t)__builtin_amdgcn_readfirstlane(r.end),
                  (uint32_t)__builtin_amdgcn_readfirstlane(r.tile)};
 }
+// The thread's index, opaque to the compiler: what is computed from it is
+// computed where it is used instead of being held in registers (or scratch)
+// from before a kernel's loops.
+template <int BLK> __device__ __forceinline__ int fresh_thread() {
+  int t = (int)threadIdx.x;
+#ifdef __HIP_DEVICE_COMPILE__
+  asm volatile("" : "+v"(t));
+#endif
+  static_assert((BLK & (BLK - 1)) == 0, "the mask bounds the index");
+  return t & (BLK - 1);
+}
+
+// Whether workgroups of more than kBlock threads (chosen by the context's size,
+// which says nothing about how many tiles its particles occupy) take several
+// tiles at once, with kBlock threads and a window each, instead of one.  They do
+// where more tiles are occupied than workgroups are resident and a tile has no
+// more than kBlock particles on average: with one tile at a time most of the
+// waves would have nothing to do and the others would wait for a place.  Joined
+// G2P + P2G and the G2P adjoint, FP32, one tile / several / workgroups of kBlock:
+// 100 352 particles in a layer one cell high (841 tiles, 512 threads) 27.9 / 22.4
+// / 19.7 and 20.0 / 16.7 / 15.8 us; 200 000 scattered ones (2704, 512) 66.4 / 49.8
+// / 42.0 and 45.8 / 40.3 / 36.4; 40 000 (2585, 1024) 110 / 52.3 / 46.3 and 58.1 /
+// 36.8 / 33.4; FP64, 51 200 in a layer (441, 512) 31.1 / 24.2 / 23.3 and 19.3 /
+// 16.4 / 14.9.  Fuller tiles stay one at a time: 600 tiles of 219 488 particles
+// take 30.5 and 22.2 us so, and two at once (four barriers a round for the longer
+// of them) 37.6 and 22.4.
+template <typename T, int BLK>
+__device__ __forceinline__ bool share_workgroup(const KCfg& c, uint32_t ntiles) {
+  constexpr uint32_t per_cu = sizeof(T) == 4 ? 1024 / BLK : 512 / BLK;   // resident workgroups: registers (FP32), LDS (FP64)
+  return BLK > kBlock && ntiles > per_cu * (uint32_t)c.cus && c.ntot <= (int64_t)kBlock * ntiles;
+}
+
+// The tile of this wave among the TILES that its workgroup takes at once, from
+// tile t0 of the list on.
+template <int BLK, int TILES> struct WaveTile {
+  static constexpr int kThreads = BLK / TILES;             // threads of a tile
+  int sub;                                                 // which of them (the same for the wave)
+  uint32_t t;                                              // its place in the list
+  bool have;                                               // (the last workgroup may have fewer)
+  TileRec tr;
+  int cnt, most;                                           // its particles, and the most of any of them
+  __device__ __forceinline__ WaveTile(const TileList& tl, uint32_t t0, uint32_t ntiles) {
+    sub = TILES == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / kThreads);
+    t = t0 + (uint32_t)sub;
+    have = TILES == 1 || t < ntiles;
+    tr = tile_record(tl, have ? t : t0);
+    cnt = have ? (int)(tr.end - tr.start) : 0;
+    most = cnt;
+#pragma unroll
+    for (int k = 0; k < (TILES == 1 ? 0 : TILES); ++k) {
+      const TileRec r = tile_record(tl, min(t0 + (uint32_t)k, ntiles - 1u));
+      most = max(most, (int)(r.end - r.start));
+    }
+  }
+  // the thread's number among those of its tile
+  __device__ __forceinline__ int thread() const { return fresh_thread<BLK>() & (kThreads - 1); }
+};
 __device__ __forceinline__ void finish_tiles(const TileList& tl) {
   if (!tl.queue || threadIdx.x != 0) return;
   __threadfence();
@@ -151,18 +208,6 @@ __device__ __forceinline__ void st_node(float* p, float a, float b, float c, flo
 __device__ __forceinline__ void st_node(double* p, double a, double b, double c, double d) {
   reinterpret_cast<double2*>(p)[0] = make_double2(a, b);
   reinterpret_cast<double2*>(p)[1] = make_double2(c, d);
-}
-
-// The thread's index, opaque to the compiler: what is computed from it is
-// computed where it is used instead of being held in registers (or scratch)
-// from before a kernel's loops.
-template <int BLK> __device__ __forceinline__ int fresh_thread() {
-  int t = (int)threadIdx.x;
-#ifdef __HIP_DEVICE_COMPILE__
-  asm volatile("" : "+v"(t));
-#endif
-  static_assert((BLK & (BLK - 1)) == 0, "the mask bounds the index");
-  return t & (BLK - 1);
 }
 
 // The sum over a wave of one double, in every lane.
@@ -432,6 +477,7 @@ template <typename T, int BLK> struct alignas(16) RunLDS {
   short wbase[BLK];
   int wcount[BLK / 64];
   unsigned short start[BLK + 1];
+  T mass[BLK / kBlock];                // particle mass of every kBlock slots, where they are of several tiles
 };
 
 template <typename T> __device__ __forceinline__ void st4(T* p, T a, T b, T c, T d) { p[0] = a; p[1] = b; p[2] = c; p[3] = d; }
@@ -480,7 +526,8 @@ __device__ __forceinline__ RunRec<T> read_record(const RunLDS<T, BLK>& L, int t)
 
 // Phase 2 for a round of rc slots whose records and wbase are in L (the
 // caller synchronised after writing them).  NV = D + 1 scatters momentum and
-// mass (mass per particle m); NV = D scatters a D-vector.  Work items cover
+// mass (mass per particle m, or L.mass with several tiles at once); NV = D
+// scatters a D-vector.  Work items cover
 // NN = 3 or 9 nodes of a run's stencil: NN = 9 takes a plane (fixed offset o0
 // in 3D, the whole stencil in 2D), NN = 3 a row along the last axis (fewer
 // registers, more items, but each item reads the run's records again).  Both
@@ -505,8 +552,8 @@ __device__ __forceinline__ int base_class(int wbase) {
   return ((i % 3) * 3 + (r / kWin) % 3) * 3 + (r % kWin) % 3;
 }
 
-template <typename T, int D, int NV, int NN, int NCOL, int BLK>
-__device__ void run_scatter_round(RunLDS<T, BLK>& L, int rc, double* win, T m) {
+template <typename T, int D, int NV, int NN, int NCOL, int BLK, int TILES>
+__device__ __forceinline__ void run_scatter_round(RunLDS<T, BLK>& L, int rc, double* win, T m) {
   constexpr int WS = Win<D>::stride;
   constexpr int NJ = NN / 3;                                  // rows per item
   constexpr int ITEMS = (D == 3 ? 9 : 3) / NJ;                // items per run
@@ -590,7 +637,7 @@ __device__ void run_scatter_round(RunLDS<T, BLK>& L, int rc, double* win, T m) {
         const int wi = base + (D == 3 ? Win<D>::idx(o0, jj, k) : Win<D>::idx(jj, k, 0));
 #pragma unroll
         for (int a = 0; a < D; ++a) atomicAdd(win + a * WS + wi, (double)acc[j][k][a]);
-        if (NV == D + 1) atomicAdd(win + 3 * WS + wi, (double)(acc[j][k][3] * m));
+        if (NV == D + 1) atomicAdd(win + 3 * WS + wi, (double)(acc[j][k][3] * (TILES == 1 ? m : L.mass[s0 / kBlock])));
       }
   }
   if (NCOL > 1) __syncthreads();
@@ -773,15 +820,15 @@ __device__ __forceinline__ bool g2p_compute(const KCfg& c, const Bufs& b, int in
 
 template <typename T> struct GatherArgs { const void* st_x; const T* post; int step, write_vc; };
 
-// The G2P of the sub-step before, for thread threadIdx.x of a tile round whose
-// first slot is p0: C and G into q, v and x into the thread's record, x (and v,
+// The G2P of the sub-step before, for particle p of a tile round whose first
+// slot is p0: C and G into q, v and x into the thread's record, x (and v,
 // C when write_vc) to si.  False when the particle's stencil left the grid
 // (flagged; its state stays).
 template <typename T, int D, int BLK>
 __device__ __forceinline__ bool gather_part(const KCfg& c, const Bufs& b, int inst, const GatherArgs<T>& ga, int64_t p0,
-                                            const P<T, D>& si, RunLDS<T, BLK>& rl, Part<T, D>& q) {
+                                            const P<T, D>& si, uint32_t p, RunLDS<T, BLK>& rl, Part<T, D>& q) {
+  const int slot = rec_pos((int)threadIdx.x);
   using X = typename Pos<T>::X;
-  const uint32_t p = threadIdx.x;
   const P<T, D> sx = pv<T, D>(ga.st_x, c.ntot).at(p0);
   Stencil<T, D> S;
   X xr[3], xn[3];
@@ -794,8 +841,8 @@ __device__ __forceinline__ bool gather_part(const KCfg& c, const Bufs& b, int in
 #pragma unroll
   for (int a = 0; a < D; ++a) {
     si.xr(a, p) = xn[a];
-    rl.rec[0][rec_pos(p)][a] = vn[a];
-    rl.rec[1][rec_pos(p)][a] = Pos<T>::hold(xn[a]);
+    rl.rec[0][slot][a] = vn[a];
+    rl.rec[1][slot][a] = Pos<T>::hold(xn[a]);
     if (ga.write_vc) {
       si.v(a, p) = vn[a];
 #pragma unroll
@@ -825,39 +872,40 @@ __device__ __forceinline__ bool gather_part(const KCfg& c, const Bufs& b, int in
 // the vector units (70 % busy, 2025 instructions per 64 particles): 130 us at
 // 1.8 M particles against 99 and 46 us for the two launches, 31 against 25 and
 // 12 at 219 488.  Loading the first tile's record with the count changed nothing.
-template <typename T, int D, bool DET, int BLK, bool GATHER>
-__global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
-k_p2g(KCfg c, Bufs b, TileList tl, const void* st_in, void* st_out, T* __restrict__ stg, T* __restrict__ gout,
-      ActiveSet act, T* __restrict__ tau_out, GatherArgs<T> q2) {
-  __shared__ double win[Win<D>::stride * kNodeVals];
-  __shared__ RunLDS<T, BLK> rl;
-  const uint32_t ntiles = *tl.count;
-  __shared__ uint32_t tile_slot;
-  for (uint32_t t = first_tile(tl, &tile_slot); t < ntiles; t = next_tile(tl, t, &tile_slot)) {
-    const TileRec tr = tile_record(tl, t);
+// TILES: the tiles that a workgroup takes at once (share_workgroup).
+template <typename T, int D, bool DET, int BLK, bool GATHER, int TILES>
+__device__ __forceinline__ void p2g_tiles(const KCfg& c, const Bufs& b, const TileList& tl, const void* st_in, void* st_out,
+                                          T* __restrict__ stg, T* __restrict__ gout, const ActiveSet& act,
+                                          T* __restrict__ tau_out, const GatherArgs<T>& q2, uint32_t ntiles, double* win,
+                                          RunLDS<T, BLK>& rl, uint32_t* tile_slot) {
+  using WT = WaveTile<BLK, TILES>;
+  constexpr int WV = Win<D>::stride * kNodeVals;           // values of a tile's window
+  for (uint32_t t0 = first_tile(tl, tile_slot); t0 * TILES < ntiles; t0 = next_tile(tl, t0, tile_slot)) {
+    const WT wt(tl, t0 * TILES, ntiles);
+    const TileRec& tr = wt.tr;
     int inst, org[3];
     tile_origin<D>(c, tr.tile, inst, org);
     const InstDev& I = b.inst[inst];
     T* g = gout + I.goff * kNodeVals;
     const T mpt = T(I.mp);
-    const int cnt = (int)(tr.end - tr.start);
-    for (int i = fresh_thread<BLK>(); i < Win<D>::stride * kNodeVals; i += BLK) win[i] = 0.0;
-    for (int r0 = 0; r0 < cnt; r0 += BLK) {
-      const int rc = min(BLK, cnt - r0);
+    for (int i = fresh_thread<BLK>(); i < TILES * WV; i += BLK) win[i] = 0.0;
+    if (TILES > 1 && threadIdx.x % kBlock == 0) rl.mass[threadIdx.x / kBlock] = mpt;
+    for (int r0 = 0; r0 < wt.most; r0 += WT::kThreads) {
+      const int rc = min(WT::kThreads, wt.cnt - r0);
       const int64_t p0 = (int64_t)tr.start + r0;
       int wb = -1;
-      if (threadIdx.x < rc) {
-        const uint32_t p = threadIdx.x;
+      if ((int)(threadIdx.x % WT::kThreads) < rc) {
+        const uint32_t p = threadIdx.x % WT::kThreads;
         const P<T, D> si = pv<T, D>(st_in, c.ntot).at(p0), so = pv<T, D>(st_out, c.ntot).at(p0);
         Part<T, D> part;
         bool moved = true;
-        if (GATHER) moved = gather_part<T, D, BLK>(c, b, inst, q2, p0, si, rl, part);
+        if (GATHER) moved = gather_part<T, D, BLK>(c, b, inst, q2, p0, si, p, rl, part);
         else load_part<T, D>(si, p, part);
         auto late = [&](T (&v)[3], typename Pos<T>::X (&x)[3]) {
 #pragma unroll
           for (int a = 0; a < D; ++a) {
-            v[a] = GATHER ? rl.rec[0][rec_pos(p)][a] : si.v(a, p);
-            x[a] = GATHER ? Pos<T>::held(rl.rec[1][rec_pos(p)][a]) : si.xr(a, p);
+            v[a] = GATHER ? rl.rec[0][rec_pos((int)threadIdx.x)][a] : si.v(a, p);
+            x[a] = GATHER ? Pos<T>::held(rl.rec[1][rec_pos((int)threadIdx.x)][a]) : si.xr(a, p);
           }
         };
         Stencil<T, D> S;
@@ -879,7 +927,7 @@ k_p2g(KCfg c, Bufs b, TileList tl, const void* st_in, void* st_out, T* __restric
 #pragma unroll
           for (int a = 0; a < D; ++a) { loc[a] = S.base[a] - org[a]; inwin &= loc[a] >= 0 && loc[a] <= kWin - 3; }
           if (inwin) {
-            wb = Win<D>::idx(loc[0], loc[1], loc[2]);
+            wb = wt.sub * WV + Win<D>::idx(loc[0], loc[1], loc[2]);
             put_record<T, D, BLK>(rl, fresh_thread<BLK>(), q, B, S.w);
           } else {
             mark_stencil_blocks<D>(c, inst, S.base, act);
@@ -893,23 +941,36 @@ k_p2g(KCfg c, Bufs b, TileList tl, const void* st_in, void* st_out, T* __restric
         }
       }
       rl.wbase[fresh_thread<BLK>()] = wb;
-      // the next round's states are on their way while this round is scattered
-      // (the barriers wait for LDS only)
       __syncthreads();
-      run_scatter_round<T, D, D + 1, 9, DET ? (D == 3 ? 27 : 9) : 1, BLK>(rl, rc, win, mpt);
+      run_scatter_round<T, D, D + 1, 9, DET ? (D == 3 ? 27 : 9) : 1, BLK, TILES>(rl, TILES == 1 ? rc : BLK, win, mpt);
     }
     __syncthreads();
     // the whole window, zeros included, to the tile's staging record
-    T* rec = stg + (int64_t)t * (kNodeVals * Win<D>::nodes);
-    for (int i = fresh_thread<BLK>(); i < Win<D>::nodes; i += BLK) {
+    T* rec = stg + (int64_t)wt.t * (kNodeVals * Win<D>::nodes);
+    for (int i = wt.thread(); i < (wt.have ? Win<D>::nodes : 0); i += WT::kThreads) {
       int l[3];
       Win<D>::coords(i, l);
-      const int wi = Win<D>::idx(l[0], l[1], l[2]);
+      const int wi = wt.sub * WV + Win<D>::idx(l[0], l[1], l[2]);
       st_node(rec + (int64_t)i * kNodeVals, (T)win[wi], (T)win[Win<D>::stride + wi], (T)win[2 * Win<D>::stride + wi],
               (T)win[3 * Win<D>::stride + wi]);
     }
     __syncthreads();
   }
+}
+
+template <typename T, int D, bool DET, int BLK, bool GATHER>
+__global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
+k_p2g(KCfg c, Bufs b, TileList tl, const void* st_in, void* st_out, T* __restrict__ stg, T* __restrict__ gout,
+      ActiveSet act, T* __restrict__ tau_out, GatherArgs<T> q2) {
+  constexpr int MOST = BLK / kBlock;                       // tiles at once, at most
+  __shared__ double win[MOST * Win<D>::stride * kNodeVals];
+  __shared__ RunLDS<T, BLK> rl;
+  __shared__ uint32_t tile_slot;
+  const uint32_t ntiles = *tl.count;
+  if (MOST > 1 && share_workgroup<T, BLK>(c, ntiles))
+    p2g_tiles<T, D, DET, BLK, GATHER, MOST>(c, b, tl, st_in, st_out, stg, gout, act, tau_out, q2, ntiles, win, rl, &tile_slot);
+  else
+    p2g_tiles<T, D, DET, BLK, GATHER, 1>(c, b, tl, st_in, st_out, stg, gout, act, tau_out, q2, ntiles, win, rl, &tile_slot);
   finish_tiles(tl);
 }
 
@@ -1676,11 +1737,11 @@ __device__ __forceinline__ void load_adj_part(const P<T, D>& st, const Adj<T, D>
 }
 
 // The G2P adjoint of particle p: x bar to ac, its record for the scatter to
-// rl; returns the node of the window that its stencil starts at, -1 when the
-// particle lies outside the window (and scattered to the grid itself).
+// rl; returns the node of the window (at win0) that its stencil starts at, -1 when
+// the particle lies outside the window (and scattered to the grid itself).
 template <typename T, int D, int BLK>
 __device__ __forceinline__ int g2p_adj_particle(const KCfg& c, const int (&org)[3], T dt, const T* g, T* gbv,
-                                                const T (*gwin)[kNodeVals], RunLDS<T, BLK>& rl, const AdjPart<T, D>& part,
+                                                const T (*gwin)[kNodeVals], int win0, RunLDS<T, BLK>& rl, const AdjPart<T, D>& part,
                                                 const Adj<T, D>& ac, uint32_t p) {
   const T dx = T(c.dx), inv_dx = T(c.inv_dx), Dk = T(4.0 * c.inv_dx * c.inv_dx);
   int wb = -1;
@@ -1759,7 +1820,7 @@ __device__ __forceinline__ int g2p_adj_particle(const KCfg& c, const int (&org)[
          [&](int o0, int o1, int o2, int64_t) {
            return ld_node(gwin[wn0 + (D == 3 ? (o0 * kWin + o1) * kWin + o2 : o0 * kWin + o1)]);
          });
-    wb = Win<D>::idx(loc[0], loc[1], loc[2]);
+    wb = win0 + Win<D>::idx(loc[0], loc[1], loc[2]);
     put_record<T, D, BLK>(rl, fresh_thread<BLK>(), q, B, S.w);
   } else {
     body(std::integral_constant<int, 1>(), [&](int, int, int, int64_t nd, T w, const T (&t)[3]) {
@@ -1797,19 +1858,19 @@ __device__ __forceinline__ int g2p_adj_particle(const KCfg& c, const int (&org)[
 // against 48 us at 219 488, 224 against 205 at 1.8 M): tiles fill fewer compute
 // units and lanes than the P2G adjoint does by itself.
 // ---------------------------------------------------------------------------
-template <typename T, int D, bool DET, int BLK>
-__global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) k_g2p_adj(KCfg c, Bufs b, TileList tl, const void* stv,
-                                                 const T* __restrict__ post, const void* adj_next, void* adj_cur,
-                                                 T* __restrict__ gvb, T* __restrict__ stg) {
-  __shared__ double win[Win<D>::stride * D];
-  __shared__ RunLDS<T, BLK> rl;
-  __shared__ alignas(16) T gwin[Win<D>::nodes][kNodeVals];     // grid velocities of the tile's window
-  const uint32_t ntiles = *tl.count;
-  constexpr int WS = Win<D>::stride;
+template <typename T, int D, bool DET, int BLK, int TILES>
+__device__ __forceinline__ void g2p_adj_tiles(const KCfg& c, const Bufs& b, const TileList& tl, const void* stv,
+                                              const T* __restrict__ post, const void* adj_next, void* adj_cur,
+                                              T* __restrict__ gvb, T* __restrict__ stg, uint32_t ntiles, double* win,
+                                              RunLDS<T, BLK>& rl, T (*gwin)[kNodeVals]) {
+  using WT = WaveTile<BLK, TILES>;
+  constexpr int WS = Win<D>::stride, WV = WS * D;          // values of a tile's window
   // a plain grid-stride loop: the work queue's loop form costs this kernel ten
   // registers and a wave per SIMD
-  for (uint32_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    const TileRec tr = tile_record(tl, t);
+  for (uint32_t t0 = blockIdx.x; t0 * TILES < ntiles; t0 += gridDim.x) {
+    const WT wt(tl, t0 * TILES, ntiles);
+    const TileRec& tr = wt.tr;
+    const int cnt = wt.cnt;
     int inst, org[3];
     tile_origin<D>(c, tr.tile, inst, org);
     const InstDev& I = b.inst[inst];
@@ -1818,54 +1879,58 @@ __global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(sizeof
     T* gbv = gvb + I.goff * kNodeVals;
     // the window's grid velocities and the first round's particles are on their
     // way together (nodes outside the grid are never read)
-    constexpr int NST = (Win<D>::nodes + BLK - 1) / BLK;
+    constexpr int NST = (Win<D>::nodes + WT::kThreads - 1) / WT::kThreads;
     Node4<T> nv[NST];
-    const int t0 = fresh_thread<BLK>();
+    const int ti = wt.thread();
+    T(*gw)[kNodeVals] = gwin + wt.sub * Win<D>::nodes;
 #pragma unroll
     for (int k = 0; k < NST; ++k) {
       int l[3];
-      Win<D>::coords(t0 + k * BLK, l);
+      Win<D>::coords(ti + k * WT::kThreads, l);
       const int gi[3] = {org[0] + l[0], org[1] + l[1], D == 3 ? org[2] + l[2] : 0};
-      bool ok = t0 + k * BLK < Win<D>::nodes;
+      bool ok = ti + k * WT::kThreads < Win<D>::nodes;
 #pragma unroll
       for (int a = 0; a < D; ++a) ok &= gi[a] >= 0 && gi[a] < c.n;
       nv[k] = Node4<T>{{T(0), T(0), T(0), T(0)}};
       if (ok) nv[k] = ld_node(at_bytes(g, node_bytes<T, D>(c, gi)));
     }
-    const int cnt = (int)(tr.end - tr.start);
     AdjPart<T, D> part;
     auto load_round = [&](int r0) {
-      if ((int)threadIdx.x < cnt - r0) {
+      const uint32_t p = threadIdx.x % WT::kThreads;
+      if ((int)p < cnt - r0) {
         const int64_t q0 = (int64_t)tr.start + r0;
-        load_adj_part<T, D>(pv<T, D>(stv, c.ntot).at(q0), av<T, D>(adj_next, c.ntot).at(q0), threadIdx.x, part);
+        load_adj_part<T, D>(pv<T, D>(stv, c.ntot).at(q0), av<T, D>(adj_next, c.ntot).at(q0), p, part);
       }
     };
     load_round(0);
-    for (int i = t0; i < WS * D; i += BLK) win[i] = 0.0;
+    for (int i = fresh_thread<BLK>(); i < TILES * WV; i += BLK) win[i] = 0.0;
 #pragma unroll
     for (int k = 0; k < NST; ++k)
-      if (t0 + k * BLK < Win<D>::nodes) st_node(gwin[t0 + k * BLK], nv[k].v[0], nv[k].v[1], nv[k].v[2], nv[k].v[3]);
+      if (ti + k * WT::kThreads < Win<D>::nodes)
+        st_node(gw[ti + k * WT::kThreads], nv[k].v[0], nv[k].v[1], nv[k].v[2], nv[k].v[3]);
     __syncthreads();
-    for (int r0 = 0; r0 < cnt; r0 += BLK) {
-    const int rc = min(BLK, cnt - r0);
+    for (int r0 = 0; r0 < wt.most; r0 += WT::kThreads) {
+    const int rc = min(WT::kThreads, cnt - r0);
     int wb = -1;
     if (r0 > 0) load_round(r0);
-    if (threadIdx.x < rc) {
+    const uint32_t p = threadIdx.x % WT::kThreads;
+    if ((int)p < rc) {
       const int64_t p0 = (int64_t)tr.start + r0;
-      wb = g2p_adj_particle<T, D, BLK>(c, org, dt, g, gbv, gwin, rl, part, av<T, D>(adj_cur, c.ntot).at(p0), threadIdx.x);
+      wb = g2p_adj_particle<T, D, BLK>(c, org, dt, g, gbv, gw, wt.sub * WV, rl, part,
+                                       av<T, D>(adj_cur, c.ntot).at(p0), p);
     }
     rl.wbase[fresh_thread<BLK>()] = wb;
     __syncthreads();
-    run_scatter_round<T, D, D, 9, DET ? (D == 3 ? 27 : 9) : 1, BLK>(rl, rc, win, T(0));
+    run_scatter_round<T, D, D, 9, DET ? (D == 3 ? 27 : 9) : 1, BLK, TILES>(rl, TILES == 1 ? rc : BLK, win, T(0));
     }
     __syncthreads();
-    for (int i = fresh_thread<BLK>(); i < Win<D>::nodes; i += BLK) {
+    for (int i = wt.thread(); i < (wt.have ? Win<D>::nodes : 0); i += WT::kThreads) {
       int l[3];
       Win<D>::coords(i, l);
-      const int wi = Win<D>::idx(l[0], l[1], l[2]);
+      const int wi = wt.sub * WV + Win<D>::idx(l[0], l[1], l[2]);
       if (DET) {
         // the whole window, zeros included, to the tile's record (the layout of P2G's staging)
-        st_node(stg + ((int64_t)t * Win<D>::nodes + i) * kNodeVals, (T)win[wi], (T)win[WS + wi],
+        st_node(stg + ((int64_t)wt.t * Win<D>::nodes + i) * kNodeVals, (T)win[wi], (T)win[WS + wi],
                 D == 3 ? (T)win[2 * WS + wi] : T(0), T(0));
         continue;
       }
@@ -1880,6 +1945,21 @@ __global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(sizeof
     }
     __syncthreads();
   }
+}
+
+template <typename T, int D, bool DET, int BLK>
+__global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
+k_g2p_adj(KCfg c, Bufs b, TileList tl, const void* stv, const T* __restrict__ post, const void* adj_next, void* adj_cur,
+          T* __restrict__ gvb, T* __restrict__ stg) {
+  constexpr int MOST = BLK / kBlock;                       // tiles at once, at most
+  __shared__ double win[MOST * Win<D>::stride * D];
+  __shared__ RunLDS<T, BLK> rl;
+  __shared__ alignas(16) T gwin[MOST * Win<D>::nodes][kNodeVals];     // grid velocities of the tiles' windows
+  const uint32_t ntiles = *tl.count;
+  if (MOST > 1 && share_workgroup<T, BLK>(c, ntiles))
+    g2p_adj_tiles<T, D, DET, BLK, MOST>(c, b, tl, stv, post, adj_next, adj_cur, gvb, stg, ntiles, win, rl, gwin);
+  else
+    g2p_adj_tiles<T, D, DET, BLK, 1>(c, b, tl, stv, post, adj_next, adj_cur, gvb, stg, ntiles, win, rl, gwin);
 }
 
 // The staged windows of the G2P adjoint (deterministic mode) added to the

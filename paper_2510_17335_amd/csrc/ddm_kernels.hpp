@@ -66,6 +66,7 @@ struct KCfg {
   double w_hm, w_mass, m_target, m_ref;
   double w_emd;
   int det;                           // deterministic mode: fixed-order window and reduction sums
+  int cus;                           // compute units of the device
   int wide;                          // tile kernels with kBlock << wide threads per workgroup (wide_tiles in ddm_runtime.hip)
   int bucket_shift;                  // tiles are listed by particle count in buckets of 2^bucket_shift (tile_bucket in ddm_sort.hip)
 };

@@ -733,10 +733,14 @@ ddm_status run_segment(ddm_ctx* x, int m, int64_t k_first, int len, const void* 
   return DDM_OK;
 }
 
-// Per-instance constants (Lame constants from (E, nu), alpha_f and the
-// cohesion shift from the friction angle, particle mass and volume, and their
-// derivatives for the final chain rule), the block-to-instance map, and the
-// pose table with its Jacobian; uploaded with synchronous copies.
+// Compute units of the current device.
+int device_cus() {
+  int dev = 0, cus = 0;
+  const bool ok = hipGetDevice(&dev) == hipSuccess &&
+                  hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0;
+  return ok ? cus : 256;
+}
+
 // Threads per workgroup of P2G and the G2P adjoint, which take a tile each:
 // kBlock << the value returned.  A tile of more particles than threads takes
 // several rounds, one after the other, so wider workgroups are faster while all
@@ -753,20 +757,23 @@ ddm_status run_segment(ddm_ctx* x, int m, int64_t k_first, int len, const void* 
 // 256 tiles they are slower (24.4 -> 26.5 us at 75 712 particles in about 290,
 // 20.4 -> 28.7 at 84 640 in a layer of five cells).  The occupied tiles are not
 // known here: a bed five cells high or more has up to 2.5 per full one and each
-// instance some at its edges.  Below some full tiles there is nothing to gain
-// (15.6 and 15.8 us at 1152 particles).
-int wide_tiles(const ddm_config& c, int64_t ntot, int n_inst) {
-  const double per_tile = c.ppc * 64.0, tiles = c.precision == DDM_F64 ? 256.0 : 512.0;
+// instance some at its edges.  Thinner and scattered beds have more; the kernels
+// see that and let a workgroup take several tiles at once (share_workgroup in
+// ddm_kernels.hip, with the times).  Below some full tiles there is nothing to
+// gain (15.6 and 15.8 us at 1152 particles).
+int wide_tiles(const ddm_config& c, int64_t ntot, int n_inst, int cus) {
+  const double per_tile = c.ppc * 64.0, tiles = (c.precision == DDM_F64 ? 1.0 : 2.0) * cus;
   if (c.dim != 3 || !(per_tile > ddm::kBlock) || !((double)ntot <= tiles * per_tile)) return 0;
   const bool most = c.precision != DDM_F64 && per_tile >= 2 * ddm::kBlock && (double)ntot >= 8.0 * per_tile &&
-                    2.5 * (double)ntot + 8.0 * n_inst * per_tile <= 256.0 * per_tile;
+                    2.5 * (double)ntot + 8.0 * n_inst * per_tile <= (double)cus * per_tile;
   return most ? 2 : 1;
 }
 
 // Kernel configuration of a context (or of a context-free call) with
-// n_inst instances and ntot padded particle slots.
-ddm::KCfg make_kcfg(const ddm_config& c, int n_inst, int64_t ntot) {
+// n_inst instances and ntot padded particle slots on a device of cus compute units.
+ddm::KCfg make_kcfg(const ddm_config& c, int n_inst, int64_t ntot, int cus) {
   ddm::KCfg k;
+  k.cus = cus;
   k.dim = c.dim; k.n = c.n_grid; k.bound = c.bound; k.shovel = c.shovel;
   k.pcontact = c.particle_contact != 0 ? 1 : 0;
   k.nlog2 = 0;
@@ -784,10 +791,11 @@ ddm::KCfg make_kcfg(const ddm_config& c, int n_inst, int64_t ntot) {
   k.w_hm = c.w_hm; k.w_mass = c.w_mass; k.m_target = c.m_target; k.m_ref = c.m_ref;
   k.w_emd = c.w_emd;
   k.det = c.deterministic ? 1 : 0;
-  k.wide = wide_tiles(c, ntot, n_inst);
-  // up to four workgroups of kBlock threads on each of 256 compute units, unless
-  // they take a tile of more than 512 particles in one round or (2D) never meet one
-  k.bucket_shift = c.dim == 3 && k.wide != 2 && (double)ntot <= 1024.0 * 64.0 * c.ppc ? 6 : 5;
+  k.wide = wide_tiles(c, ntot, n_inst, cus);
+  // up to four workgroups of kBlock threads on each compute unit, unless they take
+  // a tile of more than 512 particles in one round or (2D) never meet one (beds of
+  // more tiles than full ones have small tiles, which take the same time either way)
+  k.bucket_shift = c.dim == 3 && k.wide != 2 && (double)ntot <= 4.0 * cus * 64.0 * c.ppc ? 6 : 5;
   return k;
 }
 
@@ -823,6 +831,10 @@ ddm::InstDev make_instdev(const ddm_config& c, const ddm_instance& s, int i, int
   return d;
 }
 
+// Per-instance constants (Lame constants from (E, nu), alpha_f and the
+// cohesion shift from the friction angle, particle mass and volume, and their
+// derivatives for the final chain rule), the block-to-instance map, and the
+// pose table with its Jacobian; uploaded with synchronous copies.
 ddm_status upload_instances(ddm_ctx* x, const ddm_instance* inst) {
   const ddm_config* cfg = &x->cfg;
   const Layout& L = x->L;
@@ -944,7 +956,7 @@ ddm_status ddm_create(const ddm_config* cfg, int32_t n_inst, const ddm_instance*
   x->ws = static_cast<char*>(workspace);
   x->stream = static_cast<hipStream_t>(stream);
   x->prec = cfg->precision == DDM_F64 ? 1 : 0;
-  x->kc = make_kcfg(*cfg, n_inst, L.ntot);
+  x->kc = make_kcfg(*cfg, n_inst, L.ntot, device_cus());
 
   s = upload_instances(x, inst);
   // one synchronous clear: each takes some 50 us of a context's creation
@@ -1396,11 +1408,7 @@ ddm_status ddm_autotune(ddm_ctx* x, const char* cache_path, int32_t* sort_every_
     // nothing between calls.  R first at the default workgroup count, then the
     // workgroup count at that R.
     const int P = std::min<int>(32, x->cfg.max_steps);
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) {
-      hipDeviceProp_t prop;
-      if (hipGetDeviceProperties(&prop, dev) == hipSuccess && prop.multiProcessorCount > 0) cus = prop.multiProcessorCount;
-    }
+    const int cus = x->kc.cus;
     void* snap = x->at(L.seg_state);
     void* pid_snap = x->at(L.seg_perm);
     x->rec_first = INT32_MAX;      // the snapshot overwrites recorded segments
@@ -1692,7 +1700,7 @@ ddm_status ddm_loss_noalloc(const ddm_config* cfg, const ddm_instance* inst, int
   // one instance, one pose row (that of final_step; the kernels read row 0)
   ddm_config c1 = *cfg;
   c1.max_steps = 1;
-  ddm::KCfg kc = make_kcfg(c1, 1, ntot);
+  ddm::KCfg kc = make_kcfg(c1, 1, ntot, 256);   // (no tile kernels)
   const ddm::InstDev dev = make_instdev(*cfg, *inst, 0, 0, 0, kc.nodes);
   double row[ddm::kPoseVals] = {0};
   if (final_step >= 0 && cfg->shovel) {
