@@ -500,9 +500,13 @@ __global__ void __launch_bounds__(kBlock) k_bin_count(KCfg c, Bufs b, const void
     if (!ok) atomicOr(&b.err->flags, 2u);
     tile += (uint32_t)(c.nodes >> (c.dim == 3 ? 6 : 4)) * (uint32_t)i;
   }
+  // the tiles of a sorted wave (one, two at a tile's end) with one atomic each,
+  // one after another; lanes of further tiles, which positions in no order
+  // have, with one each at the same time
   unsigned long long todo = __ballot(live);
   uint32_t r = 0;
-  while (todo) {
+#pragma unroll 1
+  for (int k = 0; k < 8 && todo; ++k) {
     const int lead = __ffsll((long long)todo) - 1;
     const uint32_t t = (uint32_t)__builtin_amdgcn_readlane((int)tile, lead);
     const unsigned long long same = __ballot(live && tile == t);
@@ -512,6 +516,7 @@ __global__ void __launch_bounds__(kBlock) k_bin_count(KCfg c, Bufs b, const void
     if (live && tile == t) r = base + (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
     todo &= ~same;
   }
+  if ((todo >> lane) & 1ull) r = atomicAdd(&tcnt[tile], 1u);
   ck[j] = live ? (tile << (c.dim == 3 ? 6 : 4)) + cell : 0xFFFFFFFFu;
   rank[j] = r;
 }

@@ -74,3 +74,30 @@ def test_time_is_linear(prec):
         ms.append(total / count)
     print("ms per binning", ms, flush=True)
     assert ms[1] <= 30.0 * ms[0]
+
+
+@pytest.mark.parametrize("dim,n_grid", [(2, 64), (3, 64)])
+@pytest.mark.parametrize("tiles", [1, 2, 8, 9, 64])
+def test_waves_of_several_tiles(dim, n_grid, tiles):
+    """Waves whose 64 lanes lie in a given number of tiles, by turns: the first
+    eight are counted tile by tile, the lanes of further ones each by itself.
+    The state is that of the radix sort, bit for bit."""
+    import torch
+
+    import paper_2510_17335_amd as ddm
+    print("case waves", dim, tiles, flush=True)
+    sys.stdout.flush()
+    rng = np.random.default_rng(tiles)
+    inner = np.stack(np.meshgrid(*[np.arange(3, 12)] * dim, indexing="ij"), -1).reshape(-1, dim)
+    n = 700
+    at = inner[rng.permutation(len(inner))[:64]]
+    lane = np.arange(n) % 64 % tiles + (np.arange(n) // 64 * tiles) % 64
+    x = (4 * at[lane % 64] + 0.51 + rng.uniform(0.0, 3.98, size=(n, dim))) / n_grid
+    x = x.astype(np.float32).astype(np.float64)
+    states = []
+    for det in (False, True):
+        sim = _sim(ddm, [n], x, det, dim=dim)
+        sim.step(1)
+        assert sim.check().flags == 0
+        states.append(sim.get_state())
+    assert torch.equal(states[0].view(torch.int32), states[1].view(torch.int32))
