@@ -202,6 +202,17 @@ __device__ __forceinline__ Node4<double> ld_node(const Global<double>* p) {
   const D2 a = ((const Global<D2>*)p)[0], b = ((const Global<D2>*)p)[1];
   return Node4<double>{{a.x, a.y, b.x, b.y}};
 }
+// The first D values of a node (its velocity) alone.
+template <int D> __device__ __forceinline__ Node4<float> ld_velocity(const Global<float>* p) {
+  typedef float FD __attribute__((ext_vector_type(D)));
+  const FD q = *(const Global<FD>*)p;
+  return Node4<float>{{q.x, q.y, D == 3 ? q[D - 1] : 0.f, 0.f}};
+}
+template <int D> __device__ __forceinline__ Node4<double> ld_velocity(const Global<double>* p) {
+  typedef double D2 __attribute__((ext_vector_type(2)));
+  const D2 a = *(const Global<D2>*)p;
+  return Node4<double>{{a.x, a.y, D == 3 ? p[2] : 0.0, 0.0}};
+}
 __device__ __forceinline__ void st_node(float* p, float a, float b, float c, float d) {
   *reinterpret_cast<float4*>(p) = make_float4(a, b, c, d);
 }
@@ -758,8 +769,10 @@ __device__ __forceinline__ void particle_collision(const KCfg& c, const Bufs& b,
 // of its instance, the particle-level collision when PC, and the advanced
 // position.  Returns false when the advance leaves the fixed-point range or
 // the result is not finite (the caller flags it).  Computing everything
-// before the stores keeps the kernel at few registers.
-template <typename T, int D, bool PC>
+// before the stores keeps the kernel at few registers.  WHOLE: nodes are loaded
+// with their mass (one wide load); without it a load in flight holds a quarter
+// fewer registers.
+template <typename T, int D, bool PC, bool WHOLE>
 __device__ __forceinline__ bool g2p_compute(const KCfg& c, const Bufs& b, int inst, int step,
                                             const typename Pos<T>::X (&xr)[3], const Stencil<T, D>& S,
                                             const T* __restrict__ g, T (&vn)[3], T (&Cn)[3][3],
@@ -789,7 +802,8 @@ __device__ __forceinline__ bool g2p_compute(const KCfg& c, const Bufs& b, int in
 #pragma unroll
       for (int ol = 0; ol < 3; ++ol) {
         const T wl = S.w[D - 1][ol], wr = wl * rr[D - 1][ol];
-        const Node4<T> nd = ld_node(at_bytes(row, nb) + ol * kNodeVals);
+        const Global<T>* node = at_bytes(row, nb) + ol * kNodeVals;
+        const Node4<T> nd = WHOLE ? ld_node(node) : ld_velocity<D>(node);
 #pragma unroll
         for (int a = 0; a < D; ++a) { u[a] += wl * nd.v[a]; ul[a] += wr * nd.v[a]; }
       }
@@ -837,7 +851,7 @@ __device__ __forceinline__ bool gather_part(const KCfg& c, const Bufs& b, int in
   if (!make_stencil<T, D>(xr, c, S)) { flag_error(b.err, 2u, inst); return false; }
   T vn[3];
   const T* g = ga.post + (int64_t)inst * c.nodes * kNodeVals;
-  if (!g2p_compute<T, D, false>(c, b, inst, ga.step, xr, S, g, vn, q.C, xn)) flag_error(b.err, 1u, inst);
+  if (!g2p_compute<T, D, false, true>(c, b, inst, ga.step, xr, S, g, vn, q.C, xn)) flag_error(b.err, 1u, inst);
 #pragma unroll
   for (int a = 0; a < D; ++a) {
     si.xr(a, p) = xn[a];
@@ -1241,9 +1255,12 @@ void launch_grid_update(int prec, const KCfg& c, const Bufs& b, int step, const 
 // PC: with the particle-level collision (a separate instance, so that the
 // plain kernel keeps its register budget).
 // In FP32 without the particle-level collision the kernel fits 64 registers
-// with no spills: 8 waves per SIMD, more gathers in flight.  It is bound by
-// memory: 45 us for 1.8 M particles, 120 B each, against 36 us for a copy of
-// those bytes at 6 TB/s.
+// with no spills: 8 waves per SIMD, more gathers in flight.  For that the nodes
+// are loaded without their masses; whole, they cost it three spills and most of
+// the loads in flight: 7.1 -> 4.3 us at 27 440 particles, 46.5 -> 39.6 at 1.8 M
+// (joined with P2G, at 128 registers, the whole nodes are faster: 31.9 against 35.6 us
+// per launch at 219 488, 129 against 145).  It is bound by memory: 120 B a particle, 36 us for
+// a copy of those bytes of 1.8 M particles at 6 TB/s.
 template <typename T, int D, bool PC>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(PC || sizeof(T) == 8 ? 1 : 8)))
 k_g2p(KCfg c, Bufs b, int step, const void* st_in, void* st_out, const T* __restrict__ post) {
@@ -1264,7 +1281,7 @@ k_g2p(KCfg c, Bufs b, int step, const void* st_in, void* st_out, const T* __rest
   for (int a = 0; a < D; ++a) xr[a] = si.xr(a, p);
   if (!make_stencil<T, D>(xr, c, S)) { flag_error(b.err, 2u, inst); return; }
   T vn[3], Cn[3][3];
-  const bool ok = g2p_compute<T, D, PC>(c, b, inst, step, xr, S, post + (int64_t)inst * c.nodes * kNodeVals, vn, Cn, xn);
+  const bool ok = g2p_compute<T, D, PC, false>(c, b, inst, step, xr, S, post + (int64_t)inst * c.nodes * kNodeVals, vn, Cn, xn);
 #pragma unroll
   for (int a = 0; a < D; ++a) {
     so.xr(a, p) = xn[a];
