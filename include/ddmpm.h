@@ -296,8 +296,11 @@ ddm_status ddm_pass(ddm_ctx* ctx, const void* x0_dev, int32_t n_steps, const dou
  * probed.  The state is
  * restored, and a recorded rollout, its loss and its checkpoints stay valid.
  * With cache_path != NULL, a line "ddmpm dim=.. n_grid=.. prec=.. n_inst=..
- * particles=.. ppc=.. sort_every=R tile_workgroups=W" for this problem is
- * looked up first (no probe when found) and appended after a probe.  The
+ * particles=.. ppc=.. deterministic=.. particle_contact=.. kernels=..
+ * sort_every=R tile_workgroups=W" for this problem is looked up first (no probe
+ * when found) and appended after a probe.  kernels is a number that a library
+ * with other costs raises, so that it does not take an older one's choice; the two
+ * options decide which launches there are.  The
  * chosen R is written to *sort_every_out (may be NULL) and both values are
  * readable with ddm_get_launch.  Synchronises the stream.  DDM_ESTATE before
  * ddm_init_state.  The results do not depend on R or W beyond the order of

@@ -1379,6 +1379,11 @@ ddm_status ddm_pass(ddm_ctx* x, const void* x0_dev, int32_t n_steps, const doubl
   return DDM_OK;
 }
 
+// Which kernels a cached launch configuration was timed with: raised when a
+// change moves the best interval (2: sub-steps without a binning join G2P and
+// P2G, and binnings cost a quarter of what they did).
+constexpr int kTunedKernels = 2;
+
 ddm_status ddm_autotune(ddm_ctx* x, const char* cache_path, int32_t* sort_every_out) {
   Phase phase("ddm_autotune");
   if (!x) return fail(DDM_EINVAL, "NULL context");
@@ -1388,7 +1393,8 @@ ddm_status ddm_autotune(ddm_ctx* x, const char* cache_path, int32_t* sort_every_
   for (const auto& in : x->inst) n_part += in.n_particles;
   std::ostringstream key;
   key << "ddmpm dim=" << x->cfg.dim << " n_grid=" << x->cfg.n_grid << " prec=" << x->prec << " n_inst=" << x->n_inst
-      << " particles=" << n_part << " ppc=" << x->cfg.ppc;
+      << " particles=" << n_part << " ppc=" << x->cfg.ppc << " deterministic=" << x->kc.det
+      << " particle_contact=" << x->kc.pcontact << " kernels=" << kTunedKernels;
   int best = -1, best_w = 0;
   if (cache_path) {
     std::ifstream f(cache_path);
