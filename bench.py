@@ -160,14 +160,38 @@ def algorithmic_bytes_p2g_joined(n_particles, n_active, recorded, b=4, d=3):
     return n_particles * per_particle + n_active * (2 * d + 1) * b
 
 
-def algorithmic_bytes_p2g_mean(n_particles, n_active, sort_every, recorded=0.0, period=None, b=4, d=3):
-    """Mean over the P2G launches of a run that bins every sort_every sub-steps
-    (0: once) and at the start of every period sub-steps."""
-    period = period or max(1, sort_every)
-    bins = -(-period // sort_every) if sort_every else 1
-    plain = min(1.0, bins / period)
-    return plain * algorithmic_bytes_p2g(n_particles, n_active, b, d) \
-        + (1.0 - plain) * algorithmic_bytes_p2g_joined(n_particles, n_active, recorded, b, d)
+def p2g_launches(steps, sort_every, checkpoint_every=None, record_segments=0, joins=True):
+    """(plain, joined, joined and recorded) P2G launches of a forward run of
+    `steps` sub-steps from the initial state, or, with checkpoint_every, of a
+    pass: every segment is run as the reverse pass needs it once, the last
+    record_segments by the rollout and the others as replays of an unrecorded run.
+    A sub-step's P2G is launched by itself where the sub-step bins: every
+    sort_every sub-steps of the run (0: never) and at the start of every segment.
+    joins=False (the deterministic mode, particle contact): all are."""
+    K = checkpoint_every or steps
+
+    def plain(first, last):
+        return sum(1 for i in range(first, last) if i % K == 0 or (sort_every and i % sort_every == 0))
+
+    if checkpoint_every:
+        unrecorded = max(0, -(-steps // K) - record_segments) * K
+        whole = steps
+    else:
+        unrecorded, whole = steps, 0
+    if not joins:
+        return unrecorded + whole, 0, 0
+    p_whole = plain(0, whole)
+    p = plain(0, unrecorded) + p_whole
+    return p, unrecorded + whole - p, whole - p_whole
+
+
+def algorithmic_bytes_p2g_mean(n_particles, n_active, launches, b=4, d=3):
+    """Mean over the launches counted by p2g_launches."""
+    plain, joined, recorded = launches
+    total = plain * algorithmic_bytes_p2g(n_particles, n_active, b, d)
+    if joined:
+        total += joined * algorithmic_bytes_p2g_joined(n_particles, n_active, recorded / joined, b, d)
+    return total / (plain + joined)
 
 
 def algorithmic_bytes_pass(n_particles, n_active, b=4, d=3):
@@ -493,6 +517,7 @@ def forward_bench(args, torch, ddm):
     sim.set_timing(False)
     breakdown = breakdown or timing
     err = sim.check()
+    joins = not (sim.cfg.deterministic or sim.cfg.particle_contact)
     value = n * steps * args.steps / elapsed
     print(f"# batched forward: {1e3 * elapsed / args.steps:.2f} ms/step, {value:.3e} particle-steps/s, "
           f"device flags {err.flags}", flush=True)
@@ -516,7 +541,10 @@ def forward_bench(args, torch, ddm):
         print(f"# plain loop: {t_plain * 1e3:.1f} ms/step, {plain_value:.3e} particle-steps/s", flush=True)
 
     p2g_ms, p2g_n = timing["p2g"]
-    per_launch = algorithmic_bytes_p2g_mean(n, n_act, R, period=None if R else steps, b=b, d=d)
+    launches = p2g_launches(steps, R, joins=joins)
+    if p2g_n != args.steps * (launches[0] + launches[1]):
+        print(f"# P2G launches timed: {p2g_n}, by the schedule {args.steps} x {launches[0] + launches[1]}", flush=True)
+    per_launch = algorithmic_bytes_p2g_mean(n, n_act, launches, b=b, d=d)
     achieved = per_launch / (p2g_ms / p2g_n * 1e-3) / 1e9 if p2g_n else None
     fwd_bytes = algorithmic_bytes_forward(n, n_act, b, d)
     bound = HBM_PEAK_GBS * 1e9 / fwd_bytes
@@ -654,9 +682,11 @@ def main():
     dom = max(breakdown, key=lambda k: breakdown[k][0])
     p2g_ms, p2g_n = timing["p2g"]
     esz = 8 if args.precision == "f64" else 4
-    per_launch_bytes = algorithmic_bytes_p2g_mean(
-        n_part, n_act, R, recorded=min(1.0, ws[0].steps * args.steps / p2g_n) if p2g_n else 0.0,
-        period=ws[0].checkpoint_every, b=esz)
+    launches = p2g_launches(ws[0].steps, R, ws[0].checkpoint_every or 50, rseg,
+                            joins=not (bp.sim.cfg.deterministic or bp.sim.cfg.particle_contact))
+    if p2g_n != args.steps * (launches[0] + launches[1]):
+        print(f"# P2G launches timed: {p2g_n}, by the schedule {args.steps} x {launches[0] + launches[1]}", flush=True)
+    per_launch_bytes = algorithmic_bytes_p2g_mean(n_part, n_act, launches, b=esz)
     achieved = per_launch_bytes / (p2g_ms / p2g_n * 1e-3) / 1e9 if p2g_n else None
     breakdown = {k: {"ms": round(v[0], 3), "launches": v[1]} for k, v in breakdown.items() if v[1]}
 
