@@ -101,3 +101,31 @@ def test_gradient(prec, parts):
     assert np.all(np.abs(g1).max(axis=1) > 0)
     tol = 1e-8 if prec == "f64" else 1e-4
     assert np.all(np.abs(g0 - g1) <= tol * np.abs(g1).max(axis=1, keepdims=True)), (g0, g1)
+
+
+@pytest.mark.parametrize("prec,parts", [CASES[2], CASES[4], CASES[6]])
+def test_work_queue(prec, parts):
+    """The same from persistent workgroups that draw groups of tiles from the
+    queue (tile_workgroups), launched twice so that the queue's reset shows: FP32
+    states bit for bit, FP64 to the order of sums."""
+    import torch
+
+    import paper_2510_17335_amd as ddm
+    print("case shared queue", prec, parts, flush=True)
+    sys.stdout.flush()
+    states = []
+    for workgroups in (0, 7, 97):
+        cfg = ddm.make_config(3, N_GRID, prec, ppc=8.0, max_steps=8, checkpoint_every=2, sort_every=2)
+        cfg.tile_workgroups = workgroups
+        sim = ddm.Simulator(cfg, [ddm.make_instance(n, dt=1e-5, rho=1500.0 + 400.0 * i)
+                                  for i, (_, n, _) in enumerate(parts)])
+        rng = np.random.default_rng(5)
+        sim.init_state(np.concatenate([_positions(rng, *p) for p in parts]))
+        sim.step(5)
+        assert sim.check().flags == 0
+        states.append(sim.get_state())
+    for other in states[1:]:
+        if prec == "f32":
+            assert torch.equal(states[0].view(torch.int32), other.view(torch.int32))
+        else:
+            assert torch.linalg.norm(states[0] - other) <= 1e-13 * torch.linalg.norm(states[0])
