@@ -35,7 +35,8 @@ template <typename T> __device__ __forceinline__ T dabs(T x) { return x < T(0) ?
 // y (1 + e/2 + 3 e^2/8) of the residuals e = 1 - x r, 1 - x y^2, whose e^3 is
 // below the rounding: within 2 ulp, 5 and 7 instructions, where the correctly
 // rounded division takes 11 and the root 16.  v_div_fixup puts in the results
-// for zero, infinity and NaN; frsq's result for zero is not used.
+// for zero, infinity and NaN.  frsq has no such step: NaN for zero (whose result
+// is not used) and for infinity (the square of a difference of 1e154).
 template <typename T> __device__ __forceinline__ T frcp(T x);
 template <> __device__ __forceinline__ float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
 template <> __device__ __forceinline__ double frcp(double x) {

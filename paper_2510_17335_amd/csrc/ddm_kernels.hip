@@ -265,9 +265,9 @@ __device__ __forceinline__ void wave_accumulate(const double (&v)[N], double* ds
 
 // The accumulator slot of this workgroup among its instance's kAccSlots (8
 // doubles each, summed by k_grad_final).  Additions to one address follow one
-// another at about 10 ns: with one slot per instance the 857 workgroups of the
-// P2G adjoint of 219 488 particles took 27.7 us, with 64 slots 24.4 us, and the
-// 7031 of 1.8 M particles 128 and 120 us.
+// another at about 10 ns: with one slot per instance the P2G adjoint took 27.7 us
+// at 219 488 particles and 128 at 1.8 M, with 64 slots 24.4 and 120 (in workgroups
+// of 256 threads, 857 and 7041; those of 64 add four times as often).
 __device__ __forceinline__ double* acc_slot(double* pacc, int inst) {
   return pacc + ((int64_t)inst * kAccSlots + (blockIdx.x & (kAccSlots - 1))) * 8;
 }
@@ -466,7 +466,8 @@ __device__ __forceinline__ bool p2g_particle(const KCfg& c, const Bufs& b, const
 }
 
 // ---------------------------------------------------------------------------
-// Run-based window scatter of one round of up to kBlock sorted particles.
+// Run-based window scatter of one round: up to BLK sorted particles of a tile,
+// or up to kBlock of each of several.
 // Phase 1 (the caller): thread t handles slot t of the round and leaves in
 // LDS the particle's q (D values), B (D x D) and fractional position f, and
 // wbase[t] = the window index of its stencil base (-1: nothing to scatter).
@@ -883,7 +884,7 @@ __device__ __forceinline__ bool gather_part(const KCfg& c, const Bufs& b, int in
 // does not bin first needs no state but x and G in memory then: 96 B per
 // particle instead of 204 (168 instead of 228 while recording).  Bound by the
 // latency of its chain at four waves per SIMD (128 registers), at large sizes by
-// the vector units (70 % busy, 2025 instructions per 64 particles): 130 us at
+// the vector units (67 % busy, 2000 instructions per 64 particles): 130 us at
 // 1.8 M particles against 99 and 46 us for the two launches, 31 against 25 and
 // 12 at 219 488.  Loading the first tile's record with the count changed nothing.
 // TILES: the tiles that a workgroup takes at once (share_workgroup).
