@@ -463,9 +463,10 @@ void launch_active_set(const KCfg& c, const TileList& tl, const ActiveSet& act, 
 //   k_bin_order  a workgroup per tile: order by (cell, slot), permutation,
 //                gather of the state rows and ids.
 // The radix sort takes 23 to 31 launches and copies for the same, 4 to 5 us
-// each whatever their size: about 130 us per binning of 27 440 particles on a
-// 64^3 grid against 38 us here, and about 340 us for 3.5 M particles of 32
-// instances against 240 us (most of both the 192 B per particle of the gather).
+// each whatever their size: 125 us of kernels per binning of 28 880 particles on
+// a 64^3 grid against 31 us here, 124 against 36 at 219 488, 260 against 125 at
+// 1.8 M and 390 against 242 for 3.5 M particles of 32 instances (most of it the
+// 192 B per particle of the gather).
 // ---------------------------------------------------------------------------
 constexpr int kOrderCap = 2048;           // particles of a tile that k_bin_order holds in LDS
 constexpr int kOrderStep = 1024;          // and that it takes at a time of a tile of more
