@@ -20,9 +20,19 @@
 
 namespace ddm {
 
+// A lane's integer, opaque to the compiler: it is put into a vector register where it
+// is used, and what is computed from it is computed there, instead of being held
+// in registers (or scratch) from before a kernel's loops.
+__device__ __forceinline__ int fresh_lane(int v) {
+#ifdef __HIP_DEVICE_COMPILE__
+  asm volatile("" : "+v"(v));
+#endif
+  return v;
+}
+
 __device__ __forceinline__ void flag_error(DevErr* e, unsigned int bit, int inst) {
   const unsigned int old = atomicOr(&e->flags, bit);
-  if (old == 0) atomicExch(&e->first_inst, (unsigned int)inst);
+  if (old == 0) atomicExch(&e->first_inst, (unsigned int)fresh_lane(inst));
 }
 
 // Tiles of a tile kernel.  Without a queue, workgroup b takes tiles b, b +
@@ -53,16 +63,10 @@ __device__ __forceinline__ TileRec tile_record(const TileList& tl, uint32_t t) {
   return TileRec{(uint32_t)__builtin_amdgcn_readfirstlane(r.start), (uint32_t)__builtin_amdgcn_readfirstlane(r.end),
                  (uint32_t)__builtin_amdgcn_readfirstlane(r.tile)};
 }
-// The thread's index, opaque to the compiler: what is computed from it is
-// computed where it is used instead of being held in registers (or scratch)
-// from before a kernel's loops.
+// The thread's index, opaque in the same way.
 template <int BLK> __device__ __forceinline__ int fresh_thread() {
-  int t = (int)threadIdx.x;
-#ifdef __HIP_DEVICE_COMPILE__
-  asm volatile("" : "+v"(t));
-#endif
   static_assert((BLK & (BLK - 1)) == 0, "the mask bounds the index");
-  return t & (BLK - 1);
+  return fresh_lane((int)threadIdx.x) & (BLK - 1);
 }
 
 // Whether workgroups of more than kBlock threads (chosen by the context's size,
@@ -82,7 +86,7 @@ template <int BLK> __device__ __forceinline__ int fresh_thread() {
 template <typename T, int BLK>
 __device__ __forceinline__ bool share_workgroup(const KCfg& c, uint32_t ntiles) {
   constexpr uint32_t per_cu = sizeof(T) == 4 ? 1024 / BLK : 512 / BLK;   // resident workgroups: registers (FP32), LDS (FP64)
-  return BLK > kBlock && ntiles > per_cu * (uint32_t)c.cus && c.ntot <= (int64_t)kBlock * ntiles;
+  return BLK > kBlock && ntiles > per_cu * (uint32_t)c.cus && (uint32_t)(c.ntot / kBlock) <= ntiles;   // (scalar arithmetic)
 }
 
 // The tile of this wave among the TILES that its workgroup takes at once, from
@@ -904,13 +908,14 @@ __device__ __forceinline__ void p2g_tiles(const KCfg& c, const Bufs& b, const Ti
     T* g = gout + I.goff * kNodeVals;
     const T mpt = T(I.mp);
     for (int i = fresh_thread<BLK>(); i < TILES * WV; i += BLK) win[i] = 0.0;
-    if (TILES > 1 && threadIdx.x % kBlock == 0) rl.mass[threadIdx.x / kBlock] = mpt;
+    if (TILES > 1 && wt.thread() == 0) rl.mass[wt.sub] = mpt;
     for (int r0 = 0; r0 < wt.most; r0 += WT::kThreads) {
       const int rc = min(WT::kThreads, wt.cnt - r0);
-      const int64_t p0 = (int64_t)tr.start + r0;
+      // (slots count from the workgroup's first thread: no index of its own per tile)
+      const int64_t p0 = (int64_t)tr.start + r0 - wt.sub * WT::kThreads;
       int wb = -1;
-      if ((int)(threadIdx.x % WT::kThreads) < rc) {
-        const uint32_t p = threadIdx.x % WT::kThreads;
+      if ((int)threadIdx.x < wt.sub * WT::kThreads + rc) {
+        const uint32_t p = threadIdx.x;
         const P<T, D> si = pv<T, D>(st_in, c.ntot).at(p0), so = pv<T, D>(st_out, c.ntot).at(p0);
         Part<T, D> part;
         bool moved = true;
@@ -926,6 +931,12 @@ __device__ __forceinline__ void p2g_tiles(const KCfg& c, const Bufs& b, const Ti
         Stencil<T, D> S;
         T A[3][3], vel[3];
         if (moved && p2g_particle<T, D>(c, b, I, inst, part, late, so, p, S, A, vel, tau_out ? tau_out + p0 : nullptr)) {
+          // the stencil's place in the window; opaque, so that its node of the grid is
+          // formed again where that is needed (outside the window) and not kept
+          int loc[3] = {0, 0, 0};
+          bool inwin = true;
+#pragma unroll
+          for (int a = 0; a < D; ++a) { loc[a] = fresh_lane(S.base[a] - org[a]); inwin &= loc[a] >= 0 && loc[a] <= kWin - 3; }
           // node o receives w_o (q + B o) and w_o m_p with q = m_p v - A f dx and
           // B = A dx (the MLS-MPM momentum m_p v + A (x_i - x_p), x_i - x_p = (o - f) dx)
           T q[3] = {T(0), T(0), T(0)}, B[3][3] = {{T(0), T(0), T(0)}, {T(0), T(0), T(0)}, {T(0), T(0), T(0)}};
@@ -937,17 +948,14 @@ __device__ __forceinline__ void p2g_tiles(const KCfg& c, const Bufs& b, const Ti
             for (int bb = 0; bb < D; ++bb) { B[a][bb] = A[a][bb] * tdx; af += B[a][bb] * S.f[bb]; }
             q[a] = vel[a] - af;
           }
-          int loc[3] = {0, 0, 0};
-          bool inwin = true;
-#pragma unroll
-          for (int a = 0; a < D; ++a) { loc[a] = S.base[a] - org[a]; inwin &= loc[a] >= 0 && loc[a] <= kWin - 3; }
           if (inwin) {
             wb = wt.sub * WV + Win<D>::idx(loc[0], loc[1], loc[2]);
             put_record<T, D, BLK>(rl, fresh_thread<BLK>(), q, B, S.w);
           } else {
-            mark_stencil_blocks<D>(c, inst, S.base, act);
+            const int base[3] = {loc[0] + org[0], loc[1] + org[1], loc[2] + org[2]};
+            mark_stencil_blocks<D>(c, inst, base, act);
             scatter_stencil<T, D>(S.w, q, B, mpt, [&](int o0, int o1, int o2, const T (&v)[4]) {
-              T* dst = g + node_of<D>(S.base, o0, o1, o2, c.n) * kNodeVals;
+              T* dst = g + node_of<D>(base, o0, o1, o2, c.n) * kNodeVals;
 #pragma unroll
               for (int a = 0; a < D; ++a) atomicAdd(dst + a, v[a]);
               atomicAdd(dst + 3, v[3]);
@@ -973,10 +981,12 @@ __device__ __forceinline__ void p2g_tiles(const KCfg& c, const Bufs& b, const Ti
   }
 }
 
-// Workgroups of more than kBlock threads hold both loops: joined, they keep 97
-// scalars and 4 (512 threads) or 14 (1024) vector registers of each lane aside,
-// without a difference in time (forward 4.41 ms for 100 sub-steps at 219 488
-// particles either way, a pass 12.9 against 13.0 ms at 27 440).
+// Workgroups of more than kBlock threads hold both loops; joined, that takes a
+// second vector register for scalars kept aside.  With the particle's registers
+// as they were, 4 (512 threads) and 14 (1024) of them went to scratch as well: 500
+// sub-steps of 219 488 particles 23.50 -> 23.21 ms since the stencil's place is
+// kept in window coordinates alone (the one-tile loop by itself 23.10; one loop
+// with the number of tiles at run time 23.86).
 template <typename T, int D, bool DET, int BLK, bool GATHER>
 __global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
 k_p2g(KCfg c, Bufs b, TileList tl, const void* st_in, void* st_out, T* __restrict__ stg, T* __restrict__ gout,

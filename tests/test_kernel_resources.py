@@ -50,3 +50,14 @@ def test_fits_64_registers_without_scratch(kernels, name):
     assert int(found[0]["vgpr_count"]) <= 64
     assert int(found[0]["vgpr_spill_count"]) == 0
     assert int(found[0]["private_segment_fixed_size"]) == 0
+
+
+# P2G joined with the G2P before it, FP32, 256 and 512 threads: 128 registers, four
+# waves per SIMD, and nothing of a particle in scratch
+@pytest.mark.parametrize("block", [256, 512])
+def test_joined_p2g_without_scratch(kernels, block):
+    found = [m for k, m in kernels.items() if k.startswith(f"_ZN3ddm5k_p2gIfLi3ELb0ELi{block}ELb1EEE")]
+    assert len(found) == 1
+    assert int(found[0]["vgpr_count"]) <= 128
+    assert int(found[0]["vgpr_spill_count"]) == 0
+    assert int(found[0]["private_segment_fixed_size"]) == 0
